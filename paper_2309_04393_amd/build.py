@@ -11,7 +11,10 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT_DIR = os.path.join(HERE, "_lib")
 LIB = os.path.join(OUT_DIR, "libresoct.so")
-SOURCES = ["api.hip", "render.hip", "stream.hip", "octree.hip", "mlp.hip", "prefetch.hip", "serve.hip"]
+# (source, extra flags); the instantiations of render.hip are compiled in parts
+SOURCES = [("render.hip", ["-DRO_PART=4"]), ("render.hip", ["-DRO_PART=3"]), ("render.hip", ["-DRO_PART=2"]),
+           ("render.hip", ["-DRO_PART=1"]), ("serve.hip", []), ("api.hip", []), ("render.hip", ["-DRO_PART=0"]),
+           ("stream.hip", []), ("octree.hip", []), ("mlp.hip", []), ("prefetch.hip", [])]
 
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
@@ -27,9 +30,9 @@ def build(verbose: bool = False, csrc: str = CSRC, lib: str = LIB) -> str:
     os.makedirs(out_dir, exist_ok=True)
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmds, objs = [], []
-    for src in SOURCES:
-        obj = os.path.join(out_dir, src.replace(".hip", ".o"))
-        cmds.append([hipcc, *FLAGS, "-I", os.path.join(ROOT, "include"), "-I", csrc, "-c",
+    for n, (src, extra) in enumerate(SOURCES):
+        obj = os.path.join(out_dir, src.replace(".hip", f"_{n}.o"))
+        cmds.append([hipcc, *FLAGS, *extra, "-I", os.path.join(ROOT, "include"), "-I", csrc, "-c",
                      os.path.join(csrc, src), "-o", obj])
         objs.append(obj)
     if verbose:

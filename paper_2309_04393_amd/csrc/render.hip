@@ -1,15 +1,19 @@
 // Ray-guided mixed-resolution multi-channel ray casting over the residency
 // octree (Sec. 6.1, Alg. 1; Sec. 6.2; Sec. 7 implementation notes).
 //
-// One lane per ray; persistent 768-lane workgroups (one per CU) whose waves
-// take 8 x 8-pixel blocks from per-XCD queues.
+// Four lanes per ray; persistent 768-lane workgroups (one per CU) whose waves
+// take units of 4 x 4 pixels from per-XCD queues.  A ray alternates between
+// visits of a leaf (its four lanes share the leaf's channels) and samples
+// (each lane takes one of the ray's next four).
 // Sample positions and every integer decision derived from them (box, leaf,
 // brick, level) are computed in FP64; interpolation, transfer functions and
-// the channel mix in FP32; the compositing state in FP64.  Per lane, the
+// the channel mix in FP32; the compositing state in FP64, sample after
+// sample, so the image does not depend on the number of lanes.  Per ray, the
 // state of the current (leaf, level) visit is cached: which channels are
 // empty there, the slot each channel samples, and which channels miss their
-// desired brick; misses are counted once per visit with the visit's sample
-// count (one atomic per visit and channel).
+// desired brick; misses are summed while the missing channels and their
+// desired bricks stay the same, over the rays of a wave, before they reach
+// the device counters.
 //
 // Every table a lane indexes with a lane-dependent value (channel
 // parameters, zero-alpha runs, per-level brick grid and LOD thresholds,
@@ -23,22 +27,21 @@
 namespace ro {
 
 // Workgroups of kRenderLanes lanes (768: 3 waves per SIMD, up to 168 VGPRs),
-// one per CU: one copy of the frame's LDS tables plus the per-lane slot
-// words.  The 16-channel instantiations for 16-bit 32^3 and 16^3 bricks
-// without the options keep nothing in scratch; the other 16-channel ones up
-// to 40 bytes per lane, three 8-channel ones 12.  1024 lanes (4 waves per
-// SIMD, 128 VGPRs) spill more and measured 1-10 % slower, 512 lanes 35 %
-// slower.
-
-// Lanes refill only when the whole wave is idle: a wave then takes a whole
-// new 8 x 8 block and its rays start together.  Refilling single lanes as
-// their rays end keeps more lanes busy (91 % against 70 %) but spreads a
-// wave's samples over different depths and cache lines, and measured 3.4x
-// slower on the 16-channel 1080p frame; refilling from 16 idle lanes 1.5x
-// slower.
-#ifndef RO_MIN_IDLE
-#define RO_MIN_IDLE 64
-#endif
+// one per CU: one copy of the frame's LDS tables plus the per-ray words.
+// 1024 lanes (4 waves per SIMD, 128 VGPRs) spill and measured 45 % slower on
+// the 16-channel 1080p frame and twice as slow on 512 x 512 with 4 channels,
+// 512 lanes 5 % slower on both (with one lane per ray).
+//
+// What bounds the frame kernel: on the 16-channel 1080p frame (1024 x 1024 x
+// 192 voxels, half a voxel per pixel, 8.4e8 ray samples) 42.5 ms against 58
+// with one lane per ray in lockstep.  Vector instructions fill two thirds of
+// the issue slots and the address and tag units are busy throughout: 1.2e9
+// gathers of 64 lanes, each 18.5 tag lookups.  Gathers of single 16-bit
+// voxels (8 per channel instead of 4) touch as many lines each and took
+// 70 ms; aligned addresses alone (wrong voxels) save 2 %.  Frames of a few
+// thousand units are bound by their longest rays: four lanes per ray cut
+// those (455 x 256, 16 channels: 10.0 ms -> 2.1; 512 x 512, 4 channels:
+// 5.0 -> 2.2; 64 x 64, one channel: 0.59 -> 0.18).
 
 // Per-XCD block queues: blocks are dealt to them in chunks of RO_CHUNK
 // consecutive blocks (16 chunks per queue at 1080p).  On the 16-channel
@@ -51,33 +54,34 @@ namespace ro {
 #define RO_CHUNK 256
 #endif
 
-// Persistent grid (one workgroup per CU) whose waves take 8 x 8-pixel blocks
+// Persistent grid (one workgroup per CU) whose waves take units of pixels
 // from a device counter independently of each other, so a CU never waits
 // for the slowest wave of a workgroup before taking new work.
-template <int NV, int BPV, bool AOV, int EC, int EXT>
+template <int NV, int BPV, bool AOV, int EC, int EXT, int P>
 __global__ void __launch_bounds__(kRenderLanes) __attribute__((amdgpu_waves_per_eu(kRenderLanes / 256)))
-    k_render(const RenderArgs A, uint32_t *counter, uint32_t n_blocks, uint32_t tiles_x) {
-    extern __shared__ float4 s_tf[];  // [NV][kTfStride] tables, then [NV][kRenderLanes] slot words
+    k_render(const RenderArgs A, uint32_t *counter, uint32_t n_blocks, uint32_t tiles_x, uint32_t chunk,
+             uint32_t n_waves) {
+    extern __shared__ float4 s_tf[];  // tables, per-ray words, miss tables (render_lds_bytes)
     __shared__ ChanLds s_ch[NV];
+    __shared__ ChanPar<NV> s_par;
     __shared__ uint32_t s_runs[NV * kMaxRuns];
     __shared__ LevLds s_lv[kMaxL];
     __shared__ NodeLds s_nd[kMaxD + 1];
 
-    stage_frame<NV>(A, s_tf, s_ch, s_runs, s_lv, s_nd);
+    stage_frame<NV>(A, s_tf, s_ch, &s_par, s_runs, s_lv, s_nd);
+    if ((threadIdx.x >> 6) >= n_waves) return;  // a small frame: its blocks are spread over the CUs
 
-    BlockQueue q;
+    UnitQueue<P> q;
     q.counter = counter;
-    q.n_blocks = n_blocks;
+    q.n_units = n_blocks * P;
     q.offset = 0;
     q.tiles_x = tiles_x;
     q.n_queues = RO_QUEUES;
-    q.chunk = RO_CHUNK;
+    q.chunk = chunk;
     q.W = A.W;
     q.H = A.H;
-    q.min_idle = RO_MIN_IDLE;
     uint32_t st[7] = {0, 0, 0, 0, 0, 0, 0};
-    const LdsSlots sl{(uint32_t *)(s_tf + kTfStride * NV) + threadIdx.x, (uint32_t)kRenderLanes};
-    render_rays<NV, BPV, AOV, EC, EC == 0, EXT>(A, q, s_tf, s_ch, s_runs, s_lv, s_nd, st, sl);
+    render_rays<NV, BPV, AOV, EC, EXT, P>(A, q, s_tf, s_ch, &s_par, s_runs, s_lv, s_nd, st);
     if (A.stats) {
         // every lane of the workgroup is here: reduce over the wave, one atomic per wave
 #pragma unroll
@@ -90,53 +94,96 @@ __global__ void __launch_bounds__(kRenderLanes) __attribute__((amdgpu_waves_per_
     }
 }
 
+// Lanes per ray: four, each taking the next of four consecutive samples of
+// its ray and a quarter of a visit's channels; the diagnostic outputs are
+// recorded sample after sample and take one lane per ray.
+constexpr int lanes_per_ray(bool aov) { return aov ? 1 : 4; }
+
 struct QueueLaunch {
     dim3 grid;
     uint32_t *counter;
-    uint32_t n_blocks, tiles_x;
+    uint32_t n_blocks, tiles_x, chunk, n_waves;
 };
 
-template <int NV, int BPV, bool AOV, int EC, int EXT = 0>
+template <int NV, int BPV, bool AOV, int EC, int EXT>
 static hipError_t launch_one(const RenderArgs &A, const QueueLaunch &Q, hipStream_t s) {
-    const size_t lds = render_lds_bytes(NV, (EXT & 1) != 0);
-    hipError_t e = hipFuncSetAttribute((const void *)k_render<NV, BPV, AOV, EC, EXT>,
+    constexpr int P = lanes_per_ray(AOV);
+    const size_t lds = render_lds_bytes(NV, P);
+    hipError_t e = hipFuncSetAttribute((const void *)k_render<NV, BPV, AOV, EC, EXT, P>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_render<NV, BPV, AOV, EC, EXT>), Q.grid, dim3(kRenderLanes), lds, s, A, Q.counter, Q.n_blocks,
-                       Q.tiles_x);
+    hipLaunchKernelGGL((k_render<NV, BPV, AOV, EC, EXT, P>), Q.grid, dim3(kRenderLanes), lds, s, A, Q.counter, Q.n_blocks,
+                       Q.tiles_x, Q.chunk, Q.n_waves);
     return hipGetLastError();
 }
 
 // Compile-time brick edges: 32^3 and 16^3 bricks with their halo (the AOV
-// diagnostic output and the LOD-adaptive step take the generic kernel).
+// diagnostic output takes the generic kernel).
 // Render-and-skip of homogeneous nodes (EXT bit 0) and per-channel sampling
 // rates (EXT bit 1) have instantiations of their own, so the kernels that do
 // not take them carry none of their code.
+template <int NV, int BPV, int EXT>
+static hipError_t launch_edge(const RenderArgs &A, const QueueLaunch &Q, hipStream_t s) {
+    if (A.E == 34) return launch_one<NV, BPV, false, 34, EXT>(A, Q, s);
+    if (A.E == 18) return launch_one<NV, BPV, false, 18, EXT>(A, Q, s);
+    return launch_one<NV, BPV, false, 0, EXT>(A, Q, s);
+}
+
+// The instantiations are compiled in five parts, one object file each
+// (RO_PART 0 to 4; unset: all in one): the host side, 8- and 16-bit voxels without
+// and with the options.
+template <int BPV>
+hipError_t launch_plain(const RenderArgs &A, const QueueLaunch &Q, hipStream_t s);
+template <int BPV>
+hipError_t launch_options(const RenderArgs &A, bool aov, const QueueLaunch &Q, hipStream_t s);
+
+#if !defined(RO_PART) || RO_PART == 1 || RO_PART == 2
+template <int BPV>
+hipError_t launch_plain(const RenderArgs &A, const QueueLaunch &Q, hipStream_t s) {
+    if (A.nvis <= 1) return launch_edge<1, BPV, 0>(A, Q, s);
+    if (A.nvis <= 2) return launch_edge<2, BPV, 0>(A, Q, s);
+    if (A.nvis <= 4) return launch_edge<4, BPV, 0>(A, Q, s);
+    if (A.nvis <= 8) return launch_edge<8, BPV, 0>(A, Q, s);
+    return launch_edge<16, BPV, 0>(A, Q, s);
+}
+#if !defined(RO_PART) || RO_PART == 1
+template hipError_t launch_plain<1>(const RenderArgs &, const QueueLaunch &, hipStream_t);
+#endif
+#if !defined(RO_PART) || RO_PART == 2
+template hipError_t launch_plain<2>(const RenderArgs &, const QueueLaunch &, hipStream_t);
+#endif
+#endif
+
+#if !defined(RO_PART) || RO_PART == 3 || RO_PART == 4
 template <int NV, int BPV>
-static hipError_t launch_nv(const RenderArgs &A, bool aov, const QueueLaunch &Q, hipStream_t s) {
+static hipError_t launch_opt(const RenderArgs &A, bool aov, const QueueLaunch &Q, hipStream_t s) {
     if (aov) return launch_one<NV, BPV, true, 0, 3>(A, Q, s);
-    if (A.flags & RO_RENDER_ADAPTIVE_STEP) {
-        if (A.flags & RO_RENDER_HOMOGENEOUS) return launch_one<NV, BPV, false, 0, 1>(A, Q, s);
-        if (A.flags & RO_RENDER_CHANNEL_RATES) return launch_one<NV, BPV, false, 0, 2>(A, Q, s);
-        return launch_one<NV, BPV, false, 0>(A, Q, s);
-    }
-    if (A.flags & RO_RENDER_HOMOGENEOUS) {
-        if (A.E == 34) return launch_one<NV, BPV, false, 34, 1>(A, Q, s);
-        if (A.E == 18) return launch_one<NV, BPV, false, 18, 1>(A, Q, s);
-        return launch_one<NV, BPV, false, 0, 1>(A, Q, s);
-    }
-    if (A.E == 34) return launch_one<NV, BPV, false, 34>(A, Q, s);
-    if (A.E == 18) return launch_one<NV, BPV, false, 18>(A, Q, s);
-    return launch_one<NV, BPV, false, 0>(A, Q, s);
+    if (A.flags & RO_RENDER_HOMOGENEOUS) return launch_edge<NV, BPV, 1>(A, Q, s);
+    return launch_edge<NV, BPV, 2>(A, Q, s);
 }
 
 template <int BPV>
+hipError_t launch_options(const RenderArgs &A, bool aov, const QueueLaunch &Q, hipStream_t s) {
+    if (A.nvis <= 1) return launch_opt<1, BPV>(A, aov, Q, s);
+    if (A.nvis <= 2) return launch_opt<2, BPV>(A, aov, Q, s);
+    if (A.nvis <= 4) return launch_opt<4, BPV>(A, aov, Q, s);
+    if (A.nvis <= 8) return launch_opt<8, BPV>(A, aov, Q, s);
+    return launch_opt<16, BPV>(A, aov, Q, s);
+}
+#if !defined(RO_PART) || RO_PART == 3
+template hipError_t launch_options<1>(const RenderArgs &, bool, const QueueLaunch &, hipStream_t);
+#endif
+#if !defined(RO_PART) || RO_PART == 4
+template hipError_t launch_options<2>(const RenderArgs &, bool, const QueueLaunch &, hipStream_t);
+#endif
+#endif
+
+#if !defined(RO_PART) || RO_PART == 0
+template <int BPV>
 static hipError_t launch_bpv(const RenderArgs &A, bool aov, const QueueLaunch &Q, hipStream_t s) {
-    if (A.nvis <= 1) return launch_nv<1, BPV>(A, aov, Q, s);
-    if (A.nvis <= 2) return launch_nv<2, BPV>(A, aov, Q, s);
-    if (A.nvis <= 4) return launch_nv<4, BPV>(A, aov, Q, s);
-    if (A.nvis <= 8) return launch_nv<8, BPV>(A, aov, Q, s);
-    return launch_nv<16, BPV>(A, aov, Q, s);
+    if (aov || (A.flags & (RO_RENDER_HOMOGENEOUS | RO_RENDER_CHANNEL_RATES)))
+        return launch_options<BPV>(A, aov, Q, s);
+    return launch_plain<BPV>(A, Q, s);
 }
 
 // Kernel arguments of one frame (validated by the caller).
@@ -164,6 +211,7 @@ ro_status build_render_args(ro_octree *tr, const ro_frame_desc *fd, float *rgba,
     A.tx = fd->tx;
     A.ty = fd->ty;
     A.step = fd->step;
+    A.inv_step = 1.0 / fd->step;
     A.proj = fd->projection;
     A.W = fd->width;
     A.H = fd->height;
@@ -237,6 +285,8 @@ ro_status build_render_args(ro_octree *tr, const ro_frame_desc *fd, float *rgba,
         A.w0[j] = (float)(fd->win_lo[j] / 256.0);
         A.iw[j] = (float)(256.0 / ((double)fd->win_hi[j] - (double)fd->win_lo[j]));
     }
+    A.win_k = fd->projection == RO_PROJ_ORTHO ? 0.0f : (float)pix;
+    A.win_0 = fd->projection == RO_PROJ_ORTHO ? (float)(pix / fd->step) : 0.0f;
     A.term = fd->term_alpha;
     A.frame = fd->frame;
     A.flags = fd->flags;
@@ -272,6 +322,17 @@ ro_status render_device(ro_octree *tr, const ro_frame_desc *fd, float *rgba, hip
     // memset
     Q.counter = (uint32_t *)((uint8_t *)tr->b.scratch + tr->scratch_bytes - 256);
     Q.grid = dim3((unsigned)(ncu > 0 ? ncu : 256));
+    // a frame with fewer units of pixels than the chip has waves uses as many
+    // waves of each workgroup as it has units per CU (64 x 64 pixels: 0.37 ms
+    // against 0.49 ms on the few CUs that came first), and deals its blocks in
+    // smaller chunks, whole 32 x 32 tiles of them
+    const int p = lanes_per_ray((fd->flags & (RO_RENDER_AOV | RO_RENDER_BRICKS | RO_RENDER_NODES)) != 0);
+    const uint32_t n_units = Q.n_blocks * (uint32_t)p;
+    const uint32_t per_cu = (n_units + Q.grid.x - 1) / Q.grid.x;
+    Q.n_waves = per_cu < kRenderLanes / 64 ? per_cu : kRenderLanes / 64;
+    uint32_t chunk = Q.n_blocks / (RO_QUEUES * 8);
+    chunk = chunk >= RO_CHUNK ? RO_CHUNK : chunk >= 16 ? chunk & ~15u : chunk ? chunk : 1;
+    Q.chunk = chunk * (uint32_t)p;
     static_assert(RO_QUEUES * kQueueStride * 4 <= 256, "queue counters exceed the scratch tail");
     st = launch_fill_u32(Q.counter, (uint64_t)RO_QUEUES * kQueueStride, 0u, s);
     if (st) return st;
@@ -280,5 +341,6 @@ ro_status render_device(ro_octree *tr, const ro_frame_desc *fd, float *rgba, hip
     RO_HIP(g.bpv == 1 ? launch_bpv<1>(A, aov, Q, s) : launch_bpv<2>(A, aov, Q, s));
     return RO_OK;
 }
+#endif  // host part
 
 }  // namespace ro

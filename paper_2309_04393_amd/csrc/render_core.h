@@ -17,11 +17,12 @@ struct RenderArgs {
     int32_t m, L, Blog, E, depth, start_level;
     uint32_t per_channel, slot_stride;
     double eye[3], F[3], R[3], U[3];
-    double tx, ty, step;
+    double tx, ty, step, inv_step;
     int32_t proj, W, H;
     int32_t nvis;
     float term;
     uint32_t frame, flags;
+    float win_k, win_0;  // a pixel's footprint in samples: win_0 + win_k * sample index
     int32_t ident;  // visible slot j shows channel j for every channel, and m % 4 == 0
     int32_t uni;    // every visible channel has the same level range (lo[0], hi[0])
     int32_t step_lo, step_hi;  // adaptive step: the finest desired level is clamped to these
@@ -54,9 +55,21 @@ struct RenderArgs {
 
 struct ChanLds {
     int c, lo, hi, nruns;
-    float w0, iw;
     uint32_t ehi;     // one zero-opacity run starting at raw value 0: its last raw value, else ~0
     uint32_t single;  // same in every entry: every visible channel has such a run
+    uint32_t onecol;  // same in every entry: every visible channel's table has one colour
+};
+
+// Window and, where its table has one colour (onecol), colour of each visible
+// channel, one row per value so that a group's values are one vector read.
+// ehi: where every visible channel has one zero-opacity run starting at raw
+// value 0, that run's last raw value in the upper half-word (a channel is
+// empty in a node iff its metadata word does not exceed ehi | 0xFFFF); cbase:
+// first brick of the channel.
+template <int NV>
+struct __attribute__((aligned(16))) ChanPar {
+    float w0[NV], iw[NV], r[NV], g[NV], b[NV];
+    uint32_t ehi[NV], cbase[NV];
 };
 
 struct LevLds {
@@ -89,21 +102,33 @@ __device__ __forceinline__ T *gmem(T *p) {
 // (24.8 fixed point, den = W1 - W0):
 // floor(255 (256 r - W0) / den) >= a  <=>  r >= ceil((255 W0 + a den) / 65280)
 // ceil (255 (256 r - W0) / den) <= b  <=>  r <= floor((255 W0 + b den) / 65280)
-__device__ inline int build_runs(const float4 *tf, uint32_t W0, uint32_t W1, uint32_t *runs) {
-    int n = 0, e = 0;
+// zero: the entries of alpha 0, one bit each.
+__device__ inline int build_runs(const uint64_t zero[4], uint32_t W0, uint32_t W1, uint32_t *runs) {
+    int n = 0;
     const uint64_t den = (uint64_t)W1 - (uint64_t)W0;
-    while (e < 256) {
-        if (tf[e].w != 0.0f) {
-            ++e;
-            continue;
+    uint64_t prev = 0, w = zero[0], up = zero[1];  // the word before, at and after the scanned one
+    int start = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        // entries at which a run starts or ends
+        uint64_t first = w & ~((w << 1) | (prev >> 63)), last = w & ~((w >> 1) | (up << 63));
+        while (first | last) {
+            const int f = first ? __builtin_ctzll(first) : 64, l = last ? __builtin_ctzll(last) : 64;
+            if (f <= l) {
+                start = 64 * q + f;
+                first &= first - 1;
+                if (f != l) continue;
+            }
+            last &= last - 1;
+            const int a = start, b = 64 * q + l;
+            uint64_t rlo = a == 0 ? 0 : (255ull * W0 + (uint64_t)a * den + 65279ull) / 65280ull;
+            uint64_t rhi = b == 255 ? 65535ull : (255ull * W0 + (uint64_t)b * den) / 65280ull;
+            if (rhi > 65535ull) rhi = 65535ull;
+            if (rlo <= rhi && n < kMaxRuns) runs[n++] = (uint32_t)rlo | ((uint32_t)rhi << 16);
         }
-        const int a = e;
-        while (e < 256 && tf[e].w == 0.0f) ++e;
-        const int b = e - 1;
-        uint64_t rlo = a == 0 ? 0 : (255ull * W0 + (uint64_t)a * den + 65279ull) / 65280ull;
-        uint64_t rhi = b == 255 ? 65535ull : (255ull * W0 + (uint64_t)b * den) / 65280ull;
-        if (rhi > 65535ull) rhi = 65535ull;
-        if (rlo <= rhi && n < kMaxRuns) runs[n++] = (uint32_t)rlo | ((uint32_t)rhi << 16);
+        prev = w;
+        w = up;
+        up = q == 0 ? zero[2] : q == 1 ? zero[3] : 0ull;
     }
     return n;
 }
@@ -121,21 +146,14 @@ __device__ __forceinline__ bool range_empty(uint32_t mm, const uint32_t *runs, i
 // the last, so the interpolation's upper entry needs no clamp.
 constexpr int kTfStride = 257;
 
-// Transfer function of a visible channel at raw value v: window, table
-// position, linear interpolation of the LDS table (tf = the channel's
-// entries; at the top end the weight of the copy is zero).
-__device__ __forceinline__ void classify(float v, const ChanLds &ch, const float4 *tf, float &al, float &r, float &g,
-                                         float &b) {
-    float x = (v - ch.w0) * ch.iw;
+// Table position of raw value v in the window (w0, iw): entry (0 .. 255) and
+// the weight of the next one.
+__device__ __forceinline__ int tf_entry(float v, float w0, float iw, float &f) {
+    float x = (v - w0) * iw;
     x = fminf(fmaxf(x, 0.0f), 1.0f);
-    const float p = x * 255.0f;
-    const int e = (int)p;  // 0 .. 255
-    const float f = p - (float)e;
-    const float4 ta = tf[e], tb = tf[e + 1];
-    al = ta.w + (tb.w - ta.w) * f;
-    r = ta.x + (tb.x - ta.x) * f;
-    g = ta.y + (tb.y - ta.y) * f;
-    b = ta.z + (tb.z - ta.z) * f;
+    const int e = (int)(x * 255.0f);
+    f = fmaf(x, 255.0f, -(float)e);
+    return e;
 }
 
 // Two horizontally adjacent voxels (x, x + 1) in one load; the voxel grid
@@ -183,61 +201,90 @@ constexpr int kRenderLanes = RO_LANES;
 // Serving work items: up to kSegBlocks 8 x 8-pixel blocks of one request.
 constexpr uint32_t kSegBlocks = 96;
 
-// A lane's span of a node that is homogeneous for every visible channel:
-// the transparency of one taken sample, the transparency when the span
-// began, and the constant mix's summed opacity and opacity-weighted colour.
-struct HomLane {
-    double tau, t0;
-    float hsa, hsr, hsg, hsb;
-};
+// Channels whose loads are in flight together.
+constexpr int group_of(int nv) { return nv < RO_GROUP ? nv : RO_GROUP; }
 
-// Dynamic LDS of a workgroup: NV transfer-function tables, then one slot
-// word per lane and visible channel, then (kernels with render-and-skip)
-// one HomLane per lane.
-__host__ __device__ constexpr size_t render_lds_bytes(int nv, bool homog = false) {
-    return (size_t)nv * kTfStride * 16 + (size_t)nv * kRenderLanes * 4 + (homog ? kRenderLanes * sizeof(HomLane) : 0);
+// Dynamic LDS of a workgroup: NV transfer-function tables, two entries of
+// zeros (where the channels that are not sampled look up), then one slot word
+// per ray and visible channel, the reciprocals of the ray directions, and
+// each wave's table of miss counts.  P lanes work on a ray.
+constexpr int kMissEntries = 32;
+__host__ __device__ constexpr size_t render_lds_bytes(int nv, int p) {
+    return ((size_t)nv * kTfStride + 2) * 16 + ((size_t)nv * 4 + 3 * 8) * (kRenderLanes / p) +
+           (size_t)kMissEntries * 12 * (kRenderLanes / 64);
 }
 
-// Slot of each visible channel for a lane's current visit, kept in LDS (one
-// word per lane and channel, lane-minor so a wave's accesses are
-// conflict-free) rather than in registers.
-struct LdsSlots {
-    uint32_t *p;      // this lane's first word
-    uint32_t stride;  // lanes in the workgroup
-    __device__ __forceinline__ uint32_t &operator[](int j) { return p[(uint32_t)j * stride]; }
+template <int G, class T>
+__device__ __forceinline__ void group_read(const T *p, T v[G]) {
+    if constexpr (G % 4 == 0) {
+        typedef T vec4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+        for (int i = 0; i < G; i += 4) {
+            const vec4 q = *(const vec4 *)(p + i);
+            v[i] = q.x;
+            v[i + 1] = q.y;
+            v[i + 2] = q.z;
+            v[i + 3] = q.w;
+        }
+    } else {
+        for (int i = 0; i < G; ++i) v[i] = p[i];
+    }
+}
+
+// A ray's LDS words: each visible channel's slot of the current visit (0 for
+// a channel without one), kept in LDS rather than in registers, group-major
+// so that a group's words are one vector read; and 1 / d.
+template <int NV, int P>
+struct RayLds {
+    static constexpr int G = group_of(NV), kRays = kRenderLanes / P;
+    uint32_t *p;  // this lane's words of the first group
+    double *inv;  // this lane's first reciprocal
+    uint32_t *miss;  // this wave's miss counts: key, channels (0: none), samples
+    __device__ __forceinline__ RayLds(const float4 *s_tf) {
+        uint32_t *w = (uint32_t *)(s_tf + kTfStride * NV + 2);
+        p = w + threadIdx.x / P * G;
+        inv = (double *)(w + NV * kRays) + threadIdx.x / P;
+        miss = w + (NV + 6) * kRays + (threadIdx.x >> 6) * (3 * kMissEntries);
+    }
+    __device__ __forceinline__ uint32_t &slot(int j) { return p[(uint32_t)(j / G) * (kRays * G) + j % G]; }
+    __device__ __forceinline__ void group(int g, uint32_t w[G]) const {
+        group_read<G>(p + (uint32_t)(g / G) * (kRays * G), w);
+    }
+    __device__ __forceinline__ double &inverse(int a) { return inv[a * kRays]; }
 };
 
-// Pixel source of the stepping loop (first pixel of each lane, further
-// pixels when lanes of the wave are idle).
+// Pixel source of the stepping loop: a wave takes its 64 / P pixels at once
+// (8 x 8 of them for P = 1, 4 x 4 for P = 4) and the next ones when all its
+// rays have ended.
 //
-// BlockQueue: waves take 8 x 8-pixel blocks from device counters (blocks of
-// a 32 x 32 tile are consecutive, tiles in raster order).  With n_queues = 1
-// one counter hands out the blocks in order.  With n_queues > 1 the blocks
-// are dealt in chunks of `chunk` consecutive blocks, chunk c to queue
-// c mod n_queues; a workgroup starts on queue (workgroup index mod
+// Units of pixels are handed out by device counters (the units of an 8 x 8
+// block, the blocks of a 32 x 32 tile are consecutive, tiles in raster
+// order).  With n_queues = 1 one counter hands out the units in order.  With
+// n_queues > 1 they are dealt in chunks of `chunk` consecutive units, chunk c
+// to queue c mod n_queues; a workgroup starts on queue (workgroup index mod
 // n_queues), which with workgroups dealt to the XCDs in turn is its XCD's,
 // and takes from the next queues once its own is used up.  The XCDs then
 // work on separate neighbouring chunks (their L2s hold different lines)
 // while all of them still sweep the image together (the Infinity Cache is
-// shared).  Lanes whose ray ended take the next pixels of the wave's block,
-// in lane order of a ballot of the idle lanes (prefix ranks), once at least
-// min_idle lanes are idle.  Counter reads and block state are wave-uniform.
+// shared).  Counter reads and the unit are wave-uniform.
 constexpr int kQueueStride = 8;  // words between queue counters (32 bytes)
-struct BlockQueue {
-    static constexpr bool kRefill = true;
+template <int P>
+struct UnitQueue {
     uint32_t *counter;  // n_queues counters kQueueStride words apart, zero at launch (device or LDS)
-    uint32_t n_blocks;  // blocks this queue hands out: offset .. offset + n_blocks - 1
+    uint32_t n_units;   // units this queue hands out: offset .. offset + n_units - 1
     uint32_t offset, tiles_x;
     uint32_t n_queues, chunk;
     int W, H;
-    int min_idle;     // refill when at least this many lanes are idle
-    uint32_t block;   // current block (wave-uniform)
-    uint32_t used;    // its pixels handed out
     bool exhausted;
     uint32_t q, tried;  // current queue, queues found used up (wave-uniform)
 
+    __device__ __forceinline__ void init() {
+        q = blockIdx.x % n_queues;
+        tried = 0;
+        exhausted = false;
+    }
     __device__ __forceinline__ uint32_t pop() {
-        uint32_t b = n_blocks;
+        uint32_t b = n_units;
         if ((threadIdx.x & 63) == 0) {
             if (n_queues == 1) {
                 b = atomicAdd(counter, 1u);
@@ -246,7 +293,7 @@ struct BlockQueue {
                     const uint32_t i = atomicAdd(counter + q * kQueueStride, 1u);
                     const uint64_t c = (uint64_t)(i / chunk) * n_queues + q;
                     const uint64_t bb = c * chunk + i % chunk;
-                    if (bb < n_blocks) {
+                    if (bb < n_units) {
                         b = (uint32_t)bb;
                         break;
                     }
@@ -259,54 +306,30 @@ struct BlockQueue {
         tried = (uint32_t)__shfl((int)tried, 0, 64);
         return (uint32_t)__shfl((int)b, 0, 64);
     }
-    __device__ __forceinline__ void pixel(uint32_t b, uint32_t i, int &x, int &y, bool &v) const {
-        b += offset;
-        const uint32_t t = b >> 4;
-        x = (int)((t % tiles_x) * 32 + (b & 3u) * 8 + (i & 7u));
-        y = (int)((t / tiles_x) * 32 + ((b >> 2) & 3u) * 8 + (i >> 3));
-        v = x < W && y < H;
-    }
-    __device__ __forceinline__ bool more() const { return !exhausted; }
-    __device__ __forceinline__ bool first(int &x, int &y, bool &v) {
-        q = blockIdx.x % n_queues;
-        tried = 0;
-        block = pop();
-        used = 64;
-        exhausted = block >= n_blocks;
+    // this lane's pixel of the next unit; false (in every lane) when there is none
+    __device__ __forceinline__ bool next(int &x, int &y, bool &v) {
         if (exhausted) return false;
-        pixel(block, threadIdx.x & 63, x, y, v);
-        return true;
-    }
-    // want: ballot of the idle lanes; returns whether this lane got a pixel
-    __device__ __forceinline__ bool refill(uint64_t want, int &x, int &y, bool &v) {
-        if (exhausted || __popcll(want) < (unsigned)min_idle) return false;
-        const uint32_t ln = threadIdx.x & 63;
-        const bool me = (want >> ln) & 1ull;
-        const uint32_t r = (uint32_t)__popcll(want & ((1ull << ln) - 1ull));
-        const uint32_t n = (uint32_t)__popcll(want);
-        const uint32_t left = 64 - used;
-        bool got = false;
-        if (me && r < left) {
-            pixel(block, used + r, x, y, v);
-            got = true;
+        uint32_t u = pop();
+        if (u >= n_units) {
+            exhausted = true;
+            return false;
         }
-        if (n > left) {
-            const uint32_t nb = pop();
-            if (nb >= n_blocks) {
-                exhausted = true;
-                used = 64;
-            } else {
-                if (me && r >= left) {
-                    pixel(nb, r - left, x, y, v);
-                    got = true;
-                }
-                block = nb;
-                used = n - left;
-            }
+        u += offset;
+        const uint32_t b = u / P, t = b >> 4, i = (threadIdx.x & 63u) / P;
+        x = (int)((t % tiles_x) * 32 + (b & 3u) * 8);
+        y = (int)((t / tiles_x) * 32 + ((b >> 2) & 3u) * 8);
+        if (P == 4) {
+            // 2 x 2 pixels are neighbouring lanes: the 16 lanes whose gathers
+            // are looked up together touch fewer cache lines than with rows
+            // of four (18.5 against 22.5 lookups per 64-lane load)
+            x += (int)((u & 1u) * 4 + (i & 1u) + (i >> 1 & 2u));
+            y += (int)((u >> 1 & 1u) * 4 + (i >> 1 & 1u) + (i >> 2 & 2u));
         } else {
-            used += n;
+            x += (int)(i & 7u);
+            y += (int)(i >> 3);
         }
-        return got;
+        v = x < W && y < H;
+        return true;
     }
 };
 
@@ -316,63 +339,152 @@ __host__ __device__ constexpr size_t slot_bytes(int e, int bpv) {
     return ((size_t)e * e * e * bpv + 255) / 256 * 256;
 }
 
+// A value that is the same in every lane (a kernel argument, or a field of
+// the workgroup's staged request) as a scalar of its own: kept in scalar
+// registers by itself instead of being read again with its neighbours.
+__device__ __forceinline__ uint32_t scalar32(uint32_t x) {
+    x = (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+    asm volatile("" : "+s"(x));
+    return x;
+}
+__device__ __forceinline__ uint64_t scalar64(uint64_t x) {
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+    uint64_t v = ((uint64_t)hi << 32) | (uint64_t)lo;
+    asm volatile("" : "+s"(v));
+    return v;
+}
+
+// The value of lane i of the P lanes of this lane's ray.
+template <int P, int i>
+__device__ __forceinline__ uint32_t ray_lane(uint32_t v) {
+    if constexpr (P == 1) return v;
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, i * 0x55, 0xf, 0xf, true);  // quad_perm i i i i
+}
+template <int P, int i>
+__device__ __forceinline__ float ray_lane(float v) {
+    return __uint_as_float(ray_lane<P, i>(__float_as_uint(v)));
+}
+template <int P, int i>
+__device__ __forceinline__ double ray_lane(double v) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint64_t r = (uint64_t)ray_lane<P, i>((uint32_t)(b >> 32)) << 32 | ray_lane<P, i>((uint32_t)b);
+    return __longlong_as_double((long long)r);
+}
+
+// Smallest of the wave's values, in every lane.
+__device__ __forceinline__ float wave_min(float v) {
+    // row_shr 1, 2, 4, 8 within rows of 16, then the row and half broadcasts: lane 63 holds the minimum
+#define RO_STEP(ctrl)                                                                                        \
+    v = fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), ctrl, 0xf, \
+                                                            0xf, false)));
+    RO_STEP(0x111)
+    RO_STEP(0x112)
+    RO_STEP(0x114)
+    RO_STEP(0x118)
+    RO_STEP(0x142)
+    RO_STEP(0x143)
+#undef RO_STEP
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
 // EC: the brick edge with halo known at compile time (0: read from A).  A
 // constant edge turns the four gather offsets into instruction immediates.
-// ADAPT: whether the LOD-adaptive step is compiled in; EXT: bit 0
-// render-and-skip of nodes homogeneous for all channels, bit 1 per-channel
-// sampling rates (frames that ask for them go to a kernel that has them).
-template <int NV, int BPV, bool AOV, int EC, bool ADAPT, int EXT, class Source>
-__device__ __forceinline__ void render_rays(const RenderArgs &A, Source &src, const float4 *s_tf,
-                                            const ChanLds *s_ch, const uint32_t *s_runs, const LevLds *s_lv,
-                                            const NodeLds *s_nd, uint32_t stats[7], LdsSlots slot) {
+// EXT: bit 0 render-and-skip of nodes homogeneous for all channels, bit 1
+// per-channel sampling rates (frames that ask for them go to a kernel that
+// has them).
+//
+// A lane alternates between visits and samples.  A visit takes the ray's next
+// sample position, descends to its leaf, skips an empty node, or finds the
+// slot of each channel and the last sample that lies in the leaf (the visit's
+// segment).  The samples of a segment then need no tree or level logic: the
+// position, scaled to the level's voxels (an exact power of two), is one
+// multiply-add per axis.
+template <int NV, int BPV, bool AOV, int EC, int EXT, int P>
+__device__ __forceinline__ void render_rays(const RenderArgs &A, UnitQueue<P> &src, const float4 *s_tf,
+                                            const ChanLds *s_ch, const ChanPar<NV> *s_par, const uint32_t *s_runs,
+                                            const LevLds *s_lv, const NodeLds *s_nd, uint32_t stats[7]) {
     constexpr bool HOMOG = (EXT & 1) != 0;
-    constexpr bool RATES = ADAPT && (EXT & 2) != 0;
-    const int nvis = A.nvis;
-    const int D = A.depth;
-    const int L = A.L;
-    const int m = A.m;
-    constexpr int kGroup = NV < RO_GROUP ? NV : RO_GROUP;  // channels whose loads are in flight together
+    constexpr bool RATES = (EXT & 2) != 0;
+    const int nvis = (int)scalar32((uint32_t)A.nvis);
+    const int D = (int)scalar32((uint32_t)A.depth);
+    const int L = (int)scalar32((uint32_t)A.L);
+    const int m = (int)scalar32((uint32_t)A.m);
+    const double step = __longlong_as_double((long long)scalar64((uint64_t)__double_as_longlong(A.step)));
+    const uint8_t *pool = (const uint8_t *)(const __attribute__((address_space(1))) uint8_t *)scalar64(
+        reinterpret_cast<uint64_t>(A.slots));
+    const bool onecol = scalar32(s_ch[0].onecol) != 0;
+    constexpr int kGroup = group_of(NV);  // gathers
+    // The P lanes of a ray share a visit's channels: lane q takes the kOwn
+    // channels from q * kOwn on, vGroup at a time.
+    constexpr int kOwn = NV > P ? NV / P : 1;
+    constexpr int vGroup = kOwn < 4 ? kOwn : 4;
+    const int q = P == 1 ? 0 : (int)(threadIdx.x & (P - 1));
+    const int own = min(q * kOwn, NV - kOwn);  // (with more lanes than channels the last ones repeat a channel)
+    // OR over the lanes of a ray
+    auto all_of_ray = [&](uint32_t v) {
+        if (P == 4) {
+            v |= (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xf, 0xf, true);  // quad_perm 1 0 3 2
+            v |= (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xf, 0xf, true);  // quad_perm 2 3 0 1
+        }
+        return v;
+    };
     const double one_minus_term = 1.0 - (double)A.term;
     const uint32_t vismask = (nvis >= 32) ? 0xFFFFFFFFu : ((1u << nvis) - 1u);
     const int s0 = A.start_level;
     const bool noskip = (A.flags & RO_RENDER_NO_SKIP) != 0;
-    const bool adaptive = ADAPT && (A.flags & RO_RENDER_ADAPTIVE_STEP) != 0;
+    const bool adaptive = (A.flags & RO_RENDER_ADAPTIVE_STEP) != 0;
     const bool homog = HOMOG && (A.flags & RO_RENDER_HOMOGENEOUS) != 0;
     // per-channel sampling rates (with the adaptive step): a channel takes part
     // only in samples k that are multiples of its own level's x factor
     const bool rates = RATES && adaptive && (A.flags & RO_RENDER_CHANNEL_RATES) != 0;
     // traversal depth from the step (with the adaptive step): emptiness and
     // homogeneity are decided at the node of depth dd of the step's level
-    const bool tdepth = ADAPT && adaptive && (A.flags & RO_RENDER_TRAVERSAL_DEPTH) != 0;
+    const bool tdepth = adaptive && (A.flags & RO_RENDER_TRAVERSAL_DEPTH) != 0;
+    const bool per_sample = rates || (AOV && (A.aov || A.reqb));  // every sample is recorded by itself
     const NodeLds leafl = s_nd[D];
     const bool single = s_ch[0].single != 0;
+    const float2 *s_tfa = (const float2 *)s_tf;
+    RayLds<NV, P> lds(s_tf);
+    const uint32_t E = EC ? (uint32_t)EC : (uint32_t)A.E;
+    const uint32_t stride = EC ? (uint32_t)slot_bytes(EC, BPV) : A.slot_stride;
     uint32_t st_samples = 0, st_reads = 0, st_miss = 0, st_visits = 0, st_nonempty = 0, st_iters = 0, st_hom = 0;
 
     // ---- per-ray state
     int px = 0, py = 0;
     bool has = false;  // the lane holds a ray (finished or not)
+    // ray in voxels of the level whose factors are 2^vsh (per axis; 0: L0)
     double o[3] = {0, 0, 0}, d[3] = {0, 0, 0};
+    uint32_t vsh = 0;
     double Cr = 0, Cg = 0, Cb = 0, Tr = 1.0;
     float *out = nullptr;
     bool done = true;
-    long long k = 0, kend = -1, skip_to = 0;  // the lane is inside an empty node while k < skip_to
-    int rpace = 0;  // adaptive step: log2 of the lane's last sampling distance (its pace while skipping)
+    // sample index, last index of the ray, first index past the segment (whole numbers)
+    double k = 0, kend = -1, kseg = 0;
+    int rsh = 0;  // adaptive step: log2 of the segment's sampling distance
     uint32_t cur_leaf = kInvalid;
     int cur_lod = -1, lod = 0;
+    double klod = INFINITY;  // first sample index of the next level
     uint32_t emask = 0, missmask = 0;
     uint64_t lvpack = 0;
-    uint32_t nvisit = 0;
-    int lc[3] = {-1, -1, -1};  // L0 origin of the last visited leaf or skipped node (none yet)
-    int lcd = 0;                // its depth: the nodes above it are known not to be skipped
+    // samples not yet added to the miss counters: their count, the missing
+    // channels, and the finest desired brick (x | y << 8 | z << 16) and
+    // level index (<< 24) they share
+    uint32_t npend = 0, pmask = 0, pkey = 0;
+    uint32_t fpend = 0, fmask = 0, fkey = 0;  // those of the visit before, to be added
+    int lc[3] = {-1, -1, -1};      // L0 origin of the last visited leaf or skipped node (none yet)
+    int lcd = 0;                   // its depth: the nodes above it are known not to be skipped
     uint32_t last_key = kInvalid;  // (level, cell) of the last visit when uniform
+    uint32_t cbias = 0;            // when uniform: voxel index of the brick's origin in its level's slot strides
     uint32_t have = 0;             // channels with a slot from the last visit
     uint32_t stamped = 0;          // with rates: channels whose current slot carries this frame's stamp
     uint64_t rpk = 0;              // with rates: each channel's rate shift in the current visit (4 bits)
-    // render-and-skip: the lane composites a homogeneous span, one taken
-    // sample per wave iteration, until skip_to (its state in LDS)
-    bool hom_on = false;
-    HomLane *hl = nullptr;
-    if constexpr (HOMOG) hl = (HomLane *)((uint32_t *)(s_tf + kTfStride * NV) + NV * kRenderLanes) + threadIdx.x;
+
+    auto next_level = [&]() {
+        ++lod;
+        const uint32_t K = lod + 1 < L ? s_lv[lod + 1].K : kInvalid;
+        klod = K == kInvalid ? INFINITY : (double)K;
+    };
 
     // ray set-up in L0 voxel units, box interval, first sample index
     auto start = [&](int x, int y, bool valid) {
@@ -382,20 +494,23 @@ __device__ __forceinline__ void render_rays(const RenderArgs &A, Source &src, co
         const double a = (double)(2 * px + 1 - A.W) / (double)A.W;
         const double b = (double)(A.H - 2 * py - 1) / (double)A.H;
         double ow[3], dw[3];
+        // (fused multiply-adds are written out where positions and samples are
+        // computed: which products the compiler fuses would otherwise depend
+        // on the code around them)
+        const double ax = a * A.tx, by = b * A.ty;
         if (A.proj == RO_PROJ_ORTHO) {
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
-                ow[q] = A.eye[q] + a * A.tx * A.R[q] + b * A.ty * A.U[q];
+                ow[q] = fma(by, A.U[q], fma(ax, A.R[q], A.eye[q]));
                 dw[q] = A.F[q];
             }
         } else {
-            double n = 0;
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
                 ow[q] = A.eye[q];
-                dw[q] = A.F[q] + a * A.tx * A.R[q] + b * A.ty * A.U[q];
-                n += dw[q] * dw[q];
+                dw[q] = fma(by, A.U[q], fma(ax, A.R[q], A.F[q]));
             }
+            double n = fma(dw[2], dw[2], fma(dw[0], dw[0], dw[1] * dw[1]));
             n = sqrt(n);
 #pragma unroll
             for (int q = 0; q < 3; ++q) dw[q] = dw[q] / n;
@@ -404,7 +519,9 @@ __device__ __forceinline__ void render_rays(const RenderArgs &A, Source &src, co
         for (int q = 0; q < 3; ++q) {
             o[q] = ow[q] / A.sp[q];
             d[q] = dw[q] / A.sp[q];
+            lds.inverse(q) = 1.0 / d[q];
         }
+        vsh = 0;
         Cr = Cg = Cb = 0.0;
         Tr = 1.0;
         out = valid ? gmem(A.rgba) + ((size_t)py * A.W + px) * 4 : nullptr;
@@ -432,381 +549,330 @@ __device__ __forceinline__ void render_rays(const RenderArgs &A, Source &src, co
             t1 = fmin(t1, v);
         }
         done = !valid || !hit || t0 > t1;
-        k = done ? 0 : (long long)floor(t0 / A.step) - 1;
-        if (k < 0) k = 0;
-        kend = done ? -1 : (long long)ceil(t1 / A.step) + 1;
-        skip_to = 0;
+        k = done ? 0.0 : floor(t0 / A.step) - 1.0;
+        if (!(k > 0.0)) k = 0.0;
+        kend = done ? -1.0 : ceil(t1 / A.step) + 1.0;
+        // a ray without an end inside the volume (a camera without a direction) has no samples
+        if (!(kend < 9.0e15)) {
+            done = true;
+            kend = -1.0;
+        }
+        kseg = k;
+        rsh = 0;
         cur_leaf = kInvalid;
         cur_lod = -1;
-        lod = 0;
-        rpace = 0;
-        while (lod + 1 < L && (unsigned long long)k >= s_lv[lod + 1].K) ++lod;
+        lod = -1;
+        klod = -1.0;
+        while (k >= klod) next_level();
         emask = missmask = 0;
         lvpack = 0;
-        nvisit = 0;
+        npend = pmask = 0;
         lc[0] = lc[1] = lc[2] = -1;
         lcd = 0;
         last_key = kInvalid;
         have = 0;
         stamped = 0;
-        hom_on = false;
 #pragma unroll
-        for (int j = 0; j < NV; ++j) slot[j] = kInvalid;
+        for (int j = 0; j < NV; ++j) lds.slot(j) = 0;
     };
 
-    auto flush = [&]() {
-        if (missmask && nvisit) {
-#pragma unroll
-            for (int j = 0; j < NV; ++j) {
-                if (j < nvis && ((missmask >> j) & 1u)) {
-                    const ChanLds ch = s_ch[j];
-                    const int ls = min(max(cur_lod, ch.lo), ch.hi);
-                    const LevLds lv = s_lv[ls];
-                    const int bx = lc[0] >> field(lv.sh, 0), by = lc[1] >> field(lv.sh, 1),
-                              bz = lc[2] >> field(lv.sh, 2);
-                    atomicAdd(&gmem(A.cnt)[brick_dense(lv, (uint32_t)ch.c, A.per_channel, bx, by, bz)], nvisit);
-                    st_miss += nvisit;
-                }
-            }
+    // Adds n samples to the miss counters of the channels in msk at the
+    // desired bricks of key: lane j the counter of channel j.
+    auto count_misses = [&](uint32_t key, uint32_t msk, uint32_t n) {
+        const int ln = (int)(threadIdx.x & 63u);
+        if (ln < NV && ((msk >> ln) & 1u)) {
+            const int plod = (int)(key >> 24);
+            const LevLds lf = s_lv[min(max(plod, A.step_lo), A.step_hi)];
+            const ChanLds ch = s_ch[ln];
+            const LevLds lv = s_lv[min(max(plod, ch.lo), ch.hi)];
+            // the desired brick is as coarse as the shared one or coarser and contains it
+            const uint32_t s = lv.sh - lf.sh;
+            atomicAdd(&gmem(A.cnt)[brick_dense(lv, (uint32_t)ch.c, A.per_channel, field(key, 0) >> field(s, 0),
+                                               field(key, 1) >> field(s, 1), field(key, 2) >> field(s, 2))],
+                      n);
         }
-        nvisit = 0;
+    };
+    // Pending samples go to the miss counters by way of a table of the wave
+    // (kMissEntries sums in LDS, by brick and missing channels).  Device
+    // atomics leave the XCD, and on a frame with few bricks every ray of a
+    // wave, and the next units' rays, add to the same counters: one atomic per
+    // ray, visit and channel took 26 ms of a 960 x 540 frame of a 16-channel
+    // slide without bricks, one per wave and brick 7.
+    // (Called by the whole wave: every lane takes part.)
+    auto flush = [&](uint32_t n_own, uint32_t mask, uint32_t key_own) {
+        uint64_t todo = __ballot(n_own != 0 && mask != 0 && q == 0);
+        const int ln = (int)(threadIdx.x & 63u);
+        while (todo) {
+            const int first = __builtin_ctzll(todo);
+            const uint32_t key = (uint32_t)__builtin_amdgcn_readlane((int)key_own, first);
+            const uint32_t msk = (uint32_t)__builtin_amdgcn_readlane((int)mask, first);
+            const bool mine = ((todo >> ln) & 1ull) && key_own == key && mask == msk;
+            const uint64_t like = __ballot(mine);
+            uint32_t n = mine ? n_own : 0u;
+            st_miss += n * (uint32_t)__popc(msk);
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) n += (uint32_t)__shfl_xor((int)n, o, 64);
+            uint32_t *e = lds.miss + 3 * ((((key ^ key >> 13) * 0x9E3779B1u) >> 16 ^ msk) % kMissEntries);
+            const uint32_t ek = e[0], em = e[1], en = e[2];
+            const bool hit = ek == key && em == msk;
+            if (!hit && em) count_misses(ek, em, en);
+            if (ln == 0) {
+                e[0] = key;
+                e[1] = msk;
+                e[2] = hit ? en + n : n;
+            }
+            todo &= ~like;
+        }
     };
 
     auto finish = [&]() {
-        flush();
-        if (out) {
-            out[0] = (float)Cr;
-            out[1] = (float)Cg;
-            out[2] = (float)Cb;
-            out[3] = (float)(1.0 - Tr);
-        }
+        if (out && q == 0) *(float4 *)out = make_float4((float)Cr, (float)Cg, (float)Cb, (float)(1.0 - Tr));
         has = false;
+        npend = 0;
     };
 
-    {
-        int x = 0, y = 0;
-        bool v = false;
-        if (src.first(x, y, v)) start(x, y, v);
-    }
-
-    // Wave-coherent stepping: lanes advance one sample per iteration, so the
-    // lanes of a wave (neighbouring pixels) sample at the same t and share
-    // cache lines; a lane inside an empty node idles, and the wave jumps
-    // ahead only by the smallest skip over its active lanes.  The samples a
-    // lane evaluates are exactly those it would evaluate on its own.  A lane
-    // whose ray ended writes its pixel and, with a refilling source, starts
-    // the next pixel of the wave's block.
-    while (true) {
-        if (has && (done || k > kend)) finish();
-        if (Source::kRefill) {
-            const uint64_t want = __ballot(!has);
-            if (want) {
-                int x = 0, y = 0;
-                bool v = false;
-                if (src.refill(want, x, y, v)) start(x, y, v);
-            }
-        }
-        const bool active = has && !done && k <= kend;
-        const long long gap = skip_to - k;
-        uint32_t need = !active ? 0xFFFFFFFFu : (gap > 0 ? (gap < 0x7FFFFFFFll ? (uint32_t)gap : 0x7FFFFFFFu) : 0u);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) need = min(need, (uint32_t)__shfl_xor((int)need, o, 64));
-        if (need == 0xFFFFFFFFu) {
-            // no lane is stepping: the wave ends once no lane holds a ray and
-            // the source has nothing more (rays that just ended retire above)
-            if (!__any(has) && !src.more()) break;
-            continue;
-        }
-        if (need > 0) {
-            // every active lane is in an empty node or a homogeneous span:
-            // the wave jumps; a lane in a span composites the span's samples
-            // it passes, one transparency factor each (a few instructions
-            // per sample, all lanes at once)
-            if constexpr (HOMOG) {
-                if (active && hom_on) {
-                    const long long rr = ADAPT ? (1ll << rpace) : 1;
-                    const long long m = ((long long)need + rr - 1) / rr;
-                    const double tau = hl->tau;
-                    bool term = false;
-                    long long i = 0;
-                    while (i < m && !term) {
-                        Tr *= tau;
-                        ++i;
-                        term = Tr <= one_minus_term;
-                    }
-                    st_samples += (uint32_t)i;
-                    st_hom += (uint32_t)i;
-                    k += i * rr;
-                    if (term || k >= skip_to) {
-                        const double sc = (hl->t0 - Tr) / (double)hl->hsa;
-                        Cr += sc * (double)hl->hsr;
-                        Cg += sc * (double)hl->hsg;
-                        Cb += sc * (double)hl->hsb;
-                        hom_on = false;
-                        done = term;
-                    }
-                    continue;
-                }
-            }
-            k += need;
-            continue;
-        }
-        ++st_iters;  // a stepping iteration of the wave (lane busy or idle)
-        if (!active) continue;
-        if constexpr (HOMOG) {
-            if (hom_on) {
-                // the next taken sample of the span: one transparency factor,
-                // as sample by sample (early termination falls on the same
-                // sample); the colour is summed in closed form at the end
-                Tr *= hl->tau;
-                ++st_samples;
-                ++st_hom;
-                const bool term = Tr <= one_minus_term;
-                k += ADAPT ? (1ll << rpace) : 1;
-                if (term || k >= skip_to) {
-                    const double sc = (hl->t0 - Tr) / (double)hl->hsa;
-                    Cr += sc * (double)hl->hsr;
-                    Cg += sc * (double)hl->hsg;
-                    Cb += sc * (double)hl->hsb;
-                    hom_on = false;
-                    done = term;
-                }
-                continue;
-            }
-        }
-        if (k < skip_to) {
-            // a skipping lane keeps the pace of the sampling lanes (one base
-            // step, or the band's distance with the adaptive step) so the
-            // wave's lanes stay at neighbouring depths
-            k = ADAPT ? min(skip_to, k + (1ll << rpace)) : k + 1;
-            continue;
-        }
-        const double t = (double)k * A.step;
-        double u[3];
+    // The next sample position of a ray: skip the node it lies in, or set up
+    // the segment of its leaf.
+    auto visit = [&]() {
+        double oo[3], dd[3], u[3];
+        const double t = k * step;
         bool inside = true;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            u[a] = o[a] + t * d[a];
+            const int s = (int)field(vsh, a);
+            oo[a] = ldexp(o[a], s);
+            dd[a] = ldexp(d[a], s);
+            u[a] = fma(t, dd[a], oo[a]);
             inside = inside && (u[a] >= 0.0) && (u[a] < (double)A.dims[a]);
         }
         if (!inside) {
-            ++k;
-            continue;
+            k += 1.0;
+            kseg = k;
+            return;
         }
         const int iu[3] = {(int)u[0], (int)u[1], (int)u[2]};
-        while (lod + 1 < L && (unsigned long long)k >= s_lv[lod + 1].K) ++lod;
+        while (k >= klod) next_level();
         // LOD-adaptive step: the finest desired level over the visible
         // channels sets the sampling distance, r = its x factor; only samples
         // with k a multiple of r are evaluated
-        int rsh = 0, dend = D;
+        int dend = D;
+        rsh = 0;
         if (adaptive) {
             const LevLds slv = s_lv[min(max(lod, A.step_lo), A.step_hi)];
             rsh = (int)field(slv.raw, 0);
             if (tdepth) dend = (int)slv.dd;
-            rpace = rsh;
-            const long long rm = (1ll << rsh) - 1;
-            if (k & rm) {
-                skip_to = (k | rm) + 1;
-                continue;
+            const double up = ldexp(ceil(ldexp(k, -rsh)), rsh);
+            if (up != k) {
+                k = up;
+                kseg = k;
+                return;
             }
         }
         const uint32_t leaf = node_at(leafl, iu[0] >> field(leafl.nsh, 0), iu[1] >> field(leafl.nsh, 1),
                                       iu[2] >> field(leafl.nsh, 2));
-        if (leaf != cur_leaf || lod != cur_lod) {
-            flush();
-            // with a traversal depth the decision node depends on the level too
-            if (leaf != cur_leaf || (tdepth && lod != cur_lod)) {
-                // Descend from the start level and skip the first node that
-                // is empty for every visible channel (the leaf included).
-                // Every ancestor of a visited leaf is non-empty, so levels
-                // whose node also holds the last visited leaf are known
-                // non-empty and the test starts below them (the same node
-                // is skipped either way).  With HOMOG the first node in which
-                // every visible channel is empty or holds one value (and one
-                // holds a value) is rendered from those values and skipped
-                // (Alg. 1 renderAndSkipNode, Sec. 6.1: homogeneous for all
-                // channels): its samples are composited and the ray goes on
-                // past the node.  Ancestors of a visited leaf are never such
-                // nodes either (metadata nest, so their descendants would be),
-                // and the ancestors of a skipped node were tested and found
-                // not to be skipped: the shared levels above the last visited
-                // leaf or skipped node are not tested again.
-                int d0 = noskip ? dend : min(s0, dend);
-                if (lc[0] >= 0 && !noskip && !tdepth) {
-                    while (d0 < lcd) {
-                        const uint32_t sh = s_nd[d0].nsh;
-                        if (((iu[0] ^ lc[0]) >> field(sh, 0)) | ((iu[1] ^ lc[1]) >> field(sh, 1)) |
-                            ((iu[2] ^ lc[2]) >> field(sh, 2)))
-                            break;
-                        ++d0;
-                    }
-                }
-                bool skipped = false;
-                long long rs_end = 0;   // render-and-skip: the first sample past the node or the volume,
-                uint32_t rs_node = 0;   // the node,
-                uint32_t rs_mask = 0;   // its homogeneous channels (none: no such node)
-                for (int dl = d0; dl <= dend; ++dl) {
-                    const NodeLds nd = s_nd[dl];
-                    const uint32_t node = node_at(nd, iu[0] >> field(nd.nsh, 0), iu[1] >> field(nd.nsh, 1),
-                                                  iu[2] >> field(nd.nsh, 2));
-                    // the node's metadata, kGroup channels per batch of loads
-                    uint32_t em = 0, hm = 0;
-                    const uint32_t *nm = gmem(A.meta) + (size_t)node * m;
-                    if (AOV && A.nodes) A.nodes[node] = 1;
-#pragma unroll
-                    for (int g = 0; g < NV; g += kGroup) {
-                        if (g >= nvis) break;
-                        uint32_t mm[kGroup];
-                        if (kGroup == 4 && A.ident) {
-                            // channels g..g+3 are one aligned 16-byte load
-                            const uint4 v = *(const uint4 *)(nm + g);
-                            mm[0] = v.x;
-                            mm[kGroup > 1 ? 1 : 0] = v.y;
-                            mm[kGroup > 2 ? 2 : 0] = v.z;
-                            mm[kGroup > 3 ? 3 : 0] = v.w;
-                        } else {
-#pragma unroll
-                            for (int jj = 0; jj < kGroup; ++jj) mm[jj] = g + jj < nvis ? nm[s_ch[g + jj].c] : 0u;
-                        }
-                        if (single) {
-                            // one zero run [0, ehi] per channel: empty iff the maximum is within it
-#pragma unroll
-                            for (int jj = 0; jj < kGroup; ++jj) {
-                                const int j = g + jj;
-                                if (j < nvis && (mm[jj] >> 16) <= s_ch[j].ehi) em |= 1u << j;
-                            }
-                        } else {
-#pragma unroll
-                            for (int jj = 0; jj < kGroup; ++jj) {
-                                const int j = g + jj;
-                                if (j < nvis && range_empty(mm[jj], s_runs + j * kMaxRuns, s_ch[j].nruns)) em |= 1u << j;
-                            }
-                        }
-                        if (homog) {
-#pragma unroll
-                            for (int jj = 0; jj < kGroup; ++jj) {
-                                const int j = g + jj;
-                                if (j < nvis && (mm[jj] & 0xFFFFu) == (mm[jj] >> 16)) hm |= 1u << j;
-                            }
-                        }
-                        asm volatile("" ::: "memory");
-                    }
-                    hm &= ~em;
-                    if (dl == dend) emask = em;
-                    const bool all_empty = em == vismask;
-                    const bool rskip = homog && hm && (em | hm) == vismask;
-                    // (without skipping, empty nodes are stepped through;
-                    // render-and-skip changes the image, so it stays on)
-                    if ((all_empty && !noskip) || rskip) {
-                        // exit of the node (and, for render-and-skip, of the
-                        // volume: a node may reach past it, and void samples
-                        // are not composited)
-                        double te = INFINITY;
-#pragma unroll
-                        for (int a = 0; a < 3; ++a) {
-                            if (d[a] == 0.0) continue;
-                            const int sh = (int)field(nd.nsh, a);
-                            const double lo_a = (double)((iu[a] >> sh) << sh);
-                            const double bound = d[a] > 0.0 ? lo_a + (double)(1 << sh) : lo_a;
-                            te = fmin(te, (bound - o[a]) / d[a]);
-                            if (!all_empty) te = fmin(te, ((d[a] > 0.0 ? (double)A.dims[a] : 0.0) - o[a]) / d[a]);
-                        }
-                        // samples before kb lie a whole step inside; kb itself
-                        // is inside when the sampling path's own position test
-                        // (same arithmetic) puts it in the node and the volume
-                        const long long kb = (long long)floor(te / A.step);
-                        bool in = kb > k;
-                        if (in) {
-                            const double tk = (double)kb * A.step;
-#pragma unroll
-                            for (int a = 0; a < 3; ++a) {
-                                const double ua = o[a] + tk * d[a];
-                                in = in && ua >= 0.0 && ua < (double)A.dims[a] &&
-                                     ((((int)ua) ^ iu[a]) >> field(nd.nsh, a)) == 0;
-                            }
-                        }
-                        const long long kx = in ? kb + 1 : kb;  // first sample that may lie outside
-#pragma unroll
-                        for (int a = 0; a < 3; ++a) lc[a] = (iu[a] >> field(nd.nsh, a)) << field(nd.nsh, a);
-                        lcd = dl;
-                        if (all_empty) {
-                            skip_to = kx > k + 1 ? kx : k + 1;
-                            ++k;
-                            skipped = true;
-                        } else if constexpr (HOMOG) {
-                            // render-and-skip: composited after the descent
-                            rs_end = kx;
-                            rs_node = node;
-                            rs_mask = hm;
-                        }
-                        break;
-                    }
-                }
-                if constexpr (HOMOG) {
-                    if (rs_mask) {
-                        // The constant mix of the homogeneous channels (in
-                        // visible-channel order, as sampled values mix) for the
-                        // taken samples k, k + r, .. of the span: up to the
-                        // node's exit, the volume's exit (the node may reach
-                        // beyond the volume, whose samples are void) and, with
-                        // the adaptive step, the next level threshold (r may
-                        // change there).  The lane composites them one per
-                        // wave iteration from here on, without gathers, then
-                        // goes on past the node.
-                        float hp = 1.0f, hsa = 0.0f, hsr = 0.0f, hsg = 0.0f, hsb = 0.0f;
-                        const uint32_t *rm = gmem(A.meta) + (size_t)rs_node * m;
-                        for (int j = 0; j < nvis; ++j) {
-                            if (!((rs_mask >> j) & 1u)) continue;
-                            const ChanLds ch = s_ch[j];
-                            float al, r, gg, bb;
-                            classify((float)(rm[ch.c] & 0xFFFFu), ch, s_tf + j * kTfStride, al, r, gg, bb);
-                            hp *= 1.0f - al;
-                            hsa += al;
-                            hsr += al * r;
-                            hsg += al * gg;
-                            hsb += al * bb;
-                        }
-                        // samples before rs_end lie in the node and the
-                        // volume; those from the next level threshold on are
-                        // not taken
-                        long long end = rs_end;
-                        if (adaptive && lod + 1 < L && (long long)s_lv[lod + 1].K < end) end = s_lv[lod + 1].K;
-                        const long long rr = 1ll << rsh;
-                        long long n = (end - k + rr - 1) / rr;
-                        if (n < 1) n = 1;
-                        skip_to = k + n * rr;
-                        if (hsa > 0.0f) {
-                            double tau = (double)hp;
-                            for (int q = 0; q < rsh; ++q) tau *= tau;
-                            hl->tau = tau;
-                            hl->t0 = Tr;
-                            hl->hsa = hsa;
-                            hl->hsr = hsr;
-                            hl->hsg = hsg;
-                            hl->hsb = hsb;
-                            hom_on = true;
-                        } else {
-                            // nothing to composite: the span is skipped
-                            st_samples += (uint32_t)n;
-                            st_hom += (uint32_t)n;
-                            ++k;
-                        }
-                        skipped = true;
-                    }
-                }
-                if (skipped) {
-                    cur_leaf = kInvalid;
-                    continue;
-                }
-                cur_leaf = leaf;
-#pragma unroll
-                for (int a = 0; a < 3; ++a) lc[a] = (iu[a] >> field(leafl.nsh, a)) << field(leafl.nsh, a);
-                lcd = D;
+        uint32_t end_nsh = leafl.nsh;  // node whose exit ends the segment
+        bool skip = false;
+        const bool same = leaf == cur_leaf && lod == cur_lod;
+        uint32_t rs_node = 0, rs_mask = 0;  // render-and-skip: the node and its homogeneous channels
+        // with a traversal depth the decision node depends on the level too
+        if (leaf != cur_leaf || (tdepth && lod != cur_lod)) {
+            // Descend from the start level and skip the first node that
+            // is empty for every visible channel (the leaf included).
+            // Every ancestor of a visited leaf is non-empty, so levels
+            // whose node also holds the last visited leaf are known
+            // non-empty and the test starts below them (the same node
+            // is skipped either way).  With HOMOG the first node in which
+            // every visible channel is empty or holds one value (and one
+            // holds a value) is rendered from those values and skipped
+            // (Alg. 1 renderAndSkipNode, Sec. 6.1: homogeneous for all
+            // channels): its samples are composited and the ray goes on
+            // past the node.  Ancestors of a visited leaf are never such
+            // nodes either (metadata nest, so their descendants would be),
+            // and the ancestors of a skipped node were tested and found
+            // not to be skipped: the shared levels above the last visited
+            // leaf or skipped node are not tested again.  An axis whose leaf
+            // coordinates differ in their lowest n bits only is shared down to
+            // depth D - n (an axis is split at the last of the levels).
+            int d0 = noskip ? dend : min(s0, dend);
+            if (lc[0] >= 0 && !noskip && !tdepth) {
+                const uint32_t x = (uint32_t)(iu[0] ^ lc[0]) >> field(leafl.nsh, 0),
+                               y = (uint32_t)(iu[1] ^ lc[1]) >> field(leafl.nsh, 1),
+                               z = (uint32_t)(iu[2] ^ lc[2]) >> field(leafl.nsh, 2);
+                const int n = 32 - __clz((int)(x | y | z));  // the longest of the three
+                d0 = max(d0, min(lcd, D - n + 1));
             }
+            for (int dl = d0; dl <= dend; ++dl) {
+                const NodeLds nd = s_nd[dl];
+                const uint32_t node = node_at(nd, iu[0] >> field(nd.nsh, 0), iu[1] >> field(nd.nsh, 1),
+                                              iu[2] >> field(nd.nsh, 2));
+                // the node's metadata, vGroup channels per batch of loads
+                uint32_t em = 0, hm = 0;
+                const uint32_t *nm = gmem(A.meta) + (size_t)node * m;
+                if (AOV && A.nodes) A.nodes[node] = 1;
+#pragma unroll
+                for (int g = 0; g < kOwn; g += vGroup) {
+                    const int j0 = own + g;
+                    if (P == 1 && g >= nvis) break;
+                    uint32_t mm[vGroup];
+                    if (vGroup > 1 && A.ident) {
+                        group_read<vGroup>(nm + min(j0, nvis - vGroup), mm);  // one aligned load
+                    } else {
+#pragma unroll
+                        for (int jj = 0; jj < vGroup; ++jj) mm[jj] = nm[s_ch[j0 + jj].c];
+                    }
+                    if (single) {
+                        // one zero run [0, ehi] per channel: empty iff the maximum is within it
+                        uint32_t eh[vGroup];
+                        group_read<vGroup>(s_par->ehi + j0, eh);
+#pragma unroll
+                        for (int jj = 0; jj < vGroup; ++jj) em |= mm[jj] <= eh[jj] ? 1u << (j0 + jj) : 0u;
+                    } else {
+#pragma unroll
+                        for (int jj = 0; jj < vGroup; ++jj) {
+                            const int j = j0 + jj;
+                            if (j < nvis && range_empty(mm[jj], s_runs + j * kMaxRuns, s_ch[j].nruns)) em |= 1u << j;
+                        }
+                    }
+                    if (homog) {
+#pragma unroll
+                        for (int jj = 0; jj < vGroup; ++jj) {
+                            const int j = j0 + jj;
+                            if (j < nvis && (mm[jj] & 0xFFFFu) == (mm[jj] >> 16)) hm |= 1u << j;
+                        }
+                    }
+                    asm volatile("" ::: "memory");
+                }
+                em = all_of_ray(em);
+                if (homog) hm = all_of_ray(hm);
+                em &= vismask;
+                hm &= ~em;
+                if (dl == dend) emask = em;
+                const bool all_empty = em == vismask;
+                const bool rskip = homog && hm && (em | hm) == vismask;
+                // (without skipping, empty nodes are stepped through;
+                // render-and-skip changes the image, so it stays on)
+                if ((all_empty && !noskip) || rskip) {
+                    skip = true;
+                    end_nsh = nd.nsh;
+                    lcd = dl;
+                    rs_node = node;
+                    if (!all_empty) rs_mask = hm;
+                    break;
+                }
+            }
+            cur_leaf = skip ? kInvalid : leaf;
+            lcd = skip ? lcd : D;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) lc[a] = (iu[a] >> field(end_nsh, a)) << field(end_nsh, a);
+        }
+        // First sample after k that may lie outside the node (or the volume):
+        // the last one inside is found from the exit distance and confirmed
+        // by the sampling path's own position test; positions grow
+        // monotonically, so those in between are inside too.
+        double end;
+        {
+            double te = INFINITY;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                if (dd[a] == 0.0) continue;
+                const int sh = (int)field(end_nsh, a);
+                const int lo_a = (iu[a] >> sh) << sh;
+                const int bound = dd[a] > 0.0 ? min(lo_a + (1 << sh), A.dims[a]) : lo_a;
+                te = fmin(te, ((double)bound - oo[a]) * lds.inverse(a));
+            }
+            double kb = fmin(floor(te * A.inv_step), kend);
+            auto in_node = [&]() {
+                bool in = true;
+                const double tk = kb * step;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    const double ua = fma(tk, dd[a], oo[a]);
+                    in = in && ua >= 0.0 && ua < (double)A.dims[a] && ((((int)ua) ^ iu[a]) >> field(end_nsh, a)) == 0;
+                }
+                return in;
+            };
+            end = k + 1.0;
+            for (int i = 0; i < 2 && kb > k; ++i) {
+                if (in_node()) {
+                    end = kb + 1.0;
+                    break;
+                }
+                kb -= 1.0;
+            }
+        }
+        if (skip) {
+            if constexpr (HOMOG) {
+                if (rs_mask) {
+                    // The constant mix of the homogeneous channels (in
+                    // visible-channel order, as sampled values mix) for the
+                    // taken samples k, k + r, .. of the span: up to the
+                    // node's exit, the volume's exit (the node may reach
+                    // beyond the volume, whose samples are void) and, with
+                    // the adaptive step, the next level threshold (r may
+                    // change there).  One transparency factor per sample,
+                    // so early termination falls on the same sample as
+                    // sample by sample; the colour is summed in closed form.
+                    float hp = 1.0f, hsa = 0.0f, hsr = 0.0f, hsg = 0.0f, hsb = 0.0f;
+                    const uint32_t *rm = gmem(A.meta) + (size_t)rs_node * m;
+                    for (int j = 0; j < nvis; ++j) {
+                        if (!((rs_mask >> j) & 1u)) continue;
+                        const float v = (float)(rm[s_ch[j].c] & 0xFFFFu);
+                        float f, al, r, gg, bb;
+                        const int e = j * kTfStride + tf_entry(v, s_par->w0[j], s_par->iw[j], f);
+                        if (onecol) {
+                            al = fmaf(s_tfa[e].y, f, s_tfa[e].x);
+                            r = s_par->r[j];
+                            gg = s_par->g[j];
+                            bb = s_par->b[j];
+                        } else {
+                            const float4 ta = s_tf[e], tb = s_tf[e + 1];
+                            al = fmaf(tb.w - ta.w, f, ta.w);
+                            r = fmaf(tb.x - ta.x, f, ta.x);
+                            gg = fmaf(tb.y - ta.y, f, ta.y);
+                            bb = fmaf(tb.z - ta.z, f, ta.z);
+                        }
+                        hp *= 1.0f - al;
+                        hsa += al;
+                        hsr = fmaf(al, r, hsr);
+                        hsg = fmaf(al, gg, hsg);
+                        hsb = fmaf(al, bb, hsb);
+                    }
+                    if (adaptive) end = fmin(end, klod);
+                    const double rr = ldexp(1.0, rsh);
+                    const double n = fmax(ceil((end - k) / rr), 1.0);
+                    uint32_t i = 0;
+                    end = k + n * rr;
+                    if (hsa > 0.0f) {
+                        double tau = (double)hp;
+                        for (int q = 0; q < rsh; ++q) tau *= tau;
+                        const double t0 = Tr;
+                        while ((double)i < n && !done) {
+                            Tr *= tau;
+                            ++i;
+                            done = Tr <= one_minus_term;
+                        }
+                        const double sc = (t0 - Tr) / (double)hsa;
+                        Cr = fma(sc, (double)hsr, Cr);
+                        Cg = fma(sc, (double)hsg, Cg);
+                        Cb = fma(sc, (double)hsb, Cb);
+                    } else {
+                        i = (uint32_t)n;  // nothing to composite
+                    }
+                    if (q == 0) {
+                        st_samples += i;
+                        st_hom += i;
+                        st_iters += i;
+                    }
+                }
+            }
+            k = end;
+            kseg = k;
+            return;
+        }
+        if (!same) {
             cur_lod = lod;
-            ++st_visits;
+            if (q == 0) ++st_visits;
             missmask = 0;
-            lvpack = 0;
             if (rates) {
                 // the rate of each channel's clamped desired level (fixed within a visit)
                 rpk = 0;
@@ -818,160 +884,196 @@ __device__ __forceinline__ void render_rays(const RenderArgs &A, Source &src, co
             // Residency masks of the leaf give each channel the level it
             // samples (finest resident at or above the desired one).
             const uint16_t *lm = gmem(A.mask) + (size_t)leaf * m;
-            uint32_t look = 0;  // channels with a resident brick to look up
-            bool all_at = false;  // every non-empty channel resident at the common desired level
-            int lsu = 0;
-            if (NV >= 4 && A.ident && A.uni) {
+            uint32_t look = vismask & ~emask;  // channels with a resident brick to look up
+            bool uniform = false;              // they sample one level, lu0
+            int lu0 = 0;
+            if (kOwn > 1 && A.ident && A.uni) {
                 // one desired level for every channel: AND the masks of all
                 // channels (two per word) and test its bit
-                lsu = min(max(lod, A.lo[0]), A.hi[0]);
-                uint32_t andm = 0xFFFFFFFFu;
+                lu0 = min(max(lod, A.lo[0]), A.hi[0]);
+                uint32_t miss = 0;
 #pragma unroll
-                for (int g = 0; g < NV; g += 4) {
-                    if (g >= nvis) break;
-                    const uint2 v = *(const uint2 *)(lm + g);
-                    andm &= v.x & v.y;
+                for (int g = 0; g < kOwn; g += vGroup) {
+                    if (P == 1 && g >= nvis) break;
+                    uint32_t v[vGroup / 2 > 0 ? vGroup / 2 : 1];
+                    group_read<(vGroup / 2 > 0 ? vGroup / 2 : 1)>((const uint32_t *)(lm + min(own + g, nvis - vGroup)), v);
+#pragma unroll
+                    for (int i = 0; i < vGroup / 2; ++i) miss |= ~v[i];
                 }
-                andm &= andm >> 16;
-                all_at = ((andm >> lsu) & 1u) != 0;
+                miss = all_of_ray(miss | miss >> 16);
+                uniform = !((miss >> lu0) & 1u);
             }
-            if (all_at) {
-                look = vismask & ~emask;
-                lvpack = 0;
+            if (!uniform) {
+                const uint32_t want = look;
+                uint32_t levels = 0;  // levels sampled, one bit each
+                look = 0;
+                uint32_t lv0 = 0, lv1 = 0;  // their levels, 4 bits each
 #pragma unroll
-                for (int j = 0; j < NV; ++j)
-                    if ((look >> j) & 1u) lvpack |= (uint64_t)lsu << (4 * j);
-            } else {
+                for (int g = 0; g < kOwn; g += vGroup) {
+                    const int j0 = own + g;
+                    if (P == 1 && g >= nvis) break;
+                    uint32_t mk[vGroup];
+                    if (vGroup > 1 && A.ident) {
+                        uint32_t v[vGroup / 2 > 0 ? vGroup / 2 : 1];
+                        group_read<(vGroup / 2 > 0 ? vGroup / 2 : 1)>((const uint32_t *)(lm + min(j0, nvis - vGroup)), v);
 #pragma unroll
-                for (int g = 0; g < NV; g += kGroup) {
-                    if (g >= nvis) break;
-                    uint32_t mk[kGroup];
-                    if (kGroup == 4 && A.ident) {
-                        const uint2 v = *(const uint2 *)(lm + g);
-                        mk[0] = v.x & 0xFFFFu;
-                        mk[kGroup > 1 ? 1 : 0] = v.x >> 16;
-                        mk[kGroup > 2 ? 2 : 0] = v.y & 0xFFFFu;
-                        mk[kGroup > 3 ? 3 : 0] = v.y >> 16;
+                        for (int jj = 0; jj < vGroup; ++jj) mk[jj] = jj & 1 ? v[jj / 2] >> 16 : v[jj / 2] & 0xFFFFu;
                     } else {
 #pragma unroll
-                        for (int jj = 0; jj < kGroup; ++jj) mk[jj] = g + jj < nvis ? (uint32_t)lm[s_ch[g + jj].c] : 0u;
+                        for (int jj = 0; jj < vGroup; ++jj) mk[jj] = (uint32_t)lm[s_ch[j0 + jj].c];
                     }
 #pragma unroll
-                    for (int jj = 0; jj < kGroup; ++jj) {
-                        const int j = g + jj;
-                        if (j < nvis && !((emask >> j) & 1u)) {
+                    for (int jj = 0; jj < vGroup; ++jj) {
+                        const int j = j0 + jj;
+                        if ((want >> j) & 1u) {
                             const ChanLds ch = s_ch[j];
                             const int ls = min(max(lod, ch.lo), ch.hi);
                             const uint32_t mj = mk[jj] >> ls;
                             if (!(mj & 1u)) missmask |= 1u << j;
                             if (mj) {
-                                lvpack |= (uint64_t)(ls + __builtin_ctz(mj)) << (4 * j);
+                                const int lu = ls + __builtin_ctz(mj);
+                                if (j < 8) lv0 |= (uint32_t)lu << (4 * j);
+                                else lv1 |= (uint32_t)lu << (4 * j - 32);
                                 look |= 1u << j;
+                                levels |= 1u << lu;
                             }
                         }
                     }
+                }
+                look = all_of_ray(look);
+                levels = all_of_ray(levels);
+                missmask = all_of_ray(missmask);
+                lvpack = (uint64_t)all_of_ray(lv0) | (uint64_t)(NV > 8 ? all_of_ray(lv1) : 0u) << 32;
+                uniform = (levels & (levels - 1u)) == 0;
+                lu0 = __builtin_ctz(levels | 0x10000u) & 15;
+            }
+            // Misses are counted by the visits that share the missing
+            // channels and the desired bricks: the finest desired brick and
+            // the level fix the others.
+            if (missmask | pmask) {
+                const LevLds lf = s_lv[min(max(lod, A.step_lo), A.step_hi)];
+                const uint32_t key = (uint32_t)(iu[0] >> field(lf.sh, 0)) | (uint32_t)(iu[1] >> field(lf.sh, 1)) << 8 |
+                                     (uint32_t)(iu[2] >> field(lf.sh, 2)) << 16 | (uint32_t)lod << 24;
+                if (missmask != pmask || key != pkey) {
+                    // the wave adds them after the visits
+                    fpend = npend;
+                    fmask = pmask;
+                    fkey = pkey;
+                    npend = 0;
+                    pmask = rates ? 0 : missmask;
+                    pkey = key;
                 }
             }
             // When every looked-up channel samples one level, its bricks are
             // the same grid cell in each channel: if that cell and level are
             // those of the previous visit, the slots found then still hold
             // (the page table does not change during a frame).
-            uint32_t key = kInvalid;
-            if (look) {
-                int lu0 = lsu;
-                bool uniform = true;
-                if (!all_at) {
-                    lu0 = (int)((lvpack >> (4 * __builtin_ctz(look))) & 15u);
-#pragma unroll
-                    for (int j = 0; j < NV; ++j)
-                        if (((look >> j) & 1u) && (int)((lvpack >> (4 * j)) & 15u) != lu0) uniform = false;
-                }
-                if (uniform) {
-                    const LevLds lv = s_lv[lu0];
-                    key = brick_dense(lv, 0u, 0u, iu[0] >> field(lv.sh, 0), iu[1] >> field(lv.sh, 1),
-                                      iu[2] >> field(lv.sh, 2)) |
-                          ((uint32_t)lu0 << 28);
-                }
+            uint32_t key = kInvalid, cell = 0;
+            if (look && uniform) {
+                const LevLds lv = s_lv[lu0];
+                cell = brick_dense(lv, 0u, 0u, iu[0] >> field(lv.sh, 0), iu[1] >> field(lv.sh, 1),
+                                   iu[2] >> field(lv.sh, 2));
+                key = cell | ((uint32_t)lu0 << 28);
             }
             const uint32_t reuse = (key != kInvalid && key == last_key) ? have : 0u;
+            const uint32_t find = look & ~reuse;
             uint32_t nhave = reuse & look;
             // channels whose slot changes: looked up anew, or no longer sampled
-            if ((look & ~reuse) | (have & ~look)) {
-                nhave = 0;
+            if (find) {
+                uint32_t got = 0, restamp = 0;
 #pragma unroll
-                for (int g = 0; g < NV; g += kGroup) {
-                    if (g >= nvis) break;
-                    uint32_t ns[kGroup];
+                for (int g = 0; g < kOwn; g += vGroup) {
+                    const int j0 = own + g;
+                    if (P == 1 && g >= nvis) break;
+                    uint32_t ns[vGroup], cb[vGroup];
+                    group_read<vGroup>(s_par->cbase + j0, cb);
 #pragma unroll
-                    for (int jj = 0; jj < kGroup; ++jj) {
-                        const int j = g + jj;
+                    for (int jj = 0; jj < vGroup; ++jj) {
+                        const int j = j0 + jj;
                         ns[jj] = kInvalid;
-                        if ((look >> j) & 1u) {
-                            if ((reuse >> j) & 1u) {
-                                ns[jj] = slot[j];
-                            } else {
-                                const int lu = (int)((lvpack >> (4 * j)) & 15u);
-                                const LevLds lv = s_lv[lu];
-                                ns[jj] = gmem(A.pt)[brick_dense(lv, (uint32_t)s_ch[j].c, A.per_channel,
-                                                          iu[0] >> field(lv.sh, 0), iu[1] >> field(lv.sh, 1),
-                                                          iu[2] >> field(lv.sh, 2))];
+                        if ((find >> j) & 1u) {
+                            uint32_t b = cell;
+                            if (key == kInvalid) {
+                                const LevLds lv = s_lv[(int)((lvpack >> (4 * j)) & 15u)];
+                                b = brick_dense(lv, 0u, 0u, iu[0] >> field(lv.sh, 0), iu[1] >> field(lv.sh, 1),
+                                                iu[2] >> field(lv.sh, 2));
                             }
+                            ns[jj] = gmem(A.pt)[cb[jj] + b];
                         }
                     }
 #pragma unroll
-                    for (int jj = 0; jj < kGroup; ++jj) {
-                        const int j = g + jj;
-                        if (j >= nvis) break;
-                        if (ns[jj] == kInvalid) {
-                            lvpack &= ~((uint64_t)15u << (4 * j));
-                        } else {
-                            nhave |= 1u << j;
-                            if (ns[jj] != slot[j]) {
+                    for (int jj = 0; jj < vGroup; ++jj) {
+                        const int j = j0 + jj;
+                        if (ns[jj] != kInvalid) {
+                            got |= 1u << j;
+                            if (!((have >> j) & 1u) || ns[jj] != lds.slot(j)) {
                                 // with rates the stamp waits for a sample the channel takes part in
-                                if (rates) stamped &= ~(1u << j);
+                                if (rates) restamp |= 1u << j;
                                 else gmem(A.stamp)[ns[jj]] = A.frame;
+                                lds.slot(j) = ns[jj];
                             }
                         }
-                        slot[j] = ns[jj];
                     }
                     asm volatile("" ::: "memory");
                 }
+                nhave |= all_of_ray(got);
+                if (rates) stamped &= ~all_of_ray(restamp);
             }
+            // a channel without a slot reads slot 0 in the gathers
+            for (uint32_t gone = have & ~nhave; gone; gone &= gone - 1u) lds.slot(__builtin_ctz(gone)) = 0;
             have = nhave;
             last_key = key;
+            // the ray in the voxels of the segment's level
+            uint32_t nsh = 0;
+            if (key != kInvalid) {
+                const LevLds lv = s_lv[lu0];
+                nsh = lv.raw;
+                const uint32_t bx = (uint32_t)(iu[0] >> field(lv.sh, 0)) << A.Blog,
+                               by = (uint32_t)(iu[1] >> field(lv.sh, 1)) << A.Blog,
+                               bz = (uint32_t)(iu[2] >> field(lv.sh, 2)) << A.Blog;
+                cbias = (bz * E + by) * E + bx;
+            }
+            vsh = nsh;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                o[a] = ldexp(oo[a], -(int)field(nsh, a));
+                d[a] = ldexp(dd[a], -(int)field(nsh, a));
+            }
         }
-        ++st_samples;
+        // the segment: samples of this leaf at this level
+        kseg = fmin(end, klod);
+        if (have == 0 && !per_sample) {
+            // no channel has a slot here: the segment's samples are counted, not taken
+            const double rr = ldexp(1.0, rsh);
+            const double n = fmax(ceil(ldexp(kseg - k, -rsh)), 1.0);
+            const uint32_t c = (uint32_t)n;
+            npend += c;
+            if (q == 0) {
+                st_samples += c;
+                st_nonempty += c * __popc(vismask & ~emask);
+                st_iters += c;
+            }
+            k += n * rr;
+            kseg = k;
+        }
+    };
+
+    // The segment's next P samples: lane q takes the q-th of them, and each
+    // lane composites all of them in order.
+    auto sample = [&]() {
+        const double rr = (double)(1 << rsh);
+        const double kq = P == 1 ? k : k + (double)q * rr;
+        const bool mine = P == 1 || kq < kseg;
         float prod = 1.0f, sa = 0.0f, sr = 0.0f, sg = 0.0f, sbl = 0.0f;
         // channels taking part in this sample (all of them without rates)
         uint32_t part = vismask;
         if (rates) {
             part = 0;
+            const uint32_t kl = (uint32_t)(uint64_t)kq;  // rates are at most 2^15
             for (int j = 0; j < nvis; ++j) {
                 const int rs = (int)((rpk >> (4 * j)) & 15u);
-                if (!(k & ((1ll << rs) - 1))) part |= 1u << j;
+                if (!(kl & ((1u << rs) - 1u))) part |= 1u << j;
             }
-            // misses and stamps per sample (a visit's samples differ in which
-            // channels take part)
-            uint32_t mp = missmask & part;
-            while (mp) {
-                const int j = __builtin_ctz(mp);
-                mp &= mp - 1u;
-                const ChanLds ch = s_ch[j];
-                const LevLds lv = s_lv[min(max(lod, ch.lo), ch.hi)];
-                atomicAdd(&gmem(A.cnt)[brick_dense(lv, (uint32_t)ch.c, A.per_channel, iu[0] >> field(lv.sh, 0),
-                                             iu[1] >> field(lv.sh, 1), iu[2] >> field(lv.sh, 2))],
-                          1u);
-                ++st_miss;
-            }
-            uint32_t sp = have & part & ~stamped;
-            while (sp) {
-                const int j = __builtin_ctz(sp);
-                sp &= sp - 1u;
-                gmem(A.stamp)[slot[j]] = A.frame;
-            }
-            stamped |= have & part;
-        } else {
-            ++nvisit;
         }
         if (AOV && A.reqb) {
             // Bricks required per pixel: the desired brick of each channel not
@@ -984,41 +1086,33 @@ __device__ __forceinline__ void render_rays(const RenderArgs &A, Source &src, co
                 if (((emask >> j) & 1u) || !((part >> j) & 1u)) continue;
                 const ChanLds ch = s_ch[j];
                 const LevLds lv = s_lv[min(max(lod, ch.lo), ch.hi)];
-                const uint32_t key = brick_dense(lv, 0u, 0u, iu[0] >> field(lv.sh, 0), iu[1] >> field(lv.sh, 1),
-                                                 iu[2] >> field(lv.sh, 2));
+                const uint32_t key = brick_dense(lv, 0u, 0u, lc[0] >> field(lv.sh, 0), lc[1] >> field(lv.sh, 1),
+                                                 lc[2] >> field(lv.sh, 2));
                 if (rb[1 + j] != key) {
                     rb[1 + j] = key;
                     rb[0] += 1;
                 }
             }
         }
-        st_nonempty += __popc(vismask & ~emask & part);
-        st_reads += __popc(have & part);  // the channels gathered below (those with a slot)
+        const uint32_t use = have & part;  // the channels gathered below
         // ---- sample every visible channel
-        // In-brick coordinates depend only on the level a channel samples
-        // (bricks of one level share their grid), so they are computed once
-        // per distinct level of the sample.  Channels are gathered in groups
-        // of kGroup: the group's loads are all issued before any of them is
-        // used, and two horizontally adjacent voxels come in one load.
-        int lprev = -1;
+        // Channels are gathered in groups of kGroup: the group's loads are all
+        // issued before any of them is used, and two horizontally adjacent
+        // voxels come in one load.
+        const double t = kq * step;
         uint32_t idx = 0;
         float fr0 = 0.0f, fr1 = 0.0f, fr2 = 0.0f;
-        const uint32_t E = EC ? (uint32_t)EC : (uint32_t)A.E;
-        const size_t stride = EC ? slot_bytes(EC, BPV) : (size_t)A.slot_stride;
-        // in-brick voxel index and fractions of the sample at level lu
+        int lprev = -1;
+        // in-brick voxel index and fractions where channels sample different levels
         auto in_brick = [&](int lu) {
             const LevLds lv = s_lv[lu];
             uint32_t i0[3];
             float fr[3];
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                const int sft = (int)field(lv.raw, a);
-                const double ul = ldexp(u[a], -sft);
-                const int bo = (iu[a] >> field(lv.sh, a)) << A.Blog;
-                const double q = ul + 0.5 - (double)bo;
-                const int qi = (int)q;
-                i0[a] = (uint32_t)qi;
-                fr[a] = (float)(q - (double)qi);
+                const double u = ldexp(fma(t, d[a], o[a]), -(int)field(lv.raw, a)) + 0.5;
+                i0[a] = (uint32_t)((int)u - ((lc[a] >> field(lv.sh, a)) << A.Blog));
+                fr[a] = (float)__builtin_amdgcn_fract(u);
             }
             idx = (i0[2] * E + i0[1]) * E + i0[0];
             fr0 = fr[0];
@@ -1028,128 +1122,275 @@ __device__ __forceinline__ void render_rays(const RenderArgs &A, Source &src, co
         };
         // Gather, interpolate, classify and mix every channel with a slot.
         // With UNI every such channel reads the visit's one level, whose
-        // coordinates are computed before the loop, so the FP64 position is
-        // not live across the channels.
+        // coordinates are computed before the loop.
         auto sample_channels = [&](auto uni_c) {
             constexpr bool UNI = decltype(uni_c)::value;
-            // the channel count and the slot pool (the same in every lane:
-            // kernel arguments, or the workgroup's staged request) as scalar
-            // values of this sample: the group tests stay scalar compares and
-            // the pool address stays in registers instead of being hoisted
-            // out of the ray loop
-            // (the builtin returns int: each half is taken back to uint32_t
-            // before widening, so the low half is not sign-extended)
-            int nvs = __builtin_amdgcn_readfirstlane(nvis);
-            const uint64_t pa = reinterpret_cast<uint64_t>(A.slots);
-            const uint32_t phi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(pa >> 32));
-            const uint32_t plo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)pa);
-            uint64_t pv = ((uint64_t)phi << 32) | (uint64_t)plo;
-            asm volatile("" : "+s"(nvs), "+s"(pv));
-            const uint8_t *pool = (const uint8_t *)(const __attribute__((address_space(1))) uint8_t *)pv;
 #pragma unroll
-        for (int g = 0; g < NV; g += kGroup) {
-            if (g >= nvs) break;
-            uint32_t w[kGroup][4];
-            float fq[kGroup][3];
-            bool ok[kGroup];
+            for (int g = 0; g < NV; g += kGroup) {
+                if (g >= nvis) break;
+                uint32_t sw[kGroup], w[kGroup][4];
+                float fq[kGroup][3];
+                lds.group(g, sw);
+                float w0[kGroup], iw[kGroup];
+                group_read<kGroup>(s_par->w0 + g, w0);
+                group_read<kGroup>(s_par->iw + g, iw);
 #pragma unroll
-            for (int jj = 0; jj < kGroup; ++jj) {
-                const int j = g + jj;
-                // the slot words of channels past nvis stay invalid
-                ok[jj] = slot[j] != kInvalid;
-                if (rates) ok[jj] = ok[jj] && ((part >> j) & 1u);
-                if constexpr (!UNI) {
-                    const int lu = (int)((lvpack >> (4 * j)) & 15u);
-                    if (ok[jj] && lu != lprev) in_brick(lu);
+                for (int jj = 0; jj < kGroup; ++jj) {
+                    const int j = g + jj;
+                    if constexpr (!UNI) {
+                        const int lu = (int)((lvpack >> (4 * j)) & 15u);
+                        if (((use >> j) & 1u) && lu != lprev) in_brick(lu);
+                    }
+                    fq[jj][0] = fr0;
+                    fq[jj][1] = fr1;
+                    fq[jj][2] = fr2;
+                    // a channel without a slot reads slot 0 (always inside the
+                    // pool) and looks up the zero entry
+                    const uint8_t *base = pool + ((uint64_t)sw[jj] * stride + (uint64_t)(idx * (uint32_t)BPV));
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) w[jj][i] = vpair<BPV>(base + (size_t)((i & 1) * E + (i >> 1) * E * E) * BPV);
                 }
-                fq[jj][0] = fr0;
-                fq[jj][1] = fr1;
-                fq[jj][2] = fr2;
-                // a channel without a slot reads offset 0 of slot 0 (always
-                // inside the pool) and its result is discarded
-                const uint8_t *base = pool + (ok[jj] ? (size_t)slot[j] * stride + (size_t)idx * BPV : 0);
-                w[jj][0] = vpair<BPV>(base);
-                w[jj][1] = vpair<BPV>(base + (size_t)E * BPV);
-                w[jj][2] = vpair<BPV>(base + (size_t)E * E * BPV);
-                w[jj][3] = vpair<BPV>(base + (size_t)(E * E + E) * BPV);
-            }
+                // interpolated value of the group's channel jj
+                auto value = [&](int jj) {
+                    const float f0 = fq[jj][0], f1 = fq[jj][1], f2 = fq[jj][2];
+                    float c[4];
 #pragma unroll
-            for (int jj = 0; jj < kGroup; ++jj) {
-                const int j = g + jj;
-                if (!ok[jj]) continue;
-                const float f0 = fq[jj][0], f1 = fq[jj][1], f2 = fq[jj][2];
-                float v00[2], v10[2], v01[2], v11[2];
-                unpack<BPV>(w[jj][0], v00);
-                unpack<BPV>(w[jj][1], v10);
-                unpack<BPV>(w[jj][2], v01);
-                unpack<BPV>(w[jj][3], v11);
-                const float c00 = v00[0] + (v00[1] - v00[0]) * f0;
-                const float c10 = v10[0] + (v10[1] - v10[0]) * f0;
-                const float c01 = v01[0] + (v01[1] - v01[0]) * f0;
-                const float c11 = v11[0] + (v11[1] - v11[0]) * f0;
-                const float e0 = c00 + (c10 - c00) * f1;
-                const float e1 = c01 + (c11 - c01) * f1;
-                const float v = e0 + (e1 - e0) * f2;
-                float al, r, gg, bb;
-                classify(v, s_ch[j], s_tf + j * kTfStride, al, r, gg, bb);
-                if (rates) {
-                    // the channel stands for r_c base steps: transparency
-                    // (1 - alpha)^r_c, colour weight r_c alpha
-                    const int rs = (int)((rpk >> (4 * j)) & 15u);
-                    float tr = 1.0f - al;
-                    for (int q = 0; q < rs; ++q) tr *= tr;
-                    const float w = (float)(1 << rs) * al;
-                    prod *= tr;
-                    sa += w;
-                    sr += w * r;
-                    sg += w * gg;
-                    sbl += w * bb;
+                    for (int i = 0; i < 4; ++i) {
+                        float v[2];
+                        unpack<BPV>(w[jj][i], v);
+                        c[i] = fmaf(v[1] - v[0], f0, v[0]);
+                    }
+                    const float e0 = fmaf(c[1] - c[0], f1, c[0]);
+                    const float e1 = fmaf(c[3] - c[2], f1, c[2]);
+                    return fmaf(e1 - e0, f2, e0);
+                };
+                // mixes a channel of opacity al and colour (r, gg, bb); an
+                // opacity of zero changes nothing
+                auto mix = [&](int j, float al, float r, float gg, float bb) {
+                    if (rates) {
+                        // the channel stands for r_c base steps: transparency
+                        // (1 - alpha)^r_c, colour weight r_c alpha
+                        const int rs = (int)((rpk >> (4 * j)) & 15u);
+                        float tr = 1.0f - al;
+                        for (int q = 0; q < rs; ++q) tr *= tr;
+                        const float wt = (float)(1 << rs) * al;
+                        prod *= tr;
+                        sa += wt;
+                        sr = fmaf(wt, r, sr);
+                        sg = fmaf(wt, gg, sg);
+                        sbl = fmaf(wt, bb, sbl);
+                    } else {
+                        prod *= 1.0f - al;
+                        sa += al;
+                        sr = fmaf(al, r, sr);
+                        sg = fmaf(al, gg, sg);
+                        sbl = fmaf(al, bb, sbl);
+                    }
+                    if (AOV && A.aov && ((use >> j) & 1u))
+                        A.aov[((size_t)py * A.W + px) * L + (UNI ? (int)(last_key >> 28) : (int)((lvpack >> (4 * j)) & 15u))] += 1;
+                };
+                // table positions of the group, then its table reads, then the mix
+                int e[kGroup];
+                float f[kGroup];
+#pragma unroll
+                for (int jj = 0; jj < kGroup; ++jj)
+                    e[jj] = (g + jj) * kTfStride + tf_entry(value(jj), w0[jj], iw[jj], f[jj]);
+                constexpr uint32_t gm = (1u << kGroup) - 1u;
+                if (__any(((use >> g) & gm) != gm)) {
+#pragma unroll
+                    for (int jj = 0; jj < kGroup; ++jj)
+                        if (!((use >> (g + jj)) & 1u)) e[jj] = kTfStride * NV;
+                }
+                if (onecol) {
+                    // Every visible channel has one colour in all its table
+                    // entries (the usual stain colouring): its interpolation
+                    // returns that colour exactly, so only the opacity is
+                    // looked up: one 8-byte read and one multiply-add for two
+                    // 16-byte reads and eight operations.
+                    float2 ta[kGroup];
+                    float r[kGroup], gg[kGroup], bb[kGroup];
+#pragma unroll
+                    for (int jj = 0; jj < kGroup; ++jj) ta[jj] = s_tfa[e[jj]];
+                    group_read<kGroup>(s_par->r + g, r);
+                    group_read<kGroup>(s_par->g + g, gg);
+                    group_read<kGroup>(s_par->b + g, bb);
+#pragma unroll
+                    for (int jj = 0; jj < kGroup; ++jj)
+                        mix(g + jj, fmaf(ta[jj].y, f[jj], ta[jj].x), r[jj], gg[jj], bb[jj]);
                 } else {
-                    prod *= 1.0f - al;
-                    sa += al;
-                    sr += al * r;
-                    sg += al * gg;
-                    sbl += al * bb;
+#pragma unroll
+                    for (int jj = 0; jj < kGroup; ++jj) {
+                        const float4 ta = s_tf[e[jj]], tb = s_tf[e[jj] + 1];
+                        mix(g + jj, fmaf(tb.w - ta.w, f[jj], ta.w), fmaf(tb.x - ta.x, f[jj], ta.x),
+                            fmaf(tb.y - ta.y, f[jj], ta.y), fmaf(tb.z - ta.z, f[jj], ta.z));
+                    }
                 }
-                if (AOV && A.aov) A.aov[((size_t)py * A.W + px) * L + (int)((lvpack >> (4 * j)) & 15u)] += 1;
+                // the next group's loads are issued after this group is used:
+                // bounds the registers held by loads in flight
+                asm volatile("" ::: "memory");
             }
-            // the next group's loads are issued after this group is used:
-            // bounds the registers held by loads in flight
-            asm volatile("" ::: "memory");
-        }
         };
-        if (last_key != kInvalid) {
-            // one level for every channel with a slot (the visit's lookup key)
-            in_brick((int)(last_key >> 28));
-            sample_channels(std::true_type{});
-        } else {
-            sample_channels(std::false_type{});
-        }
-        if (sa > 0.0f) {
-            if (rsh == 0 || rates) {
-                const float as = 1.0f - prod;
-                const float sc = as / sa;
-                Cr += Tr * (double)(sr * sc);
-                Cg += Tr * (double)(sg * sc);
-                Cb += Tr * (double)(sbl * sc);
-                Tr *= 1.0 - (double)as;
+        float as = 0.0f, cr = 0.0f, cg = 0.0f, cb = 0.0f;
+        double trr = 1.0, dr = 0.0, dg = 0.0, db = 0.0;  // with opacity correction
+        const bool corr = rsh != 0 && !rates;
+        if (mine) {
+            if (last_key != kInvalid) {
+                // one level for every channel with a slot (the visit's lookup key)
+                int qi[3];
+                float fr[3];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    const double u = fma(t, d[a], o[a]) + 0.5;
+                    qi[a] = (int)u;
+                    fr[a] = (float)__builtin_amdgcn_fract(u);
+                }
+                idx = ((uint32_t)qi[2] * E + (uint32_t)qi[1]) * E + (uint32_t)qi[0] - cbias;
+                fr0 = fr[0];
+                fr1 = fr[1];
+                fr2 = fr[2];
+                sample_channels(std::true_type{});
             } else {
-                // opacity correction for a sample standing for r base steps:
-                // transparency prod^r, colour scaled with the opacity
-                double tr = (double)prod;
-                for (int q = 0; q < rsh; ++q) tr *= tr;
-                const double sc = (1.0 - tr) / (double)sa;
-                Cr += Tr * ((double)sr * sc);
-                Cg += Tr * ((double)sg * sc);
-                Cb += Tr * ((double)sbl * sc);
-                Tr *= tr;
+                sample_channels(std::false_type{});
             }
-            if (Tr <= one_minus_term) done = true;
+            if (sa > 0.0f) {
+                if (!corr) {
+                    as = 1.0f - prod;
+                    const float sc = as / sa;
+                    cr = sr * sc;
+                    cg = sg * sc;
+                    cb = sbl * sc;
+                } else {
+                    // opacity correction for a sample standing for r base steps:
+                    // transparency prod^r, colour scaled with the opacity
+                    trr = (double)prod;
+                    for (int i = 0; i < rsh; ++i) trr *= trr;
+                    const double sc = (1.0 - trr) / (double)sa;
+                    dr = (double)sr * sc;
+                    dg = (double)sg * sc;
+                    db = (double)sbl * sc;
+                }
+            }
+        }
+        uint32_t taken = 0;
+        const uint32_t hit = (sa > 0.0f ? 1u : 0u) | (mine ? 2u : 0u);
+        auto composite = [&](auto lane_c) {
+            constexpr int i = decltype(lane_c)::value;
+            const uint32_t h = ray_lane<P, i>(hit);
+            if (done || !(h & 2u)) return;
+            ++taken;
+            if (!(h & 1u)) return;
+            if (!corr) {
+                Cr = fma(Tr, (double)ray_lane<P, i>(cr), Cr);
+                Cg = fma(Tr, (double)ray_lane<P, i>(cg), Cg);
+                Cb = fma(Tr, (double)ray_lane<P, i>(cb), Cb);
+                Tr *= 1.0 - (double)ray_lane<P, i>(as);
+            } else {
+                Cr = fma(Tr, ray_lane<P, i>(dr), Cr);
+                Cg = fma(Tr, ray_lane<P, i>(dg), Cg);
+                Cb = fma(Tr, ray_lane<P, i>(db), Cb);
+                Tr *= ray_lane<P, i>(trr);
+            }
+            done = Tr <= one_minus_term;
+        };
+        composite(std::integral_constant<int, 0>{});
+        if (P == 4) {
+            composite(std::integral_constant<int, 1>{});
+            composite(std::integral_constant<int, 2>{});
+            composite(std::integral_constant<int, 3>{});
+        }
+        if (!rates) {
+            npend += taken;
+        } else {
+            // misses and stamps per sample (a visit's samples differ in which
+            // channels take part)
+            const bool counts = P == 1 || (uint32_t)q < taken;
+            uint32_t mp = counts ? missmask & part : 0u;
+            while (mp) {
+                const int j = __builtin_ctz(mp);
+                mp &= mp - 1u;
+                const ChanLds ch = s_ch[j];
+                const LevLds lv = s_lv[min(max(lod, ch.lo), ch.hi)];
+                atomicAdd(&gmem(A.cnt)[brick_dense(lv, (uint32_t)ch.c, A.per_channel, lc[0] >> field(lv.sh, 0),
+                                                   lc[1] >> field(lv.sh, 1), lc[2] >> field(lv.sh, 2))],
+                          1u);
+                ++st_miss;
+            }
+            uint32_t sp = counts ? have & part & ~stamped : 0u;
+            const uint32_t now = all_of_ray(sp);
+            while (sp) {
+                const int j = __builtin_ctz(sp);
+                sp &= sp - 1u;
+                gmem(A.stamp)[lds.slot(j)] = A.frame;
+            }
+            stamped |= now;
+        }
+        if (P == 1 || (uint32_t)q < taken) {
+            ++st_samples;
+            st_nonempty += __popc(vismask & ~emask & part);
+            st_reads += __popc(use);
         }
         // the next sample: with the adaptive step the next multiple of r (the
-        // level only grows along the ray, so no grid point lies in between);
-        // each lane keeps its own phase and samples on every iteration
-        k += 1ll << rsh;
+        // level only grows along the ray, so no grid point lies in between)
+        k += P == 1 ? rr : rr * (double)taken;
+    };
+
+    // Rays of a wave keep together, so that their gathers share cache lines: a
+    // ray samples while its index is at most klim, counted from the last ray
+    // of the wave (as of when the limit was last set).  The distance is in
+    // whole groups of P samples, 1.25 of them per sample that a pixel's
+    // footprint spans: where neighbouring rays are far apart their samples
+    // share few lines anyway and fewer waits count more (one group on the
+    // 16-channel 1080p frame at half a voxel a pixel: 42.5 ms, two groups
+    // 44.7; on a 455 x 256 frame of the same channels at three voxels a pixel
+    // one group 2.6 ms, five 2.1).
+    // Visits wait until kVisitLanes lanes need one or no ray can sample: a
+    // visit is a chain of dependent loads and several hundred instructions,
+    // whatever the number of lanes that take part (512 x 512, 4 channels:
+    // every visit at once 2.7 ms, at four lanes 2.6, 16: 2.2, 24: 2.15).
+    constexpr int kVisitLanes = 24;
+    double klim = -1.0;
+    if ((threadIdx.x & 63u) < kMissEntries) lds.miss[3 * (threadIdx.x & 63u) + 1] = 0;
+    src.init();
+    while (true) {
+        const bool fin = has && (done || k > kend);
+        if (__any(fin)) {
+            flush(fin ? npend : 0u, pmask, pkey);
+            if (fin) finish();
+        }
+        if (!__any(has)) {
+            int x = 0, y = 0;
+            bool v = false;
+            if (!src.next(x, y, v)) break;
+            start(x, y, v);
+        }
+        const bool active = has && !done && k <= kend;
+        const bool wv = active && k >= kseg;
+        const uint64_t bv = __ballot(wv);
+        bool ws = active && !wv && k <= klim;
+        uint64_t bs = __ballot(ws);
+        if (!bs) {
+            // (the minimum is taken by all lanes of the wave, not under a branch)
+            // the limit bounds the lanes' distance only: a rounded index does
+            const float kmin = wave_min(active ? (float)k : 3.0e38f);
+            const float groups = floorf(1.25f * fmaf(kmin, A.win_k, A.win_0) + 0.5f);
+            klim = (double)(kmin + (float)P * fmaxf(groups, 1.0f) - 1.0f);
+            ws = active && !wv && (k <= klim || !bv);
+            bs = __ballot(ws);
+        }
+        if (!(bv | bs)) continue;  // rays that just began without a sample
+        if (bv && (!bs || __popcll(bv) >= kVisitLanes)) {
+            if (wv) visit();
+            flush(fpend, fmask, fkey);
+            fpend = 0;
+            continue;
+        }
+        ++st_iters;  // a stepping iteration of the wave (lane busy or idle)
+        if (ws) sample();
+    }
+    // the table's sums
+    for (int i = 0; i < kMissEntries; ++i) {
+        const uint32_t *e = lds.miss + 3 * i;
+        if (e[1]) count_misses(e[0], e[1], e[2]);
     }
     stats[0] = st_samples;
     stats[1] = st_reads;
@@ -1162,16 +1403,17 @@ __device__ __forceinline__ void render_rays(const RenderArgs &A, Source &src, co
 
 // Workgroup set-up: stage the frame's transfer functions, zero-alpha runs,
 // channel parameters, per-level brick tables and per-level node tables in
-// LDS.  Ends with a workgroup barrier.
+// LDS.  A wave looks over a channel's table with four 64-entry ballots (a
+// scan by one lane, entry after entry through LDS, was 10 us of a small
+// frame).  Where every visible table has one colour, the tables are staged as
+// (opacity, step) pairs.  Ends with a workgroup barrier.
 template <int NV>
-__device__ __forceinline__ void stage_frame(const RenderArgs &A, float4 *s_tf, ChanLds *s_ch, uint32_t *s_runs,
-                                            LevLds *s_lv, NodeLds *s_nd) {
+__device__ __forceinline__ void stage_frame(const RenderArgs &A, float4 *s_tf, ChanLds *s_ch, ChanPar<NV> *s_par,
+                                            uint32_t *s_runs, LevLds *s_lv, NodeLds *s_nd) {
     const int nvis = A.nvis;
-    for (int i = threadIdx.x; i < nvis * kTfStride; i += blockDim.x) {
-        const int t = i / kTfStride, e = i - t * kTfStride;
-        s_tf[i] = A.tf[t * 256 + (e < 256 ? e : 255)];
-    }
     const unsigned t = threadIdx.x;
+    const int lane = (int)(t & 63u), wave = (int)(t >> 6), waves = (int)(blockDim.x >> 6);
+    const float4 *tf = gmem(A.tf);
     if (t < (unsigned)A.L) {
         LevLds lv;
         lv.raw = A.lsh[t];
@@ -1183,6 +1425,12 @@ __device__ __forceinline__ void stage_frame(const RenderArgs &A, float4 *s_tf, C
         lv.dd = A.dd[t];
         s_lv[t] = lv;
     }
+    if (t < (unsigned)NV && t >= (unsigned)nvis) {
+        s_par->w0[t] = s_par->iw[t] = 0.0f;
+        s_par->r[t] = s_par->g[t] = s_par->b[t] = 0.0f;
+        s_par->ehi[t] = s_par->cbase[t] = 0;
+        s_ch[t].c = 0;
+    }
     if (t >= 64 && t < 64u + (unsigned)A.depth + 1u) {
         const unsigned dl = t - 64;
         NodeLds nd;
@@ -1191,28 +1439,65 @@ __device__ __forceinline__ void stage_frame(const RenderArgs &A, float4 *s_tf, C
         nd.noff = A.noff[dl];
         s_nd[dl] = nd;
     }
+    for (int j = wave; j < nvis; j += waves) {
+        const float4 e0 = tf[j * 256];
+        uint64_t zero[4], same = ~0ull;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 e = tf[j * 256 + 64 * q + lane];
+            zero[q] = __ballot(e.w == 0.0f);
+            // (x - x is zero for finite values only)
+            same &= __ballot(e.x == e0.x && e.y == e0.y && e.z == e0.z && (e.x - e.x) + (e.y - e.y) + (e.z - e.z) == 0.0f);
+        }
+        if (lane == 0) {
+            ChanLds ch;
+            ch.c = A.vis[j];
+            ch.lo = A.lo[j];
+            ch.hi = A.hi[j];
+            s_par->w0[j] = A.w0[j];
+            s_par->iw[j] = A.iw[j];
+            s_par->r[j] = e0.x;
+            s_par->g[j] = e0.y;
+            s_par->b[j] = e0.z;
+            s_par->cbase[j] = (uint32_t)A.vis[j] * A.per_channel;
+            ch.onecol = same == ~0ull;
+            ch.nruns = build_runs(zero, A.W0[j], A.W1[j], s_runs + j * kMaxRuns);
+            const uint32_t r0 = s_runs[j * kMaxRuns];
+            ch.ehi = (ch.nruns == 1 && (r0 & 0xFFFFu) == 0) ? (r0 >> 16) : 0xFFFFFFFFu;
+            s_par->ehi[j] = (r0 & 0xFFFF0000u) | 0xFFFFu;
+            ch.single = 0;
+            s_ch[j] = ch;
+        }
+    }
     __syncthreads();
-    if (t < (unsigned)nvis) {
-        ChanLds ch;
-        ch.c = A.vis[t];
-        ch.lo = A.lo[t];
-        ch.hi = A.hi[t];
-        ch.w0 = A.w0[t];
-        ch.iw = A.iw[t];
-        ch.nruns = build_runs(s_tf + t * kTfStride, A.W0[t], A.W1[t], s_runs + t * kMaxRuns);
-        const uint32_t r0 = s_runs[t * kMaxRuns];
-        ch.ehi = (ch.nruns == 1 && (r0 & 0xFFFFu) == 0) ? (r0 >> 16) : 0xFFFFFFFFu;
-        ch.single = 0;
-        s_ch[t] = ch;
+    uint32_t all = 1, one = 1;
+    for (int j = 0; j < nvis; ++j) {
+        all &= s_ch[j].ehi != 0xFFFFFFFFu ? 1u : 0u;
+        one &= s_ch[j].onecol;
+    }
+    if (t < 2) {
+        if (one) ((float2 *)s_tf)[NV * kTfStride + t] = make_float2(0.0f, 0.0f);
+        else s_tf[NV * kTfStride + t] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    }
+    if (one) {
+        float2 *tfa = (float2 *)s_tf;
+        for (int i = (int)t; i < nvis * kTfStride; i += (int)blockDim.x) {
+            const int c = i / kTfStride, e = min(i - c * kTfStride, 255);
+            const float a = tf[c * 256 + e].w;
+            tfa[i] = make_float2(a, tf[c * 256 + min(e + 1, 255)].w - a);
+        }
+    } else {
+        for (int i = (int)t; i < nvis * kTfStride; i += (int)blockDim.x) {
+            const int c = i / kTfStride, e = min(i - c * kTfStride, 255);
+            s_tf[i] = tf[c * 256 + e];
+        }
     }
     __syncthreads();
     if (t < (unsigned)nvis) {
-        uint32_t all = 1;
-        for (int j = 0; j < nvis; ++j) all &= s_ch[j].ehi != 0xFFFFFFFFu ? 1u : 0u;
         s_ch[t].single = all;
+        s_ch[t].onecol = one;
     }
     __syncthreads();
-
 }
 
 }  // namespace ro

@@ -43,6 +43,8 @@ __host__ __device__ inline uint32_t serve_segments(int W, int H) {
 }
 
 
+constexpr int kServeP = 4;  // lanes per ray, as in the frame kernel
+
 // Renders work item `seg` (kSegBlocks consecutive 8 x 8-pixel blocks, the
 // blocks of a 32 x 32 tile consecutive, tiles in raster order) of the
 // request staged in sA.  The workgroup's waves take the item's blocks from
@@ -50,23 +52,21 @@ __host__ __device__ inline uint32_t serve_segments(int W, int H) {
 // finish early take more blocks.
 template <int NV, int BPV, int EC>
 __device__ __forceinline__ void serve_item(const RenderArgs &sA, uint32_t seg, uint32_t *s_next, const float4 *s_tf,
-                                           const ChanLds *s_ch, const uint32_t *s_runs, const LevLds *s_lv,
-                                           const NodeLds *s_nd) {
+                                           const ChanLds *s_ch, const ChanPar<NV> *s_par, const uint32_t *s_runs,
+                                           const LevLds *s_lv, const NodeLds *s_nd) {
     const uint32_t tiles_x = ((uint32_t)sA.W + 31) / 32, tiles_y = ((uint32_t)sA.H + 31) / 32;
     const uint32_t first = seg * kSegBlocks, n_blk = tiles_x * tiles_y * 16;
-    BlockQueue q;
+    UnitQueue<kServeP> q;
     q.counter = s_next;
-    q.n_blocks = min(kSegBlocks, n_blk - first);
-    q.offset = first;
+    q.n_units = min(kSegBlocks, n_blk - first) * kServeP;
+    q.offset = first * kServeP;
     q.tiles_x = tiles_x;
     q.n_queues = 1;
     q.chunk = 1;
     q.W = sA.W;
     q.H = sA.H;
-    q.min_idle = 64;
     uint32_t st[7] = {0, 0, 0, 0, 0, 0, 0};
-    const LdsSlots sl{(uint32_t *)(s_tf + kTfStride * NV) + threadIdx.x, (uint32_t)kRenderLanes};
-    render_rays<NV, BPV, false, EC, true, 0>(sA, q, s_tf, s_ch, s_runs, s_lv, s_nd, st, sl);
+    render_rays<NV, BPV, false, EC, 0, kServeP>(sA, q, s_tf, s_ch, s_par, s_runs, s_lv, s_nd, st);
     if (sA.stats) {
 #pragma unroll
         for (int j = 0; j < 7; ++j) {
@@ -87,6 +87,7 @@ __global__ void __launch_bounds__(kRenderLanes) __attribute__((amdgpu_waves_per_
     extern __shared__ float4 s_tf[];  // [NV][kTfStride] tables, then [NV][kRenderLanes] slot words
     __shared__ RenderArgs sA;
     __shared__ ChanLds s_ch[NV];
+    __shared__ ChanPar<NV> s_par;
     __shared__ uint32_t s_runs[NV * kMaxRuns];
     __shared__ LevLds s_lv[kMaxL];
     __shared__ NodeLds s_nd[kMaxD + 1];
@@ -108,10 +109,10 @@ __global__ void __launch_bounds__(kRenderLanes) __attribute__((amdgpu_waves_per_
             uint32_t *dst = (uint32_t *)&sA;
             for (unsigned i = threadIdx.x; i < sizeof(RenderArgs) / 4; i += blockDim.x) dst[i] = src[i];
             __syncthreads();
-            stage_frame<NV>(sA, s_tf, s_ch, s_runs, s_lv, s_nd);
+            stage_frame<NV>(sA, s_tf, s_ch, &s_par, s_runs, s_lv, s_nd);
             cur = req;
         }
-        serve_item<NV, BPV, EC>(sA, sw & 0x3FFFFFFu, &s_next, s_tf, s_ch, s_runs, s_lv, s_nd);
+        serve_item<NV, BPV, EC>(sA, sw & 0x3FFFFFFu, &s_next, s_tf, s_ch, &s_par, s_runs, s_lv, s_nd);
         __threadfence();  // this item's pixels are visible device-wide before it is counted
         __syncthreads();  // sA, the LDS tables, s_seg and s_next are reused by the next segment
         if (threadIdx.x == 0) {
@@ -161,6 +162,7 @@ __global__ void __launch_bounds__(kRenderLanes) __attribute__((amdgpu_waves_per_
     extern __shared__ float4 s_tf[];
     __shared__ RenderArgs sA;
     __shared__ ChanLds s_ch[NV];
+    __shared__ ChanPar<NV> s_par;
     __shared__ uint32_t s_runs[NV * kMaxRuns];
     __shared__ LevLds s_lv[kMaxL];
     __shared__ NodeLds s_nd[kMaxD + 1];
@@ -207,10 +209,10 @@ __global__ void __launch_bounds__(kRenderLanes) __attribute__((amdgpu_waves_per_
             uint32_t *dst = (uint32_t *)&sA;
             for (unsigned i = threadIdx.x; i < sizeof(RenderArgs) / 4; i += blockDim.x) dst[i] = sys_load(src + i);
             __syncthreads();
-            stage_frame<NV>(sA, s_tf, s_ch, s_runs, s_lv, s_nd);
+            stage_frame<NV>(sA, s_tf, s_ch, &s_par, s_runs, s_lv, s_nd);
             cur = it.x;
         }
-        serve_item<NV, BPV, EC>(sA, it.y & 0x3FFFFFFu, &s_next, s_tf, s_ch, s_runs, s_lv, s_nd);
+        serve_item<NV, BPV, EC>(sA, it.y & 0x3FFFFFFu, &s_next, s_tf, s_ch, &s_par, s_runs, s_lv, s_nd);
         __threadfence();
         __syncthreads();  // sA, the LDS tables, s_item and s_next are reused by the next item
         if (threadIdx.x == 0) {
@@ -324,7 +326,7 @@ static inline uint32_t *serve_done(const ro_server *s, int h) {
 template <int NV, int BPV, int EC>
 static hipError_t serve_attr1() {
     return hipFuncSetAttribute((const void *)k_serve<NV, BPV, EC>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)render_lds_bytes(NV));
+                               (int)render_lds_bytes(NV, kServeP));
 }
 
 template <int NV, int BPV>
@@ -341,7 +343,7 @@ static hipError_t ring_attr() {
     for (const void *f : {(const void *)k_serve_ring<16, BPV, 0>, (const void *)k_serve_ring<16, BPV, 18>,
                           (const void *)k_serve_ring<16, BPV, 34>})
         if (e == hipSuccess)
-            e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)render_lds_bytes(16));
+            e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)render_lds_bytes(16, kServeP));
     return e;
 }
 
@@ -353,7 +355,7 @@ static void ring_launch_e(const ro_server *s, uint32_t launch, hipStream_t st) {
     unsigned long long *records = (unsigned long long *)(d + ring_off_records());
     const RenderArgs *descs = (const RenderArgs *)(d + ring_off_descs());
     const uint2 *ring = (const uint2 *)(d + ring_off_ring(s->max_req));
-    hipLaunchKernelGGL((k_serve_ring<16, BPV, EC>), dim3(s->ncu), dim3(kRenderLanes), render_lds_bytes(16), st, ctl,
+    hipLaunchKernelGGL((k_serve_ring<16, BPV, EC>), dim3(s->ncu), dim3(kRenderLanes), render_lds_bytes(16, kServeP), st, ctl,
                        descs, ring, s->rcap - 1, ring_head(s), ring_closed(s), records, launch, ring_done(s),
                        flags);
 }
@@ -375,7 +377,7 @@ static void serve_launch_e(const ro_server *s, int h, hipStream_t st) {
     const uint32_t *dt = (const uint32_t *)(d + sizeof(ServeHeader) + (size_t)s->max_req * sizeof(RenderArgs));
     uint32_t *q = serve_queue(s, h);
     hipLaunchKernelGGL(k_serve_reset, dim3(1), dim3(64), 0, st, q, serve_done(s, h), s->max_req);
-    hipLaunchKernelGGL((k_serve<NV, BPV, EC>), dim3(s->ncu), dim3(kRenderLanes), render_lds_bytes(NV), st, dh, dd, dt,
+    hipLaunchKernelGGL((k_serve<NV, BPV, EC>), dim3(s->ncu), dim3(kRenderLanes), render_lds_bytes(NV, kServeP), st, dh, dd, dt,
                        q);
 }
 
