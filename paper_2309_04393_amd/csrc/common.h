@@ -95,17 +95,19 @@ struct ro_volume {
     ro::VolGeo g;
 };
 
+namespace ro {
+// LRU select: bins of its histograms, words of its state before the victims,
+// and the candidates that it may rank beyond those asked for.
+constexpr uint32_t kSelHistWords = 3 * 2048, kSelStateWords = 32, kSelSlack = 4096;
+}  // namespace ro
+
 // Scratch layout of a cache (byte offsets into bufs.scratch).
 struct CacheScratch {
     size_t keys;       // n_slots uint64 LRU keys
-    size_t hist;       // 256 uint32 radix histogram
-    size_t sel;        // select state (see stream.hip)
-    size_t cand;       // max_batch uint64 candidate keys
-    size_t victims;    // max_batch uint32
-    size_t evicted;    // max_batch uint32
-    size_t uploads;    // max_batch uint32 dense indices
-    size_t srcidx;     // max_batch uint32 staged index
-    size_t touch;      // max_batch uint32 slots to touch
+    size_t hist;       // kSelHistWords uint32 radix histograms
+    size_t sel;        // select state (see stream.hip), then max_batch uint32 victims
+    size_t cand;       // max_batch + kSelSlack uint64 candidate keys
+    size_t batch;      // uploads' dense indices, their staged indices, slots to touch: 2 * max_batch uint32
     size_t compact;    // request compaction work space (compact_scratch_bytes of every brick)
     size_t outpairs;   // usage readback output and LRU candidate slots
     size_t total;      // bytes
@@ -137,9 +139,11 @@ ro_status launch_fill_u32(uint32_t *p, uint64_t n, uint32_t v, hipStream_t s);
 ro_status launch_fill_u16(uint16_t *p, uint64_t n, uint16_t v, hipStream_t s);
 ro_status launch_fill_u8(uint8_t *p, uint64_t n, uint8_t v, hipStream_t s);
 
+// Uploads n_new bricks (batch: dense indices, staged indices) and stamps
+// n_touch slots (batch, after the uploads).  result (kSelStateWords + n_new
+// words) receives the number of slots found and then their indices.
 ro_status stream_bricks_device(ro_cache *c, uint32_t frame, uint32_t n_new, uint32_t n_touch,
-                               const void *staged, hipStream_t s, uint32_t *k_eff_host,
-                               uint32_t *victims_host, uint32_t *evicted_host);
+                               const uint32_t *batch, const void *staged, hipStream_t s, uint32_t *result);
 ro_status read_requests_device(ro_cache *c, uint32_t cap, uint32_t *ids, uint32_t *counts,
                                uint32_t *n_unique, uint64_t *total, hipStream_t s);
 size_t compact_scratch_bytes(uint64_t n, uint32_t lim);

@@ -3,6 +3,7 @@
 // the CPU under a global limit; Sec. 5.3: slot selection with LRU eviction).
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "common.h"
@@ -307,158 +308,314 @@ ro_status read_usage_device(ro_cache *c, uint32_t frame, uint32_t cap, uint32_t 
 }
 
 // ------------------------------------------------------- LRU slot choice
+//
+// Radix select of the k smallest LRU keys, then their order by rank.  The
+// time is launches and dependent round trips, not bytes: 218551 slots are
+// 4 MB.  A slot's key has 64 bits but few of them differ within one cache
+// (few frames are alive, and their sequence numbers lie close), so the keys
+// pass reduces the ranges of the high and of the low words, and the digits
+// are taken from (hi - hi_min) : (lo - lo_min), 11 bits each: three passes
+// take 33 bits, where eight passes of a histogram and a pick took 64.  No
+// block waits for another and none ends a pass for the others (a fence of
+// device scope writes the XCD's L2 back: 38 us a pass): every block of the
+// next launch picks the digit itself from the 2048 counts.  What the three
+// passes leave undecided goes to the rank, if it is at most kSelSlack
+// candidates more than asked for; if it is more, the collecting blocks count
+// the further digits each for itself.
 
-// Select state words.
-enum { SEL_ELIG = 0, SEL_KEFF = 1, SEL_KREM = 2, SEL_NCAND = 3, SEL_PREFIX = 4 /* u64 at 4..5 */ };
+constexpr int kSelDigit = 11, kSelBins = 1 << kSelDigit, kSelPasses = 3;
+constexpr uint32_t kSelThreads = 1024, kSelBlocks = 128;
+static_assert(kSelHistWords == kSelPasses * kSelBins, "histogram area");
+static_assert(kSelBins == 2 * kSelThreads, "two bins per thread");
 
-__global__ void k_touch(uint32_t *__restrict__ stamp, const uint32_t *__restrict__ slots, uint32_t n,
-                        uint32_t f) {
-    uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+// Choice after a pass: `krem` smallest of the keys whose short key equals
+// `prefix` above bit `shift`, and all below; `extra` keys of the prefix are
+// beyond those asked for.
+struct SelChoice {
+    unsigned long long prefix;
+    uint32_t shift, krem, extra;
+};
+
+// Select state (zero at the start but the minima, which are ~0).
+struct SelState {
+    uint32_t elig;          // eligible slots
+    uint32_t keff;          // min(eligible, asked for)
+    uint32_t ncand;         // candidates collected
+    uint32_t hmin, hmax;    // range of the high words
+    uint32_t lmin, lmax;    // range of the low words
+    uint32_t pad;
+    SelChoice after[kSelPasses];  // [p]: the choice after pass p
+};
+static_assert(sizeof(SelState) <= 4 * kSelStateWords, "select state area");
+
+// Key with the bits that no key of the cache uses taken out (the same order).
+struct ShortKey {
+    uint32_t hmin, lmin, lobits, bits;
+    __device__ ShortKey(const SelState *st) {
+        const uint32_t hr = st->hmax - st->hmin, lr = st->lmax - st->lmin;
+        hmin = st->hmin;
+        lmin = st->lmin;
+        lobits = lr ? 32 - (uint32_t)__clz(lr) : 0;
+        bits = lobits + (hr ? 32 - (uint32_t)__clz(hr) : 0);
+    }
+    __device__ unsigned long long operator()(unsigned long long k) const {
+        return ((unsigned long long)((uint32_t)(k >> 32) - hmin) << lobits) | ((uint32_t)k - lmin);
+    }
+};
+
+__device__ inline unsigned long long above(unsigned long long k, uint32_t shift) { return shift >= 64 ? 0 : k >> shift; }
+
+// The choice before the first pass.
+__device__ inline SelChoice sel_first(const SelState *st, uint32_t n_new, uint32_t bits) {
+    const uint32_t k = min(st->elig, n_new);
+    return {0, bits, k, st->elig - k};
+}
+
+// Next digit of a choice: its low bit and its mask.
+__device__ inline uint32_t digit_shift(uint32_t shift) { return shift > kSelDigit ? shift - kSelDigit : 0; }
+__device__ inline uint32_t digit_mask(uint32_t shift) { return (1u << (shift - digit_shift(shift))) - 1; }
+
+// The choice after the digit of c, whose bins hold hist[] keys: the bin with
+// the krem-th key.  By a whole block of 1024; every thread gets it.
+__device__ inline SelChoice sel_pick(const SelChoice &c, const uint32_t *hist, SelChoice *lds, uint32_t *wsum) {
+    const uint32_t b = 2 * threadIdx.x, v0 = hist[b], v1 = hist[b + 1];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    uint32_t x = v0 + v1;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+    }
+    if (lane == 63) wsum[wid] = x;
+    if (threadIdx.x == 0) *lds = c;  // nothing to choose: krem is 0
+    __syncthreads();
+    uint32_t before = x - v0 - v1;
+    for (int w = 0; w < wid; ++w) before += wsum[w];
+    const uint32_t shift = digit_shift(c.shift);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const uint32_t v = j ? v1 : v0;
+        if (before < c.krem && c.krem <= before + v)  // one bin of the block
+            *lds = {c.prefix | ((unsigned long long)(b + j) << shift), shift, c.krem - before,
+                    before + v - c.krem};
+        before += v;
+    }
+    __syncthreads();
+    const SelChoice r = *lds;
+    __syncthreads();
+    return r;
+}
+
+// Counts the next digit of c over the block's share of the keys (from i0 on
+// at the given stride) in h.  Between two barriers of the caller.
+__device__ inline void sel_count(const SelChoice &c, const ShortKey &sk, const unsigned long long *__restrict__ keys,
+                                 uint32_t S, uint32_t i0, uint32_t stride, uint32_t *h) {
+    const uint32_t shift = digit_shift(c.shift), mask = digit_mask(c.shift);
+    for (uint32_t i = i0 + threadIdx.x; i < S; i += stride) {
+        const unsigned long long raw = keys[i];
+        if (raw == ~0ull) continue;
+        const unsigned long long k = sk(raw);
+        if (above(k, c.shift) == above(c.prefix, c.shift)) atomicAdd(&h[(uint32_t)(k >> shift) & mask], 1u);
+    }
+}
+
+// Stamps the resident bricks of the batch, and clears the histograms and the
+// select state (a kernel, so that no memset stands between the launches).
+__global__ void __launch_bounds__(1024) k_touch_clear(uint32_t *__restrict__ stamp, const uint32_t *__restrict__ slots,
+                                                      uint32_t n, uint32_t f, uint32_t *__restrict__ hist,
+                                                      SelState *__restrict__ st) {
+    const uint32_t i = blockIdx.x * 1024 + threadIdx.x;
     if (i < n) stamp[slots[i]] = f;
+    if (i < kSelHistWords) hist[i] = 0;
+    if (i < kSelStateWords) ((uint32_t *)st)[i] = 0;
+    __syncthreads();
+    if (i == 0) st->hmin = st->lmin = ~0u;
 }
 
 // LRU key per slot: free slots first in ascending index (key = slot), then
 // occupied slots by (stamp, seq) (key = (stamp + 1) << 32 | seq); slots used
 // in the current frame are not eligible (key = ~0).  Keys are unique.
-__global__ void __launch_bounds__(256) k_keys(const uint32_t *__restrict__ slot_brick,
-                                              const uint32_t *__restrict__ stamp,
-                                              const uint32_t *__restrict__ seq, uint32_t S, uint32_t f,
-                                              unsigned long long *__restrict__ keys,
-                                              uint32_t *__restrict__ sel) {
-    __shared__ uint32_t lds[4];
-    uint32_t i = blockIdx.x * 256 + threadIdx.x;
-    uint32_t elig = 0;
-    if (i < S) {
-        unsigned long long k;
-        if (slot_brick[i] == kInvalid) {
-            k = i;
-            elig = 1;
-        } else if (stamp[i] == f) {
-            k = ~0ull;
-        } else {
-            k = ((unsigned long long)(stamp[i] + 1u) << 32) | seq[i];
-            elig = 1;
-        }
+__global__ void __launch_bounds__(1024) k_keys(const uint32_t *__restrict__ slot_brick,
+                                               const uint32_t *__restrict__ stamp,
+                                               const uint32_t *__restrict__ seq, uint32_t S, uint32_t f,
+                                               unsigned long long *__restrict__ keys, SelState *__restrict__ state) {
+    __shared__ uint32_t red[5];
+    if (threadIdx.x < 5) red[threadIdx.x] = threadIdx.x == 1 || threadIdx.x == 3 ? ~0u : 0u;
+    __syncthreads();
+    uint32_t elig = 0, hmin = ~0u, hmax = 0, lmin = ~0u, lmax = 0;
+    for (uint32_t i = blockIdx.x * kSelThreads + threadIdx.x; i < S; i += gridDim.x * kSelThreads) {
+        const uint32_t sb = slot_brick[i], st = stamp[i], sq = seq[i];
+        unsigned long long k = ((unsigned long long)(st + 1u) << 32) | sq;
+        if (sb == kInvalid) k = i;
+        else if (st == f) k = ~0ull;
         keys[i] = k;
+        if (k != ~0ull) {
+            ++elig;
+            hmin = min(hmin, (uint32_t)(k >> 32));
+            hmax = max(hmax, (uint32_t)(k >> 32));
+            lmin = min(lmin, (uint32_t)k);
+            lmax = max(lmax, (uint32_t)k);
+        }
     }
-    uint32_t tot;
-    block_excl_scan_256(elig, lds, &tot);
-    if (threadIdx.x == 0 && tot) atomicAdd(&sel[SEL_ELIG], tot);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        elig += __shfl_xor(elig, o, 64);
+        hmin = min(hmin, (uint32_t)__shfl_xor(hmin, o, 64));
+        hmax = max(hmax, (uint32_t)__shfl_xor(hmax, o, 64));
+        lmin = min(lmin, (uint32_t)__shfl_xor(lmin, o, 64));
+        lmax = max(lmax, (uint32_t)__shfl_xor(lmax, o, 64));
+    }
+    if ((threadIdx.x & 63) == 0 && elig) {
+        atomicAdd(&red[0], elig);
+        atomicMin(&red[1], hmin);
+        atomicMax(&red[2], hmax);
+        atomicMin(&red[3], lmin);
+        atomicMax(&red[4], lmax);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && red[0]) {
+        atomicAdd(&state->elig, red[0]);
+        atomicMin(&state->hmin, red[1]);
+        atomicMax(&state->hmax, red[2]);
+        atomicMin(&state->lmin, red[3]);
+        atomicMax(&state->lmax, red[4]);
+    }
 }
 
-__global__ void k_sel_init(uint32_t *sel, uint32_t n_new) {
-    uint32_t k = sel[SEL_ELIG] < n_new ? sel[SEL_ELIG] : n_new;
-    sel[SEL_KEFF] = k;
-    sel[SEL_KREM] = k;
-    sel[SEL_NCAND] = 0;
-    sel[SEL_PREFIX] = 0;
-    sel[SEL_PREFIX + 1] = 0;
+// Choice before pass `pass`, the same in every thread (block 0 keeps it for
+// the next launch).  done: no further digit is needed.
+__device__ inline SelChoice sel_before(int pass, SelState *st, const ShortKey &sk, const uint32_t *hist,
+                                       uint32_t n_new, SelChoice *lds, uint32_t *wsum) {
+    if (pass == 0) return sel_first(st, n_new, sk.bits);
+    SelChoice c = pass == 1 ? sel_first(st, n_new, sk.bits) : st->after[pass - 2];
+    if (c.extra > 0 && c.krem > 0) c = sel_pick(c, hist + (pass - 1) * kSelBins, lds, wsum);
+    if (blockIdx.x == 0 && threadIdx.x == 0) st->after[pass - 1] = c;
+    return c;
 }
 
-// Radix-select pass: histogram of the digit at `shift` over keys whose
-// higher digits equal the prefix chosen so far.
-__global__ void __launch_bounds__(256) k_hist(const unsigned long long *__restrict__ keys, uint32_t S,
-                                              const uint32_t *__restrict__ sel, int shift,
-                                              uint32_t *__restrict__ hist) {
-    __shared__ uint32_t h[256];
-    if (sel[SEL_KREM] == 0) return;
+// Pass 0, 1 or 2 of the select: histogram of the next digit over the keys of
+// the prefix chosen so far.
+__global__ void __launch_bounds__(1024) k_select(const unsigned long long *__restrict__ keys, uint32_t S,
+                                                 SelState *state, uint32_t *__restrict__ hist, uint32_t n_new,
+                                                 int pass) {
+    __shared__ uint32_t h[kSelBins], wsum[kSelThreads / 64];
+    __shared__ SelChoice lds;
+    const ShortKey sk(state);
+    const SelChoice c = sel_before(pass, state, sk, hist, n_new, &lds, wsum);
+    if (c.extra == 0 || c.krem == 0) return;  // the prefix stands
     h[threadIdx.x] = 0;
+    h[threadIdx.x + kSelThreads] = 0;
     __syncthreads();
-    unsigned long long prefix = ((unsigned long long)sel[SEL_PREFIX + 1] << 32) | sel[SEL_PREFIX];
-    int hs = shift + 8;
-    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < S; i += gridDim.x * 256) {
-        unsigned long long k = keys[i];
-        if (hs < 64 && (k >> hs) != (prefix >> hs)) continue;
-        atomicAdd(&h[(k >> shift) & 255u], 1u);
-    }
+    sel_count(c, sk, keys, S, blockIdx.x * kSelThreads, gridDim.x * kSelThreads, h);
     __syncthreads();
-    if (h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], h[threadIdx.x]);
-}
-
-__global__ void __launch_bounds__(256) k_pick(uint32_t *__restrict__ hist, uint32_t *__restrict__ sel,
-                                              int shift) {
-    __shared__ uint32_t lds[4];
-    uint32_t krem = sel[SEL_KREM];
-    uint32_t v = hist[threadIdx.x];
-    hist[threadIdx.x] = 0;
-    if (krem == 0) return;
-    uint32_t tot;
-    uint32_t before = block_excl_scan_256(v, lds, &tot);
-    if (before < krem && krem <= before + v) {
-        unsigned long long prefix = ((unsigned long long)sel[SEL_PREFIX + 1] << 32) | sel[SEL_PREFIX];
-        prefix |= (unsigned long long)threadIdx.x << shift;
-        sel[SEL_PREFIX] = (uint32_t)prefix;
-        sel[SEL_PREFIX + 1] = (uint32_t)(prefix >> 32);
-        sel[SEL_KREM] = krem - before;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const uint32_t b = threadIdx.x + j * kSelThreads;
+        if (h[b]) atomicAdd(&hist[pass * kSelBins + b], h[b]);
     }
 }
 
-// Collect the k_eff smallest keys (all keys <= the selected threshold).
-__global__ void __launch_bounds__(256) k_collect(const unsigned long long *__restrict__ keys, uint32_t S,
-                                                 uint32_t *__restrict__ sel,
-                                                 unsigned long long *__restrict__ cand,
-                                                 uint32_t *__restrict__ cand_slot, uint32_t cap) {
-    if (sel[SEL_KEFF] == 0) return;
-    unsigned long long thr = ((unsigned long long)sel[SEL_PREFIX + 1] << 32) | sel[SEL_PREFIX];
-    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < S; i += gridDim.x * 256) {
-        unsigned long long k = keys[i];
-        if (k <= thr) {
-            uint32_t at = atomicAdd(&sel[SEL_NCAND], 1u);
-            if (at < cap) {  // exactly k_eff keys qualify (keys are unique)
-                cand[at] = k;
-                cand_slot[at] = i;
-            }
+// Collect the keys up to the end of the chosen prefix: at least the k_eff
+// smallest, at most k_eff + kSelSlack.
+__global__ void __launch_bounds__(1024) k_collect(const unsigned long long *__restrict__ keys, uint32_t S,
+                                                  SelState *state, const uint32_t *__restrict__ hist, uint32_t n_new,
+                                                  unsigned long long *__restrict__ cand,
+                                                  uint32_t *__restrict__ cand_slot, uint32_t cap, int passes) {
+    __shared__ uint32_t h[kSelBins], wsum[kSelThreads / 64];
+    __shared__ SelChoice lds;
+    const uint32_t keff = min(state->elig, n_new);
+    if (blockIdx.x == 0 && threadIdx.x == 0) state->keff = keff;
+    if (keff == 0) return;
+    const ShortKey sk(state);
+    SelChoice c = sel_before(passes, state, sk, hist, n_new, &lds, wsum);
+    while (c.extra > kSelSlack) {  // every block over all keys; a digit less each time, keys are unique
+        h[threadIdx.x] = 0;
+        h[threadIdx.x + kSelThreads] = 0;
+        __syncthreads();
+        sel_count(c, sk, keys, S, 0, kSelThreads, h);
+        __syncthreads();
+        const uint32_t left = c.shift;
+        c = sel_pick(c, h, &lds, wsum);
+        if (c.shift >= left) break;  // never with unique keys
+    }
+    const unsigned long long thr = above(c.prefix, c.shift);
+    const int lane = threadIdx.x & 63;
+    for (uint32_t i0 = blockIdx.x * kSelThreads; i0 < S; i0 += gridDim.x * kSelThreads) {
+        const uint32_t i = i0 + threadIdx.x;
+        const unsigned long long raw = i < S ? keys[i] : ~0ull;
+        const bool in = raw != ~0ull && above(sk(raw), c.shift) <= thr;
+        const unsigned long long bal = __ballot(in);
+        if (bal == 0) continue;
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(&state->ncand, (uint32_t)__popcll(bal));
+        at = __shfl(at, 0, 64) + (uint32_t)__popcll(bal & ((1ull << lane) - 1));
+        if (in && at < cap) {
+            cand[at] = raw;
+            cand_slot[at] = i;
         }
     }
 }
 
-// Order the candidates: rank = number of smaller keys (keys are unique).
-__global__ void __launch_bounds__(256) k_rank(const unsigned long long *__restrict__ cand,
-                                              const uint32_t *__restrict__ cand_slot,
-                                              const uint32_t *__restrict__ sel,
-                                              uint32_t *__restrict__ victims) {
-    __shared__ unsigned long long tile[256];
-    uint32_t n = sel[SEL_KEFF];
-    uint32_t i = blockIdx.x * 256 + threadIdx.x;
-    unsigned long long mine = i < n ? cand[i] : 0;
-    uint32_t rank = 0;
-    for (uint32_t t0 = 0; t0 < n; t0 += 256) {
-        __syncthreads();
-        if (t0 + threadIdx.x < n) tile[threadIdx.x] = cand[t0 + threadIdx.x];
-        __syncthreads();
-        uint32_t lim = n - t0 < 256 ? n - t0 : 256;
-        for (uint32_t j = 0; j < lim; ++j) rank += tile[j] < mine;
+// Order of the candidates (rank = number of smaller keys; keys are unique)
+// and the page-table update of the first k_eff: evict the victim's brick,
+// insert the upload.  A wave ranks eight candidates, its lanes over all the
+// others, so that 4096 candidates are 512 waves of 64 steps (one thread per
+// candidate was 8 blocks of 2048 dependent LDS reads: 33 us for 2048).
+constexpr uint32_t kRankPerWave = 8;
+__global__ void __launch_bounds__(256) k_rank_update(const unsigned long long *__restrict__ cand,
+                                                     const uint32_t *__restrict__ cand_slot,
+                                                     const SelState *__restrict__ state, uint32_t cap,
+                                                     const uint32_t *__restrict__ uploads,
+                                                     uint32_t *__restrict__ victims, uint32_t *__restrict__ pt,
+                                                     uint32_t *__restrict__ slot_brick,
+                                                     uint32_t *__restrict__ stamp, uint32_t *__restrict__ seq,
+                                                     uint32_t f, uint32_t seq_base) {
+    const uint32_t k_eff = state->keff, n = min(state->ncand, cap);
+    const uint32_t i0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * kRankPerWave;
+    const uint32_t lane = threadIdx.x & 63;
+    if (k_eff == 0 || i0 >= n) return;
+    const unsigned long long own = i0 + (lane & 7) < n ? cand[i0 + (lane & 7)] : 0;
+    unsigned long long mine[kRankPerWave];
+    uint32_t cnt[kRankPerWave];
+#pragma unroll
+    for (uint32_t r = 0; r < kRankPerWave; ++r) {
+        mine[r] = __shfl(own, (int)r, 64);
+        cnt[r] = 0;
     }
-    if (i < n) victims[rank] = cand_slot[i];
-}
-
-// Page-table update: evict the victim's brick, insert the upload.
-__global__ void k_pt_update(const uint32_t *__restrict__ sel, const uint32_t *__restrict__ victims,
-                            const uint32_t *__restrict__ uploads, uint32_t *__restrict__ pt,
-                            uint32_t *__restrict__ slot_brick, uint32_t *__restrict__ stamp,
-                            uint32_t *__restrict__ seq, uint32_t *__restrict__ evicted, uint32_t f,
-                            uint32_t seq_base) {
-    uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= sel[SEL_KEFF]) return;
-    uint32_t slot = victims[i];
-    uint32_t old = slot_brick[slot];
+    for (uint32_t j0 = 0; j0 < n; j0 += 512) {  // eight loads in flight
+        unsigned long long o[8];
+#pragma unroll
+        for (uint32_t q = 0; q < 8; ++q) {
+            const uint32_t j = j0 + 64 * q + lane;
+            o[q] = cand[min(j, n - 1)];
+            if (j >= n) o[q] = ~0ull;
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < 8; ++q)
+#pragma unroll
+            for (uint32_t r = 0; r < kRankPerWave; ++r) cnt[r] += (uint32_t)__popcll(__ballot(o[q] < mine[r]));
+    }
+    uint32_t rank = 0;
+#pragma unroll
+    for (uint32_t r = 0; r < kRankPerWave; ++r) rank = lane == r ? cnt[r] : rank;
+    if (lane >= kRankPerWave || i0 + lane >= n || rank >= k_eff) return;
+    const uint32_t slot = cand_slot[i0 + lane], old = slot_brick[slot], b = uploads[rank];
     if (old != kInvalid) pt[old] = kInvalid;
-    evicted[i] = old;
-    uint32_t b = uploads[i];
+    victims[rank] = slot;
     pt[b] = slot;
     slot_brick[slot] = b;
     stamp[slot] = f;
-    seq[slot] = seq_base + i;
+    seq[slot] = seq_base + rank;
 }
 
 // Brick scatter: staged brick src[i] -> slot victims[i], 16-byte vectors.
-__global__ void __launch_bounds__(256) k_scatter(const uint32_t *__restrict__ sel,
+__global__ void __launch_bounds__(256) k_scatter(const SelState *__restrict__ state,
                                                  const uint32_t *__restrict__ victims,
                                                  const uint32_t *__restrict__ src,
                                                  const uint4 *__restrict__ staged, uint4 *__restrict__ slots,
                                                  uint32_t vec_per_slot) {
     uint32_t i = blockIdx.y;
-    if (i >= sel[SEL_KEFF]) return;
+    if (i >= state->keff) return;
     const uint4 *from = staged + (size_t)src[i] * vec_per_slot;
     uint4 *to = slots + (size_t)victims[i] * vec_per_slot;
     for (uint32_t v = blockIdx.x * 256 + threadIdx.x; v < vec_per_slot; v += gridDim.x * 256)
@@ -466,66 +623,52 @@ __global__ void __launch_bounds__(256) k_scatter(const uint32_t *__restrict__ se
 }
 
 ro_status stream_bricks_device(ro_cache *c, uint32_t frame, uint32_t n_new, uint32_t n_touch,
-                               const void *staged, hipStream_t s, uint32_t *k_eff_host,
-                               uint32_t *victims_host, uint32_t *evicted_host) {
+                               const uint32_t *batch, const void *staged, hipStream_t s, uint32_t *result) {
     const VolGeo &g = c->vol->g;
     uint8_t *sc = (uint8_t *)c->b.scratch;
-    uint32_t S = c->desc.n_slots;
+    const uint32_t S = c->desc.n_slots;
     unsigned long long *keys = (unsigned long long *)(sc + c->sc.keys);
     uint32_t *hist = (uint32_t *)(sc + c->sc.hist);
-    uint32_t *sel = (uint32_t *)(sc + c->sc.sel);
+    SelState *sel = (SelState *)(sc + c->sc.sel);
     unsigned long long *cand = (unsigned long long *)(sc + c->sc.cand);
-    uint32_t *victims = (uint32_t *)(sc + c->sc.victims);
-    uint32_t *evicted = (uint32_t *)(sc + c->sc.evicted);
-    uint32_t *uploads = (uint32_t *)(sc + c->sc.uploads);
-    uint32_t *srcidx = (uint32_t *)(sc + c->sc.srcidx);
-    uint32_t *touch = (uint32_t *)(sc + c->sc.touch);
-    // candidate slots share the evicted array's space until the update
-    uint32_t *cand_slot = (uint32_t *)(sc + c->sc.outpairs);
-    if (n_touch) {
-        hipLaunchKernelGGL(k_touch, dim3((n_touch + 255) / 256), dim3(256), 0, s, c->b.stamps, touch, n_touch,
-                           frame);
-        RO_HIP(hipGetLastError());
-    }
-    *k_eff_host = 0;
-    if (n_new == 0) return RO_OK;
-    RO_HIP(hipMemsetAsync(sel, 0, 64, s));
-    RO_HIP(hipMemsetAsync(hist, 0, 1024, s));
-    uint32_t nb = (S + 255) / 256;
-    hipLaunchKernelGGL(k_keys, dim3(nb), dim3(256), 0, s, c->b.slot_brick, c->b.stamps, c->b.seqs, S, frame,
+    uint32_t *victims = (uint32_t *)sel + kSelStateWords;  // read back with the state in one copy
+    const uint32_t *uploads = (uint32_t *)(sc + c->sc.batch), *srcidx = uploads + n_new, *touch = srcidx + n_new;
+    uint32_t *cand_slot = (uint32_t *)(sc + c->sc.outpairs);  // at least n_slots words
+    if (n_new + n_touch == 0) return RO_OK;
+    RO_HIP(hipMemcpyAsync(sc + c->sc.batch, batch, 4 * (2 * (size_t)n_new + n_touch), hipMemcpyHostToDevice, s));
+    hipLaunchKernelGGL(k_touch_clear, dim3((std::max(n_touch, kSelHistWords) + 1023) / 1024), dim3(1024), 0, s,
+                       c->b.stamps, touch, n_touch, frame, hist, sel);
+    RO_HIP(hipGetLastError());
+    if (n_new == 0) return RO_OK;  // the copy from pageable memory is complete when its call returns
+    const uint32_t cap = std::min(n_new + kSelSlack, S);
+    const uint32_t nb = std::min((S + kSelThreads - 1) / kSelThreads, kSelBlocks);
+    // no pass where all slots fit the candidates: the rank takes them apart
+    const int passes = S > cap ? kSelPasses : 0;
+    hipLaunchKernelGGL(k_keys, dim3(nb), dim3(kSelThreads), 0, s, c->b.slot_brick, c->b.stamps, c->b.seqs, S, frame,
                        keys, sel);
     RO_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_sel_init, dim3(1), dim3(1), 0, s, sel, n_new);
-    RO_HIP(hipGetLastError());
-    uint32_t hb = nb < 1024 ? nb : 1024;
-    for (int shift = 56; shift >= 0; shift -= 8) {
-        hipLaunchKernelGGL(k_hist, dim3(hb), dim3(256), 0, s, keys, S, sel, shift, hist);
-        RO_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_pick, dim3(1), dim3(256), 0, s, hist, sel, shift);
+    for (int p = 0; p < passes; ++p) {
+        hipLaunchKernelGGL(k_select, dim3(nb), dim3(kSelThreads), 0, s, keys, S, sel, hist, n_new, p);
         RO_HIP(hipGetLastError());
     }
-    hipLaunchKernelGGL(k_collect, dim3(hb), dim3(256), 0, s, keys, S, sel, cand, cand_slot, n_new);
+    hipLaunchKernelGGL(k_collect, dim3(nb), dim3(kSelThreads), 0, s, keys, S, sel, hist, n_new, cand, cand_slot, cap,
+                       passes);
     RO_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_rank, dim3((n_new + 255) / 256), dim3(256), 0, s, cand, cand_slot, sel, victims);
-    RO_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_pt_update, dim3((n_new + 255) / 256), dim3(256), 0, s, sel, victims, uploads,
-                       c->b.page_table, c->b.slot_brick, c->b.stamps, c->b.seqs, evicted, frame,
-                       c->seq_next);
+    hipLaunchKernelGGL(k_rank_update, dim3((cap + 4 * kRankPerWave - 1) / (4 * kRankPerWave)), dim3(256), 0, s, cand,
+                       cand_slot, sel, cap, uploads, victims, c->b.page_table, c->b.slot_brick, c->b.stamps,
+                       c->b.seqs, frame, c->seq_next);
     RO_HIP(hipGetLastError());
     uint32_t vps = g.slot_stride / 16;
     uint32_t gx = (vps + 255) / 256;
     hipLaunchKernelGGL(k_scatter, dim3(gx, n_new), dim3(256), 0, s, sel, victims, srcidx,
                        (const uint4 *)staged, (uint4 *)c->b.slots, vps);
     RO_HIP(hipGetLastError());
-    uint32_t selh[8];
-    RO_HIP(hipMemcpyAsync(selh, sel, 32, hipMemcpyDeviceToHost, s));
-    RO_HIP(hipMemcpyAsync(victims_host, victims, 4 * (size_t)n_new, hipMemcpyDeviceToHost, s));
-    RO_HIP(hipMemcpyAsync(evicted_host, evicted, 4 * (size_t)n_new, hipMemcpyDeviceToHost, s));
+    RO_HIP(hipMemcpyAsync(result, sel, 4 * (kSelStateWords + (size_t)n_new), hipMemcpyDeviceToHost, s));
     RO_HIP(hipStreamSynchronize(s));
-    *k_eff_host = selh[SEL_KEFF];
+    result[0] = ((const SelState *)result)->keff;
+    memmove(result + 1, result + kSelStateWords, 4 * (size_t)result[0]);
     return RO_OK;
 }
-
 
 // Every resident brick whose dense index lies in [lo, hi) leaves the cache:
 // its page-table entry and its slot's brick are cleared, so the slot is free.
