@@ -3,20 +3,27 @@
 // This network is an addition to the paper's method; it only changes which
 // bricks are streamed, never how a frame is rendered from a cache state.
 //
-// All three layers run on MFMA (v_mfma_f32_16x16x16_f16: FP16 operands,
-// FP32 accumulation).  A wave owns 16 rows at a time.  Layer shapes with
-// padding: X [rows][32] (24 features), W1 [32][64], W2 [64][64],
-// W3 [64][16] (9 logits), Z [rows][16].  Operand lane layout of the 16x16x16
-// instruction (wave64, lane l, i = 0..3):
-//   A (16 x 16, row-major M x K):  A[l % 16][4 (l / 16) + i]
-//   B (16 x 16, K x N):            B[4 (l / 16) + i][l % 16]
-//   C/D (16 x 16, M x N):          D[4 (l / 16) + i][l % 16]
-// Activations move from the D layout to the A layout through a per-wave LDS
-// tile.  Training recomputes the forward pass per tile, backpropagates with
-// the loss scaled by the number of unmasked entries (so FP16 operands stay
-// in range), accumulates weight gradients in FP32 per wave, reduces the
-// per-wave partials in a fixed order (deterministic) and applies Adam to FP32
-// master weights, refreshing the FP16 copies.
+// All products run on MFMA (v_mfma_f32_16x16x16_f16: FP16 operands, FP32
+// accumulation).  A wave owns 16 rows at a time.  Layer shapes with padding:
+// X [rows][32] (24 features), W1 [32][64], W2 [64][64], W3 [64][16] (9
+// logits), Z [rows][16].  Operand lane layout of the 16x16x16 instruction
+// (wave64, lane l = 16 q + r, i = 0..3):
+//   A (16 x 16, row-major M x K):  A[r][4 q + i]
+//   B (16 x 16, K x N):            B[4 q + i][r]
+//   C/D (16 x 16, M x N):          D[4 q + i][r]
+// So a 4-vector per lane, a fragment, that is A of a matrix is B of its
+// transpose, a product's D is B of the matrix and A of its transpose, and
+// D^T is the product with the operands exchanged.  Every operand is therefore
+// made in registers, in the training kernel by taking each layer both ways:
+// nothing goes through LDS, where the 2-byte fragment reads and their waits
+// were what the kernels spent their time on.  Weights are held as fragments
+// over all the rows of a wave; the FP16 copies hold W2 and W3 in both orders,
+// so that a fragment is one 8-byte load.
+// Training recomputes the forward pass per tile, backpropagates with the loss
+// scaled by the number of unmasked entries (so FP16 operands stay in range),
+// accumulates weight gradients in FP32 per wave, sums a block's four waves in
+// LDS and the blocks' partials in a fixed order (deterministic) and applies
+// Adam to FP32 master weights, refreshing the FP16 copies.
 #include <math.h>
 #include <string.h>
 
@@ -30,387 +37,403 @@ typedef float f4_t __attribute__((ext_vector_type(4)));
 // FP32 parameter block layout (floats), padded shapes.
 constexpr int kW1 = 0, kB1 = kW1 + 32 * 64, kW2 = kB1 + 64, kB2 = kW2 + 64 * 64, kW3 = kB2 + 64,
               kB3 = kW3 + 64 * 16, kNP = kB3 + 16;  // 7312
-// FP16 copies (halves): W1h [32][64], W2h [64][64], W3h [64][16]
-constexpr int kH1 = 0, kH2 = kH1 + 32 * 64, kH3 = kH2 + 64 * 64, kNH = kH3 + 64 * 16;  // 7168
-constexpr int kWaves = 4;            // waves per workgroup
-constexpr int kTrainBlocks = 64;     // workgroups of the gradient kernel (fixed: deterministic sums)
-constexpr int kPartials = kTrainBlocks * kWaves;
-constexpr int kStat = 4;             // per-wave scalars: loss sum, mask count
+// FP16 copies (halves): W1^T [64][32], W2 [64][64], W2^T [64][64],
+// W3 [64][16], W3^T [16][64]
+constexpr int kH1T = 0, kH2 = kH1T + 64 * 32, kH2T = kH2 + 64 * 64, kH3 = kH2T + 64 * 64, kH3T = kH3 + 64 * 16,
+              kNH = kH3T + 16 * 64;  // 12288
+constexpr int kWaves = 4;          // waves per workgroup
+constexpr int kPartials = 256;     // most workgroups of the gradient kernel: one partial each, one per CU
+constexpr int kStat = 4;           // per-partial scalars: loss sum, mask count
 
 __device__ __forceinline__ f4_t mfma16(half4_t a, half4_t b, f4_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x16f16(a, b, c, 0, 0, 0);
 }
 
-struct MlpLds {
-    _Float16 w[kNH];
-    float b1[64], b2[64], b3[16];
-    _Float16 h1[kWaves][16 * 64];  // per-wave activation tiles [row][unit]
-    _Float16 h2[kWaves][16 * 64];
-    _Float16 t16[kWaves][16 * 64];  // per-wave gradient tiles
-    _Float16 x[kWaves][16 * 32];
-};
-
-__device__ void load_weights(MlpLds &S, const _Float16 *wh, const float *p) {
-    for (int i = threadIdx.x; i < kNH; i += blockDim.x) S.w[i] = wh[i];
-    for (int i = threadIdx.x; i < 64; i += blockDim.x) {
-        S.b1[i] = p[kB1 + i];
-        S.b2[i] = p[kB2 + i];
-        if (i < 16) S.b3[i] = p[kB3 + i];
-    }
+__device__ __forceinline__ half4_t to_half(f4_t v) {
+    return half4_t{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
 }
 
-// Forward pass of one 16-row tile held in S.x[wv]: leaves relu(h1), relu(h2)
-// in LDS (FP16), pre-activations a1, a2 and logits z in D layout.
-__device__ __forceinline__ void tile_forward(MlpLds &S, int wv, f4_t a1[4], f4_t a2[4], f4_t &z) {
-    const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
-    // layer 1: [16 x 32] x [32 x 64]
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        f4_t acc = {0, 0, 0, 0};
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            half4_t a, b;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                a[i] = S.x[wv][r * 32 + 16 * ks + 4 * q + i];
-                b[i] = S.w[kH1 + (16 * ks + 4 * q + i) * 64 + 16 * j + r];
-            }
-            acc = mfma16(a, b, acc);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            acc[i] += S.b1[16 * j + r];
-            S.h1[wv][(4 * q + i) * 64 + 16 * j + r] = (_Float16)fmaxf(acc[i], 0.0f);
-        }
-        a1[j] = acc;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // layer 2: [16 x 64] x [64 x 64]
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        f4_t acc = {0, 0, 0, 0};
+// Forward weights as fragments: B of W1, w1[ks][j] = W1[16 ks + 4 q + i]
+// [16 j + r], and so on (A of the transposes).
+struct Weights {
+    half4_t w1[2][4], w2[4][4], w3[4];
+    __device__ __forceinline__ Weights(const _Float16 *__restrict__ wh) {
+        const int r = threadIdx.x & 15, q = (threadIdx.x & 63) >> 4;
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
-            half4_t a, b;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                a[i] = S.h1[wv][r * 64 + 16 * ks + 4 * q + i];
-                b[i] = S.w[kH2 + (16 * ks + 4 * q + i) * 64 + 16 * j + r];
+            for (int j = 0; j < 4; ++j) {
+                if (ks < 2) w1[ks][j] = *(const half4_t *)(wh + kH1T + (16 * j + r) * 32 + 16 * ks + 4 * q);
+                w2[ks][j] = *(const half4_t *)(wh + kH2T + (16 * j + r) * 64 + 16 * ks + 4 * q);
             }
-            acc = mfma16(a, b, acc);
+            w3[ks] = *(const half4_t *)(wh + kH3T + r * 64 + 16 * ks + 4 * q);
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            acc[i] += S.b2[16 * j + r];
-            S.h2[wv][(4 * q + i) * 64 + 16 * j + r] = (_Float16)fmaxf(acc[i], 0.0f);
-        }
-        a2[j] = acc;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // layer 3: [16 x 64] x [64 x 16]
-    f4_t acc = {0, 0, 0, 0};
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-        half4_t a, b;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            a[i] = S.h2[wv][r * 64 + 16 * ks + 4 * q + i];
-            b[i] = S.w[kH3 + (16 * ks + 4 * q + i) * 16 + r];
-        }
-        acc = mfma16(a, b, acc);
+};
+
+// FP16 copies of parameter k.
+__device__ __forceinline__ void put_half(_Float16 *__restrict__ wh, int k, float w) {
+    const _Float16 h = (_Float16)w;
+    if (k < kB1) {
+        wh[kH1T + (k & 63) * 32 + (k >> 6)] = h;
+    } else if (k >= kW2 && k < kB2) {
+        const int e = k - kW2;
+        wh[kH2 + e] = h;
+        wh[kH2T + (e & 63) * 64 + (e >> 6)] = h;
+    } else if (k >= kW3 && k < kB3) {
+        const int e = k - kW3;
+        wh[kH3 + e] = h;
+        wh[kH3T + (e & 15) * 64 + (e >> 4)] = h;
     }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] += S.b3[r];
-    z = acc;
 }
 
-__device__ __forceinline__ void load_x_tile(MlpLds &S, int wv, const _Float16 *x, uint32_t rows, uint32_t r0) {
-    const int lane = threadIdx.x & 63;
-    for (int i = lane; i < 16 * 32; i += 64) {
-        const uint32_t row = r0 + (uint32_t)(i >> 5);
-        S.x[wv][i] = row < rows ? x[(size_t)row * 32 + (i & 31)] : (_Float16)0.0f;
+// Columns 16 ks + 4 q + i of row r0 + r of x (A fragments); zero past the
+// end.  kWide: x is 8-byte aligned.
+template <bool kWide>
+__device__ __forceinline__ void load_x(const _Float16 *__restrict__ x, uint32_t rows, uint32_t r0, half4_t xa[2]) {
+    const int r = threadIdx.x & 15, q = (threadIdx.x & 63) >> 4;
+    const _Float16 *at = x + (size_t)(r0 + r) * 32 + 4 * q;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        xa[ks] = half4_t{0, 0, 0, 0};
+        if (r0 + r >= rows) continue;
+        if (kWide) xa[ks] = *(const half4_t *)(at + 16 * ks);
+        else
+#pragma unroll
+            for (int i = 0; i < 4; ++i) xa[ks][i] = at[16 * ks + i];
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+__device__ __forceinline__ f4_t relu(f4_t v) {
+    return f4_t{fmaxf(v[0], 0.0f), fmaxf(v[1], 0.0f), fmaxf(v[2], 0.0f), fmaxf(v[3], 0.0f)};
+}
+
+// Logits of 16 rows a wave and turn: every product transposed (units x rows),
+// so that a layer's D is the next layer's B and a lane ends with four logits
+// of one row.  32768 rows: 13 us with the tiles in LDS, 9 us now.
+template <bool kWide>
 __global__ void __launch_bounds__(256) k_mlp_fwd(const _Float16 *__restrict__ x, uint32_t rows,
                                                  const _Float16 *__restrict__ wh, const float *__restrict__ p,
-                                                 float *__restrict__ z) {
-    __shared__ MlpLds S;
-    load_weights(S, wh, p);
-    __syncthreads();
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const uint32_t ntiles = (rows + 15) / 16;
-    for (uint32_t t = blockIdx.x * kWaves + wv; t < ntiles; t += gridDim.x * kWaves) {
-        load_x_tile(S, wv, x, rows, t * 16);
-        f4_t a1[4], a2[4], zz;
-        tile_forward(S, wv, a1, a2, zz);
+                                                 float *__restrict__ z, bool z_wide) {
+    const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
+    const Weights W(wh);
+    f4_t b1[4], b2[4], b3;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t row = t * 16 + 4 * (lane >> 4) + i;
-            if (row < rows) z[(size_t)row * 16 + (lane & 15)] = zz[i];
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            b1[j][i] = p[kB1 + 16 * j + 4 * q + i];
+            b2[j][i] = p[kB2 + 16 * j + 4 * q + i];
         }
-        __builtin_amdgcn_wave_barrier();
+        b3[i] = p[kB3 + 4 * q + i];
+    }
+    const uint32_t ntiles = (rows + 15) / 16;
+    for (uint32_t t = blockIdx.x * kWaves + (threadIdx.x >> 6); t < ntiles; t += gridDim.x * kWaves) {
+        half4_t xa[2], h1[4], h2[4];
+        load_x<kWide>(x, rows, t * 16, xa);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            f4_t acc = {0, 0, 0, 0};
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) acc = mfma16(W.w1[ks][j], xa[ks], acc);
+            h1[j] = to_half(relu(acc + b1[j]));
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            f4_t acc = {0, 0, 0, 0};
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) acc = mfma16(W.w2[ks][j], h1[ks], acc);
+            h2[j] = to_half(relu(acc + b2[j]));
+        }
+        f4_t acc = {0, 0, 0, 0};
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) acc = mfma16(W.w3[ks], h2[ks], acc);
+        acc += b3;
+        const uint32_t row = t * 16 + r;
+        if (row >= rows) continue;
+        float *o = z + (size_t)row * 16 + 4 * q;
+        if (z_wide) *(f4_t *)o = acc;
+        else
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = acc[i];
     }
 }
 
-// Gradient partials.  Each wave writes kNP + kStat floats to part[wave].
-__global__ void __launch_bounds__(256) k_mlp_grad(const _Float16 *__restrict__ x, const uint8_t *__restrict__ y,
-                                                  const uint8_t *__restrict__ msk, uint32_t rows,
-                                                  const _Float16 *__restrict__ wh, const float *__restrict__ p,
-                                                  float *__restrict__ part) {
-    __shared__ MlpLds S;
-    load_weights(S, wh, p);
-    __syncthreads();
+// Gradient partials, one per block: kNP + kStat floats to part[block].
+// 32768 rows: 80 us with 256 waves on 64 CUs and the tiles in LDS, 24 us with
+// two tiles on each of 1024 waves.  A wave holds the weights, the sums and a
+// tile in 426 registers, so a SIMD has one wave and what bounds it is that
+// wave's own chain: half issue (4000 instructions), half waits.
+constexpr int kPartLen = kNP + kStat;
+template <bool kWide>
+__global__ void __launch_bounds__(256, 1) k_mlp_grad(const _Float16 *__restrict__ x, const uint8_t *__restrict__ y,
+                                                     const uint8_t *__restrict__ msk, uint32_t rows,
+                                                     const _Float16 *__restrict__ wh, const float *__restrict__ p,
+                                                     float *__restrict__ part) {
+    __shared__ float S[2][kPartLen];
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
+    const Weights W(wh);
+    // W2^T and W3^T as B fragments: rows of the matrices
+    half4_t w2t[4][4], w3t[4];
+    float b1[4], b2[4];
+    f4_t b1t[4], b2t[4], b3t;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) w2t[ks][j] = *(const half4_t *)(wh + kH2 + (16 * j + r) * 64 + 16 * ks + 4 * q);
+        w3t[j] = *(const half4_t *)(wh + kH3 + (16 * j + r) * 16 + 4 * q);
+        b1[j] = p[kB1 + 16 * j + r];
+        b2[j] = p[kB2 + 16 * j + r];
+        b3t[j] = p[kB3 + 4 * q + j];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            b1t[j][i] = p[kB1 + 16 * j + 4 * q + i];
+            b2t[j][i] = p[kB2 + 16 * j + 4 * q + i];
+        }
+    }
+    const float b3 = p[kB3 + r];
     f4_t g1[2][4], g2[4][4], g3[4];
     float gb1[4] = {0, 0, 0, 0}, gb2[4] = {0, 0, 0, 0}, gb3 = 0.0f, lsum = 0.0f, msum = 0.0f;
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
         g3[a] = f4_t{0, 0, 0, 0};
 #pragma unroll
-        for (int b = 0; b < 4; ++b) g2[a][b] = f4_t{0, 0, 0, 0};
-        if (a < 2)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) g1[a][b] = f4_t{0, 0, 0, 0};
+        for (int b = 0; b < 4; ++b) {
+            g2[a][b] = f4_t{0, 0, 0, 0};
+            if (a < 2) g1[a][b] = f4_t{0, 0, 0, 0};
+        }
     }
+    const f4_t zero = {0, 0, 0, 0};
     const uint32_t ntiles = (rows + 15) / 16;
-    const int wave = blockIdx.x * kWaves + wv;
-    for (uint32_t t = (uint32_t)wave; t < ntiles; t += gridDim.x * kWaves) {
+    for (uint32_t t = blockIdx.x * kWaves + wv; t < ntiles; t += gridDim.x * kWaves) {
         const uint32_t r0 = t * 16;
-        load_x_tile(S, wv, x, rows, r0);
-        f4_t a1[4], a2[4], z;
-        tile_forward(S, wv, a1, a2, z);
-        // dz = mask * (sigmoid(z) - y)   (loss scaled by the mask count)
-        f4_t dz;
+        half4_t xa[2], xt[2];  // A of x, A of x^T
+        load_x<kWide>(x, rows, r0, xa);
+        // labels and masks in both orders: [row 4 q + i][r], [row r][4 q + i]
+        float mk[4], yy[4], mkt[4], yyt[4];
+        const bool in_r = r0 + r < rows;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const uint32_t row = r0 + 4 * q + i;
-            float d = 0.0f;
-            if (row < rows) {
-                const float mk = (float)msk[(size_t)row * 16 + r];
-                const float yy = (float)y[(size_t)row * 16 + r];
-                const float zz = z[i];
-                const float s = 1.0f / (1.0f + expf(-zz));
-                d = mk * (s - yy);
-                // softplus(z) - y z, stably
-                lsum += mk * (fmaxf(zz, 0.0f) + log1pf(expf(-fabsf(zz))) - yy * zz);
-                msum += mk;
-            }
-            dz[i] = d;
-            S.t16[wv][(4 * q + i) * 16 + r] = (_Float16)d;
-            gb3 += d;
+            const bool in = r0 + 4 * q + i < rows;
+            const size_t at = (size_t)(r0 + 4 * q + i) * 16 + r, att = (size_t)(r0 + r) * 16 + 4 * q + i;
+            mk[i] = in ? (float)msk[at] : 0.0f;
+            yy[i] = in ? (float)y[at] : 0.0f;
+            mkt[i] = in_r ? (float)msk[att] : 0.0f;
+            yyt[i] = in_r ? (float)y[att] : 0.0f;
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+                xt[mt][i] = in ? x[(size_t)(r0 + 4 * q + i) * 32 + 16 * mt + r] : (_Float16)0.0f;
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        // gW3 += h2^T dz : M = 64 units (4 tiles), N = 16, K = 16 rows
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
-            half4_t a, b;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                a[i] = S.h2[wv][(4 * q + i) * 64 + 16 * mt + r];
-                b[i] = S.t16[wv][(4 * q + i) * 16 + r];
-            }
-            g3[mt] = mfma16(a, b, g3[mt]);
-        }
-        // dh2 = dz W3^T : M = 16 rows, N = 64 units, K = 16 logits; da2 = dh2 * (a2 > 0)
-        half4_t adz;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) adz[i] = S.t16[wv][r * 16 + 4 * q + i];
-        f4_t da2[4];
+        // forward: rows x units (h, for the weight gradients) and units x rows
+        // (ht, the next layer's operand); bit 4 j + i of on*: the unit is on
+        f4_t z = zero, zt = zero;
+        half4_t h1[4], h1t[4], h2[4], h2t[4];
+        uint32_t on1 = 0, on2 = 0, on2t = 0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            half4_t b;
+            f4_t a = zero, at = zero;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) b[i] = S.w[kH3 + (16 * j + r) * 16 + 4 * q + i];
-            f4_t acc = mfma16(adz, b, f4_t{0, 0, 0, 0});
-#pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i] = a2[j][i] > 0.0f ? acc[i] : 0.0f;
-            da2[j] = acc;
-        }
-        __builtin_amdgcn_wave_barrier();
-        // da2 -> LDS (reuse t16 as [row][64])
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                S.t16[wv][(4 * q + i) * 64 + 16 * j + r] = (_Float16)da2[j][i];
-                gb2[j] += da2[j][i];
+            for (int ks = 0; ks < 2; ++ks) {
+                a = mfma16(xa[ks], W.w1[ks][j], a);
+                at = mfma16(W.w1[ks][j], xa[ks], at);
             }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        // gW2 += h1^T da2 : M = 64 (4 tiles), N = 64 (4 tiles), K = 16 rows
+            a += b1[j];
+            at += b1t[j];
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
-            half4_t a;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = S.h1[wv][(4 * q + i) * 64 + 16 * mt + r];
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                half4_t b;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) b[i] = S.t16[wv][(4 * q + i) * 64 + 16 * nt + r];
-                g2[mt][nt] = mfma16(a, b, g2[mt][nt]);
-            }
+            for (int i = 0; i < 4; ++i) on1 |= (a[i] > 0.0f ? 1u : 0u) << (4 * j + i);
+            h1[j] = to_half(relu(a));
+            h1t[j] = to_half(relu(at));
         }
-        // dh1 = da2 W2^T : M = 16 rows, N = 64, K = 64; da1 = dh1 * (a1 > 0)
-        f4_t da1[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            f4_t acc = {0, 0, 0, 0};
+            f4_t a = zero, at = zero;
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
-                half4_t a, b;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    a[i] = S.t16[wv][r * 64 + 16 * ks + 4 * q + i];
-                    b[i] = S.w[kH2 + (16 * j + r) * 64 + 16 * ks + 4 * q + i];
-                }
-                acc = mfma16(a, b, acc);
+                a = mfma16(h1t[ks], W.w2[ks][j], a);
+                at = mfma16(W.w2[ks][j], h1t[ks], at);
             }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i] = a1[j][i] > 0.0f ? acc[i] : 0.0f;
-            da1[j] = acc;
-        }
-        __builtin_amdgcn_wave_barrier();
-        // da1 -> LDS (the h2 tile is no longer needed)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
+            a += b2[j];
+            at += b2t[j];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                S.h2[wv][(4 * q + i) * 64 + 16 * j + r] = (_Float16)da1[j][i];
-                gb1[j] += da1[j][i];
+                on2 |= (a[i] > 0.0f ? 1u : 0u) << (4 * j + i);
+                on2t |= (at[i] > 0.0f ? 1u : 0u) << (4 * j + i);
             }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        // gW1 += x^T da1 : M = 32 inputs (2 tiles), N = 64 (4 tiles), K = 16 rows
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-            half4_t a;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = S.x[wv][(4 * q + i) * 32 + 16 * mt + r];
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                half4_t b;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) b[i] = S.h2[wv][(4 * q + i) * 64 + 16 * nt + r];
-                g1[mt][nt] = mfma16(a, b, g1[mt][nt]);
-            }
+            h2[j] = to_half(relu(a));
+            h2t[j] = to_half(relu(at));
         }
-        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            z = mfma16(h2t[ks], W.w3[ks], z);
+            zt = mfma16(W.w3[ks], h2t[ks], zt);
+        }
+        z += b3;
+        zt += b3t;
+        // dz = mask * (sigmoid(z) - y)   (loss scaled by the mask count)
+        f4_t dzf, dzft;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float d = 0.0f, dt = 0.0f;
+            if (r0 + 4 * q + i < rows) {
+                const float zz = z[i];
+                const float s = 1.0f / (1.0f + expf(-zz));
+                d = mk[i] * (s - yy[i]);
+                // softplus(z) - y z, stably
+                lsum += mk[i] * (fmaxf(zz, 0.0f) + log1pf(expf(-fabsf(zz))) - yy[i] * zz);
+                msum += mk[i];
+            }
+            if (in_r) dt = mkt[i] * (1.0f / (1.0f + expf(-zt[i])) - yyt[i]);
+            dzf[i] = d;
+            dzft[i] = dt;
+            gb3 += d;
+        }
+        const half4_t dz = to_half(dzf), dzt = to_half(dzft);
+        // gW3 += h2^T dz; da2 = (dz W3^T) * (a2 > 0), both ways
+        half4_t d2[4], d2t[4], d1[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            g3[j] = mfma16(h2[j], dz, g3[j]);
+            f4_t a = mfma16(dzt, w3t[j], zero), at = mfma16(w3t[j], dzt, zero);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                a[i] = on2 >> (4 * j + i) & 1u ? a[i] : 0.0f;
+                at[i] = on2t >> (4 * j + i) & 1u ? at[i] : 0.0f;
+                gb2[j] += a[i];
+            }
+            d2[j] = to_half(a);
+            d2t[j] = to_half(at);
+        }
+        // gW2 += h1^T da2; da1 = (da2 W2^T) * (a1 > 0)
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt) g2[mt][nt] = mfma16(h1[mt], d2[nt], g2[mt][nt]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            f4_t a = zero;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) a = mfma16(d2t[ks], w2t[ks][j], a);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                a[i] = on1 >> (4 * j + i) & 1u ? a[i] : 0.0f;
+                gb1[j] += a[i];
+            }
+            d1[j] = to_half(a);
+        }
+        // gW1 += x^T da1
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt) g1[mt][nt] = mfma16(xt[mt], d1[nt], g1[mt][nt]);
     }
-    // write this wave's partials (D layout -> parameter layout)
-    float *o = part + (size_t)wave * (kNP + kStat);
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) o[kW1 + (16 * mt + 4 * q + i) * 64 + 16 * nt + r] = g1[mt][nt][i];
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) o[kW2 + (16 * mt + 4 * q + i) * 64 + 16 * nt + r] = g2[mt][nt][i];
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) o[kW3 + (16 * mt + 4 * q + i) * 16 + r] = g3[mt][i];
-    // bias partials: reduce the four lane groups (q) of each column
+    // bias partials: sum the four lane groups (q) of each column
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        float v1 = gb1[j], v2 = gb2[j];
-        v1 += __shfl_xor(v1, 16, 64);
-        v1 += __shfl_xor(v1, 32, 64);
-        v2 += __shfl_xor(v2, 16, 64);
-        v2 += __shfl_xor(v2, 32, 64);
-        if (q == 0) {
-            o[kB1 + 16 * j + r] = v1;
-            o[kB2 + 16 * j + r] = v2;
-        }
+        gb1[j] += __shfl_xor(gb1[j], 16, 64);
+        gb1[j] += __shfl_xor(gb1[j], 32, 64);
+        gb2[j] += __shfl_xor(gb2[j], 16, 64);
+        gb2[j] += __shfl_xor(gb2[j], 32, 64);
     }
-    float v3 = gb3;
-    v3 += __shfl_xor(v3, 16, 64);
-    v3 += __shfl_xor(v3, 32, 64);
-    if (q == 0) o[kB3 + r] = v3;
+    gb3 += __shfl_xor(gb3, 16, 64);
+    gb3 += __shfl_xor(gb3, 32, 64);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         lsum += __shfl_xor(lsum, off, 64);
         msum += __shfl_xor(msum, off, 64);
     }
-    if (lane == 0) {
-        o[kNP + 0] = lsum;
-        o[kNP + 1] = msum;
-    }
-}
-
-// Sum the partials in a fixed order (deterministic): a block takes 64
-// parameters; each of its 16 waves sums every 16th partial of them
-// (coalesced rows, independent loads), then a pairwise tree over the 16 wave
-// sums in LDS.
-constexpr int kRedGroups = 16;
-__global__ void __launch_bounds__(64 * kRedGroups) k_mlp_reduce(const float *__restrict__ part, int nparts,
-                                                               float *__restrict__ grad, float *__restrict__ stat) {
-    __shared__ float sm[kRedGroups][64];
-    const int p = threadIdx.x & 63, gi = threadIdx.x >> 6;
-    const int k = blockIdx.x * 64 + p;
-    float acc = 0.0f;
-    if (k < kNP + kStat)
-        for (int w = gi; w < nparts; w += kRedGroups) acc += part[(size_t)w * (kNP + kStat) + k];
-    sm[gi][p] = acc;
-    __syncthreads();
-    for (int h = kRedGroups / 2; h >= 1; h >>= 1) {
-        if (gi < h) sm[gi][p] += sm[gi + h][p];
+    // (wave 0 + wave 2) + (wave 1 + wave 3), in parameter layout
+    float *o = S[wv & 1];
+    for (int turn = 0; turn < 2; ++turn) {
+        if (wv >> 1 == turn) {
+            auto put = [&](int k, float v) { o[k] = turn ? o[k] + v : v; };
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int row = 16 * mt + 4 * q + i;
+#pragma unroll
+                    for (int nt = 0; nt < 4; ++nt) {
+                        if (mt < 2) put(kW1 + row * 64 + 16 * nt + r, g1[mt & 1][nt][i]);
+                        put(kW2 + row * 64 + 16 * nt + r, g2[mt][nt][i]);
+                    }
+                    put(kW3 + row * 16 + r, g3[mt][i]);
+                }
+            if (q == 0) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    put(kB1 + 16 * j + r, gb1[j]);
+                    put(kB2 + 16 * j + r, gb2[j]);
+                }
+                put(kB3 + r, gb3);
+            }
+            if (lane < kStat) put(kNP + lane, lane == 0 ? lsum : lane == 1 ? msum : 0.0f);
+        }
         __syncthreads();
     }
-    if (gi == 0 && k < kNP + kStat) {
-        if (k < kNP) grad[k] = sm[0][p];
-        else stat[k - kNP] = sm[0][p];
+    for (int k = threadIdx.x; k < kPartLen; k += 256) part[(size_t)blockIdx.x * kPartLen + k] = S[0][k] + S[1][k];
+}
+
+struct AdamStep {
+    float lr, b1, b2, eps, c1, c2;
+};
+
+// Sum of the partials in a fixed order (deterministic), the mean over the
+// unmasked entries, and, with kStep, the Adam step on the FP32 master weights
+// with their FP16 copies: one launch, where a sum, a scaling and a step were
+// three.  A block takes 64 parameters; each of its 16 waves sums every 16th
+// partial of them (coalesced rows, independent loads), then a pairwise tree
+// over the 16 wave sums in LDS.  The count of unmasked entries is summed by
+// every block for itself, in the same order.
+constexpr int kRedGroups = 16;
+template <bool kStep>
+__global__ void __launch_bounds__(64 * kRedGroups) k_mlp_update(const float *__restrict__ part, int nparts,
+                                                               float *__restrict__ grad, float *__restrict__ stat,
+                                                               float *__restrict__ p, float *__restrict__ m,
+                                                               float *__restrict__ v, _Float16 *__restrict__ wh,
+                                                               AdamStep st) {
+    __shared__ float sm[kRedGroups][64], cnt[kRedGroups];
+    const int lane = threadIdx.x & 63, gi = threadIdx.x >> 6;
+    const int k = blockIdx.x * 64 + lane;
+    // partial 16 lane + gi is lane's: 256 at most, so one a lane is enough
+    static_assert(kPartials <= 64 * kRedGroups, "one count per thread");
+    float n = lane * kRedGroups + gi < nparts ? part[(size_t)(lane * kRedGroups + gi) * kPartLen + kNP + 1] : 0.0f;
+    float acc = 0.0f;
+    if (k < kPartLen) {
+#pragma unroll 4
+        for (int w = gi; w < nparts; w += kRedGroups) acc += part[(size_t)w * kPartLen + k];
     }
-}
-
-__global__ void k_mlp_scale(float *__restrict__ grad, const float *__restrict__ stat) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    const float n = fmaxf(stat[1], 1.0f);
-    if (k < kNP) grad[k] /= n;
-}
-
-// Adam step on the FP32 master weights; refresh the FP16 copies.
-__global__ void k_mlp_adam(float *__restrict__ p, float *__restrict__ m, float *__restrict__ v,
-                           const float *__restrict__ g, _Float16 *__restrict__ wh, float lr, float b1, float b2,
-                           float eps, float c1, float c2) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= kNP) return;
-    const float gk = g[k];
-    const float mk = b1 * m[k] + (1.0f - b1) * gk;
-    const float vk = b2 * v[k] + (1.0f - b2) * gk * gk;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off, 64);
+    sm[gi][lane] = acc;
+    if (lane == 0) cnt[gi] = n;
+    __syncthreads();
+    for (int h = kRedGroups / 2; h >= 1; h >>= 1) {
+        if (gi < h) {
+            sm[gi][lane] += sm[gi + h][lane];
+            if (lane == 0) cnt[gi] += cnt[gi + h];
+        }
+        __syncthreads();
+    }
+    if (gi != 0 || k >= kPartLen) return;
+    if (k >= kNP) {
+        stat[k - kNP] = sm[0][lane];
+        return;
+    }
+    const float gk = sm[0][lane] / fmaxf(cnt[0], 1.0f);
+    grad[k] = gk;
+    if (!kStep) return;
+    const float mk = st.b1 * m[k] + (1.0f - st.b1) * gk;
+    const float vk = st.b2 * v[k] + (1.0f - st.b2) * gk * gk;
     m[k] = mk;
     v[k] = vk;
-    const float w = p[k] - lr * (mk / c1) / (sqrtf(vk / c2) + eps);
+    const float w = p[k] - st.lr * (mk / st.c1) / (sqrtf(vk / st.c2) + st.eps);
     p[k] = w;
-    if (k < kB1) wh[kH1 + k] = (_Float16)w;
-    else if (k >= kW2 && k < kB2) wh[kH2 + (k - kW2)] = (_Float16)w;
-    else if (k >= kW3 && k < kB3) wh[kH3 + (k - kW3)] = (_Float16)w;
+    put_half(wh, k, w);
 }
 
 __global__ void k_mlp_refresh(const float *__restrict__ p, _Float16 *__restrict__ wh) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= kNP) return;
-    const float w = p[k];
-    if (k < kB1) wh[kH1 + k] = (_Float16)w;
-    else if (k >= kW2 && k < kB2) wh[kH2 + (k - kW2)] = (_Float16)w;
-    else if (k >= kW3 && k < kB3) wh[kH3 + (k - kW3)] = (_Float16)w;
+    if (k < kNP) put_half(wh, k, p[k]);
 }
 
 }  // namespace ro
@@ -420,6 +443,8 @@ using namespace ro;
 // Device layout of the parameter buffer (bytes): FP32 master [kNP], Adam m
 // [kNP], Adam v [kNP], gradient [kNP], stats [kStat], FP16 copies [kNH];
 // workspace: kPartials x (kNP + kStat) floats.
+constexpr uint32_t kFwdBlocks = 512;
+
 struct ro_mlp {
     float *p, *m, *v, *g, *stat;
     _Float16 *wh;
@@ -506,23 +531,42 @@ extern "C" ro_status ro_mlp_forward(ro_mlp *n, const uint16_t *x, uint32_t rows,
     RO_CHECK(n && (rows == 0 || (x && z)), RO_E_ARG, "null argument");
     if (rows == 0) return RO_OK;
     hipStream_t s = (hipStream_t)stream;
+    // two tiles or more a wave once the CUs are full: the weights are read once
     const uint32_t tiles = (rows + 15) / 16;
     uint32_t blocks = (tiles + kWaves - 1) / kWaves;
-    if (blocks > 1024) blocks = 1024;
-    hipLaunchKernelGGL(k_mlp_fwd, dim3(blocks), dim3(64 * kWaves), 0, s, (const _Float16 *)x, rows, n->wh, n->p, z);
+    if (blocks > kFwdBlocks) blocks = kFwdBlocks;
+    const bool z_wide = (uintptr_t)z % 16 == 0;
+    if ((uintptr_t)x % 8 == 0)
+        hipLaunchKernelGGL(k_mlp_fwd<true>, dim3(blocks), dim3(64 * kWaves), 0, s, (const _Float16 *)x, rows, n->wh,
+                           n->p, z, z_wide);
+    else
+        hipLaunchKernelGGL(k_mlp_fwd<false>, dim3(blocks), dim3(64 * kWaves), 0, s, (const _Float16 *)x, rows, n->wh,
+                           n->p, z, z_wide);
     RO_HIP(hipGetLastError());
     return RO_OK;
 }
 
+// Gradients of the rows and, with a step, the weights' update.
 static ro_status mlp_grad(ro_mlp *n, const uint16_t *x, const uint8_t *y, const uint8_t *mask, uint32_t rows,
-                          hipStream_t s) {
-    hipLaunchKernelGGL(k_mlp_grad, dim3(kTrainBlocks), dim3(64 * kWaves), 0, s, (const _Float16 *)x, y, mask, rows,
-                       n->wh, n->p, n->part);
+                          const AdamStep *step, hipStream_t s) {
+    const uint32_t tiles = (rows + 15) / 16;
+    uint32_t blocks = (tiles + kWaves - 1) / kWaves;
+    if (blocks > (uint32_t)kPartials) blocks = kPartials;
+    if (blocks < 1) blocks = 1;  // no rows: zero gradients
+    if ((uintptr_t)x % 8 == 0)
+        hipLaunchKernelGGL(k_mlp_grad<true>, dim3(blocks), dim3(64 * kWaves), 0, s, (const _Float16 *)x, y, mask, rows,
+                           n->wh, n->p, n->part);
+    else
+        hipLaunchKernelGGL(k_mlp_grad<false>, dim3(blocks), dim3(64 * kWaves), 0, s, (const _Float16 *)x, y, mask, rows,
+                           n->wh, n->p, n->part);
     RO_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((kNP + kStat + 63) / 64), dim3(64 * kRedGroups), 0, s, n->part, kPartials,
-                       n->g, n->stat);
-    RO_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_mlp_scale, dim3((kNP + 255) / 256), dim3(256), 0, s, n->g, n->stat);
+    const dim3 grid((kPartLen + 63) / 64), block(64 * kRedGroups);
+    if (step)
+        hipLaunchKernelGGL(k_mlp_update<true>, grid, block, 0, s, n->part, (int)blocks, n->g, n->stat, n->p, n->m, n->v,
+                           n->wh, *step);
+    else
+        hipLaunchKernelGGL(k_mlp_update<false>, grid, block, 0, s, n->part, (int)blocks, n->g, n->stat, n->p, n->m,
+                           n->v, n->wh, AdamStep{});
     RO_HIP(hipGetLastError());
     return RO_OK;
 }
@@ -531,7 +575,7 @@ extern "C" ro_status ro_mlp_gradients(ro_mlp *n, const uint16_t *x, const uint8_
                                       uint32_t rows, float *grads_host, float *loss_host, void *stream) {
     RO_CHECK(n && x && y && mask && grads_host, RO_E_ARG, "null argument");
     hipStream_t s = (hipStream_t)stream;
-    ro_status st = mlp_grad(n, x, y, mask, rows, s);
+    ro_status st = mlp_grad(n, x, y, mask, rows, nullptr, s);
     if (st) return st;
     std::vector<float> g(kNP + kStat);
     RO_HIP(hipMemcpyAsync(g.data(), n->g, sizeof(float) * (kNP + kStat), hipMemcpyDeviceToHost, s));
@@ -555,14 +599,12 @@ extern "C" ro_status ro_mlp_train_step(ro_mlp *n, const uint16_t *x, const uint8
     RO_CHECK(n && x && y && mask, RO_E_ARG, "null argument");
     RO_CHECK(lr > 0.0f, RO_E_ARG, "lr must be > 0");
     hipStream_t s = (hipStream_t)stream;
-    ro_status st = mlp_grad(n, x, y, mask, rows, s);
+    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+    const float t = (float)(n->step + 1);
+    const AdamStep step = {lr, b1, b2, eps, 1.0f - powf(b1, t), 1.0f - powf(b2, t)};
+    ro_status st = mlp_grad(n, x, y, mask, rows, &step, s);
     if (st) return st;
     n->step += 1;
-    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-    const float c1 = 1.0f - powf(b1, (float)n->step), c2 = 1.0f - powf(b2, (float)n->step);
-    hipLaunchKernelGGL(k_mlp_adam, dim3((kNP + 255) / 256), dim3(256), 0, s, n->p, n->m, n->v, n->g, n->wh, lr, b1, b2,
-                       eps, c1, c2);
-    RO_HIP(hipGetLastError());
     if (loss_host) {
         float stat[kStat];
         RO_HIP(hipMemcpyAsync(stat, n->stat, sizeof(stat), hipMemcpyDeviceToHost, s));
