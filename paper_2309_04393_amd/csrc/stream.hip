@@ -61,67 +61,112 @@ __device__ inline uint32_t block_excl_scan_256(uint32_t v, uint32_t *lds4, uint3
 
 // ------------------------------------------------------ request compaction
 
+// Four counters of a thread, in one load where the array allows it (a score
+// array is the caller's); zero past the end.
+__device__ inline uint4 load_four(const uint32_t *__restrict__ arr, uint64_t base, uint64_t n) {
+    if (base + 4 <= n && ((uintptr_t)arr & 15) == 0) return *(const uint4 *)(arr + base);
+    uint4 v = {0, 0, 0, 0};
+    if (base < n) v.x = arr[base];
+    if (base + 1 < n) v.y = arr[base + 1];
+    if (base + 2 < n) v.z = arr[base + 2];
+    if (base + 3 < n) v.w = arr[base + 3];
+    return v;
+}
+
+// Sum over the block of 256, the same in every thread.
+__device__ inline unsigned long long block_sum_256(unsigned long long v, unsigned long long *lds4) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if ((threadIdx.x & 63) == 0) lds4[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = lds4[0] + lds4[1] + lds4[2] + lds4[3];
+    __syncthreads();
+    return v;
+}
+
+// Result of a compaction, read back in one copy.
+struct CompactTotals {
+    unsigned long long sum;
+    uint32_t n;
+    uint32_t pad;
+};
+
 // Per block of 1024 counters: number of nonzero counters and the sum of all.
 __global__ void __launch_bounds__(256) k_req_count(const uint32_t *__restrict__ cnt, uint64_t n,
                                                    uint32_t *__restrict__ blk,
-                                                   unsigned long long *__restrict__ total) {
-    __shared__ uint32_t lds[4];
-    uint64_t base = (uint64_t)blockIdx.x * 1024 + threadIdx.x * 4;
-    uint32_t nz = 0;
-    unsigned long long sum = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        uint64_t i = base + k;
-        if (i < n) {
-            uint32_t v = cnt[i];
-            nz += v != 0;
-            sum += v;
-        }
+                                                   unsigned long long *__restrict__ sums) {
+    __shared__ unsigned long long lds[4];
+    const uint4 v = load_four(cnt, (uint64_t)blockIdx.x * 1024 + threadIdx.x * 4, n);
+    const uint32_t nz = (v.x != 0) + (v.y != 0) + (v.z != 0) + (v.w != 0);
+    const unsigned long long tot = block_sum_256(nz, lds);
+    const unsigned long long sum = block_sum_256((unsigned long long)v.x + v.y + v.z + v.w, lds);
+    if (threadIdx.x == 0) {
+        blk[blockIdx.x] = (uint32_t)tot;
+        sums[blockIdx.x] = sum;
     }
-    uint32_t tot;
-    block_excl_scan_256(nz, lds, &tot);
-    // wave-reduce the sums, one atomic per wave
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-    if ((threadIdx.x & 63) == 0 && sum) atomicAdd(total, sum);
-    if (threadIdx.x == 0) blk[blockIdx.x] = tot;
 }
 
 // Exclusive scan of nblk block counts by one block; writes offsets and the
-// grand total at offs[nblk].
+// grand total at offs[nblk].  With out, the totals of the counts and of sums.
 __global__ void __launch_bounds__(256) k_scan_blocks(const uint32_t *__restrict__ blk, uint32_t nblk,
-                                                     uint32_t *__restrict__ offs) {
+                                                     uint32_t *__restrict__ offs,
+                                                     const unsigned long long *__restrict__ sums,
+                                                     CompactTotals *__restrict__ out) {
     __shared__ uint32_t lds[4];
+    __shared__ unsigned long long lds8[4];
     uint32_t carry = 0;
+    unsigned long long sum = 0;
     for (uint32_t b0 = 0; b0 < nblk; b0 += 256) {
         uint32_t i = b0 + threadIdx.x;
         uint32_t v = i < nblk ? blk[i] : 0;
+        if (out && i < nblk) sum += sums[i];
         uint32_t tot;
         uint32_t e = block_excl_scan_256(v, lds, &tot);
         if (i < nblk) offs[i] = carry + e;
         carry += tot;
     }
     if (threadIdx.x == 0) offs[nblk] = carry;
+    if (!out) return;
+    sum = block_sum_256(sum, lds8);
+    if (threadIdx.x == 0) *out = {sum, carry, 0};
 }
 
 // Writes the ID and count of every nonzero counter at its ascending rank r
 // (out_ids[r], out_vals[r], only for r < lim) and clears every nonzero
-// counter, whatever its rank.
+// counter, whatever its rank.  Without offs, a block sums the counts of the
+// blocks before it itself and the last one writes the totals: a launch less,
+// and at most four loads a thread while nblk <= kDirectBlocks.
+constexpr uint32_t kDirectBlocks = 1024;
 __global__ void __launch_bounds__(256) k_req_write(uint32_t *__restrict__ cnt, uint64_t n,
-                                                   const uint32_t *__restrict__ offs, VolGeo g,
+                                                   const uint32_t *__restrict__ offs,
+                                                   const uint32_t *__restrict__ blk,
+                                                   const unsigned long long *__restrict__ sums,
+                                                   CompactTotals *__restrict__ out, VolGeo g,
                                                    uint32_t *__restrict__ out_ids, uint32_t *__restrict__ out_vals,
                                                    uint32_t lim) {
     __shared__ uint32_t lds[4];
-    uint64_t base = (uint64_t)blockIdx.x * 1024 + threadIdx.x * 4;
-    uint32_t v[4], nz = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        uint64_t i = base + k;
-        v[k] = i < n ? cnt[i] : 0;
-        nz += v[k] != 0;
+    __shared__ unsigned long long lds8[4];
+    const uint64_t base = (uint64_t)blockIdx.x * 1024 + threadIdx.x * 4;
+    const uint4 q = load_four(cnt, base, n);
+    const uint32_t v[4] = {q.x, q.y, q.z, q.w};
+    const uint32_t nz = (v[0] != 0) + (v[1] != 0) + (v[2] != 0) + (v[3] != 0);
+    uint32_t before;
+    const bool last = !offs && blockIdx.x == gridDim.x - 1;
+    unsigned long long sum = 0;
+    if (offs) {
+        before = offs[blockIdx.x];
+    } else {
+        uint32_t a = 0;
+        for (uint32_t b = threadIdx.x; b < blockIdx.x; b += 256) a += blk[b];
+        before = (uint32_t)block_sum_256(a, lds8);
+        if (last) {
+            for (uint32_t b = threadIdx.x; b < gridDim.x; b += 256) sum += sums[b];
+            sum = block_sum_256(sum, lds8);
+        }
     }
     uint32_t tot;
-    uint32_t r = offs[blockIdx.x] + block_excl_scan_256(nz, lds, &tot);
+    uint32_t r = before + block_excl_scan_256(nz, lds, &tot);
+    if (last && threadIdx.x == 0) *out = {sum, before + tot, 0};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         if (v[k]) {
@@ -140,48 +185,54 @@ ro_status read_requests_device(ro_cache *c, uint32_t cap, uint32_t *ids, uint32_
     return compact_dense(c, c->b.counters, cap, ids, counts, n_unique, total, s);
 }
 
-// Work space of one compaction of n entries: nblk = ceil(n / 1024) block
-// counts, nblk + 1 offsets, the 64-bit sum, and lim output IDs and values.
-size_t compact_scratch_bytes(uint64_t n, uint32_t lim) {
+// Work space of one compaction of n entries: the totals, nblk = ceil(n /
+// 1024) block counts and nblk + 1 offsets, nblk 64-bit block sums, and lim
+// output IDs and values.
+static constexpr uint64_t up256(uint64_t v) { return (v + 255) / 256 * 256; }
+
+static constexpr uint64_t compact_bytes(uint64_t n, uint64_t lim) {
     const uint64_t nblk = (n + 1023) / 1024;
-    return 256 + (((2 * nblk + 1) * 4 + 255) / 256) * 256 + 2 * (((uint64_t)lim * 4 + 255) / 256) * 256;
+    return 256 + up256((2 * nblk + 1) * 4) + up256(nblk * 8) + 2 * up256(lim * 4);
 }
+
+size_t compact_scratch_bytes(uint64_t n, uint32_t lim) { return compact_bytes(n, lim); }
 
 // Compaction of the dense per-brick array arr (g.total entries) in the work
 // space ws (compact_scratch_bytes(g.total, lim) bytes, 256-byte aligned):
 // copies the first min(cap, lim) (ID, value) pairs in ascending ID order to
 // the host, with the distinct count and the sum, and clears the array.
-// Clears its counters with a fill kernel (no memset).  Synchronises.
+// Synchronises.
 ro_status compact_dense_ws(const VolGeo &g, uint32_t *arr, uint8_t *ws, uint32_t lim, uint32_t cap, uint32_t *ids,
                            uint32_t *counts, uint32_t *n_unique, uint64_t *total, hipStream_t s) {
     const uint32_t nblk = (uint32_t)((g.total + 1023) / 1024);
-    unsigned long long *tot = (unsigned long long *)ws;
+    CompactTotals *tot = (CompactTotals *)ws;
     uint32_t *blk = (uint32_t *)(ws + 256);
     uint32_t *offs = blk + nblk;
-    uint32_t *out_ids = (uint32_t *)(ws + 256 + (((2 * (uint64_t)nblk + 1) * 4 + 255) / 256) * 256);
-    uint32_t *out_vals = out_ids + (((uint64_t)lim * 4 + 255) / 256) * 64;
-    ro_status st = launch_fill_u32((uint32_t *)tot, 2, 0u, s);
-    if (st) return st;
-    hipLaunchKernelGGL(k_req_count, dim3(nblk), dim3(256), 0, s, arr, g.total, blk, tot);
+    unsigned long long *sums = (unsigned long long *)(ws + 256 + up256((2 * (uint64_t)nblk + 1) * 4));
+    uint32_t *out_ids = (uint32_t *)((uint8_t *)sums + up256((uint64_t)nblk * 8));
+    uint32_t *out_vals = out_ids + up256((uint64_t)lim * 4) / 4;
+    hipLaunchKernelGGL(k_req_count, dim3(nblk), dim3(256), 0, s, arr, g.total, blk, sums);
     RO_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(256), 0, s, blk, nblk, offs);
+    const bool direct = nblk <= kDirectBlocks;
+    if (!direct) {
+        hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(256), 0, s, blk, nblk, offs, sums, tot);
+        RO_HIP(hipGetLastError());
+    }
+    hipLaunchKernelGGL(k_req_write, dim3(nblk), dim3(256), 0, s, arr, g.total, direct ? nullptr : offs, blk, sums, tot,
+                       g, out_ids, out_vals, lim);
     RO_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_req_write, dim3(nblk), dim3(256), 0, s, arr, g.total, offs, g, out_ids, out_vals, lim);
-    RO_HIP(hipGetLastError());
-    uint32_t nu = 0;
-    unsigned long long t = 0;
-    RO_HIP(hipMemcpyAsync(&nu, offs + nblk, 4, hipMemcpyDeviceToHost, s));
-    RO_HIP(hipMemcpyAsync(&t, tot, 8, hipMemcpyDeviceToHost, s));
+    CompactTotals t;
+    RO_HIP(hipMemcpyAsync(&t, tot, sizeof(t), hipMemcpyDeviceToHost, s));
     RO_HIP(hipStreamSynchronize(s));
-    uint32_t k = nu < cap ? nu : cap;
+    uint32_t k = t.n < cap ? t.n : cap;
     k = k < lim ? k : lim;
     if (k) {
         RO_HIP(hipMemcpyAsync(ids, out_ids, 4 * (size_t)k, hipMemcpyDeviceToHost, s));
         RO_HIP(hipMemcpyAsync(counts, out_vals, 4 * (size_t)k, hipMemcpyDeviceToHost, s));
         RO_HIP(hipStreamSynchronize(s));
     }
-    *n_unique = nu;
-    *total = t;
+    *n_unique = t.n;
+    *total = t.sum;
     return RO_OK;
 }
 
@@ -201,8 +252,7 @@ ro_status compact_dense(ro_cache *c, uint32_t *arr, uint32_t cap, uint32_t *ids,
 // that GPU's copy, so calls that overlap on one GPU race.
 constexpr uint64_t kNoAllocMaxBricks = 1ull << 26;
 constexpr uint32_t kNoAllocMaxPairs = RO_NOALLOC_MAX_PAIRS;
-constexpr size_t kNoAllocBytes = 256 + (((2 * (kNoAllocMaxBricks / 1024) + 1) * 4 + 255) / 256) * 256 +
-                                 2 * (((size_t)kNoAllocMaxPairs * 4 + 255) / 256) * 256;
+constexpr size_t kNoAllocBytes = compact_bytes(kNoAllocMaxBricks, kNoAllocMaxPairs);
 
 }  // namespace ro
 
@@ -290,7 +340,8 @@ ro_status read_usage_device(ro_cache *c, uint32_t frame, uint32_t cap, uint32_t 
     uint32_t *out = (uint32_t *)(sc + c->sc.outpairs);
     hipLaunchKernelGGL(k_use_count, dim3(nblk), dim3(256), 0, s, c->b.stamps, c->b.slot_brick, S, frame, blk);
     RO_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(256), 0, s, blk, nblk, offs);
+    hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(256), 0, s, blk, nblk, offs,
+                       (const unsigned long long *)nullptr, (CompactTotals *)nullptr);
     RO_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_use_write, dim3(nblk), dim3(256), 0, s, c->b.stamps, c->b.slot_brick, S, frame,
                        offs, out);
