@@ -470,10 +470,11 @@ ro_status octree_update(ro_octree *tr, const std::vector<uint32_t> &dirty, hipSt
     const VolGeo &g = tr->cache->vol->g;
     const TreeGeo &t = tr->t;
     const int D = t.depth;
-    // runs first, then the bricks, in the tree's scratch
+    // runs first, then the bricks, in the tree's scratch (its last 256 bytes
+    // are the frame kernel's)
     constexpr size_t kRunBytes = 4096;
     constexpr size_t kRunsMax = kRunBytes / sizeof(LeafRun);  // as many channels x levels as a volume has
-    const size_t cap = (tr->scratch_bytes - kRunBytes) / sizeof(uint32_t);
+    const size_t cap = (tr->scratch_bytes - 256 - kRunBytes) / sizeof(uint32_t);
     std::vector<LeafRun> runs;
     runs.reserve(kRunsMax);
     std::vector<uint8_t> buf;
