@@ -43,17 +43,6 @@ namespace ro {
 // those (455 x 256, 16 channels: 10.0 ms -> 2.1; 512 x 512, 4 channels:
 // 5.0 -> 2.2; 64 x 64, one channel: 0.59 -> 0.18).
 
-// Per-XCD block queues: blocks are dealt to them in chunks of RO_CHUNK
-// consecutive blocks (16 chunks per queue at 1080p).  On the 16-channel
-// 1080p frame chunks of 256 measured 0.6 % faster than 64, 16 0.7 % slower,
-// 1024 as 256, and 4096 (one region per XCD) 4 % slower.
-#ifndef RO_QUEUES
-#define RO_QUEUES 8
-#endif
-#ifndef RO_CHUNK
-#define RO_CHUNK 256
-#endif
-
 // Persistent grid (one workgroup per CU) whose waves take units of pixels
 // from a device counter independently of each other, so a CU never waits
 // for the slowest wave of a workgroup before taking new work.
@@ -330,9 +319,7 @@ ro_status render_device(ro_octree *tr, const ro_frame_desc *fd, float *rgba, hip
     const uint32_t n_units = Q.n_blocks * (uint32_t)p;
     const uint32_t per_cu = (n_units + Q.grid.x - 1) / Q.grid.x;
     Q.n_waves = per_cu < kRenderLanes / 64 ? per_cu : kRenderLanes / 64;
-    uint32_t chunk = Q.n_blocks / (RO_QUEUES * 8);
-    chunk = chunk >= RO_CHUNK ? RO_CHUNK : chunk >= 16 ? chunk & ~15u : chunk ? chunk : 1;
-    Q.chunk = chunk * (uint32_t)p;
+    Q.chunk = queue_chunk(Q.n_blocks) * (uint32_t)p;
     static_assert(RO_QUEUES * kQueueStride * 4 <= 256, "queue counters exceed the scratch tail");
     st = launch_fill_u32(Q.counter, (uint64_t)RO_QUEUES * kQueueStride, 0u, s);
     if (st) return st;

@@ -268,6 +268,23 @@ struct RayLds {
 // while all of them still sweep the image together (the Infinity Cache is
 // shared).  Counter reads and the unit are wave-uniform.
 constexpr int kQueueStride = 8;  // words between queue counters (32 bytes)
+// Per-XCD block queues: blocks are dealt to them in chunks of RO_CHUNK
+// consecutive blocks (16 chunks per queue at 1080p).  On the 16-channel
+// 1080p frame chunks of 256 measured 0.6 % faster than 64, 16 0.7 % slower,
+// 1024 as 256, and 4096 (one region per XCD) 4 % slower.
+#ifndef RO_QUEUES
+#define RO_QUEUES 8
+#endif
+#ifndef RO_CHUNK
+#define RO_CHUNK 256
+#endif
+// Blocks per chunk of an image of n_blocks: smaller images in smaller chunks,
+// whole 32 x 32 tiles of them.
+__host__ __device__ inline uint32_t queue_chunk(uint32_t n_blocks) {
+    const uint32_t c = n_blocks / (RO_QUEUES * 8);
+    return c >= RO_CHUNK ? RO_CHUNK : c >= 16 ? c & ~15u : c ? c : 1;
+}
+
 template <int P>
 struct UnitQueue {
     uint32_t *counter;  // n_queues counters kQueueStride words apart, zero at launch (device or LDS)
@@ -277,10 +294,12 @@ struct UnitQueue {
     int W, H;
     bool exhausted;
     uint32_t q, tried;  // current queue, queues found used up (wave-uniform)
+    uint32_t taken;     // units handed out to this wave
 
     __device__ __forceinline__ void init() {
         q = blockIdx.x % n_queues;
         tried = 0;
+        taken = 0;
         exhausted = false;
     }
     __device__ __forceinline__ uint32_t pop() {
@@ -314,6 +333,7 @@ struct UnitQueue {
             exhausted = true;
             return false;
         }
+        ++taken;
         u += offset;
         const uint32_t b = u / P, t = b >> 4, i = (threadIdx.x & 63u) / P;
         x = (int)((t % tiles_x) * 32 + (b & 3u) * 8);

@@ -1,16 +1,16 @@
 // Multi-request rendering for the serving loop (an addition to the paper's
 // method): one persistent kernel renders a batch of frame requests of
 // different viewports, channel subsets and transfer functions over the
-// shared cache and octree.  Workgroups pop work items (up to 96 blocks of
-// 8 x 8 pixels of one request) from a device queue; when an item belongs to
-// another request than the previous one, the workgroup stages that
-// request's descriptor and tables in LDS.  Every pixel runs the same per-ray
-// code as the frame kernel, so a request's image does not depend on what
-// else is in the batch.
+// shared cache and octree.  A workgroup stages a request's descriptor and
+// tables in LDS; its waves then take the request's 4 x 4-pixel units from
+// device counters as the frame kernel's waves do, and when the request is
+// used up the workgroup goes on to the next one that is not.  Every pixel
+// runs the same per-ray code as the frame kernel, so a request's image does
+// not depend on what else is in the batch.
 //
-// The host prepares descriptors and the work list in pinned host memory owned
+// The host prepares the descriptors in pinned host memory owned
 // by the server.  There are two halves used alternately, each with its own
-// device copy, queue counter and stream, so a batch can be prepared while the
+// device copy, unit counters and stream, so a batch can be prepared while the
 // previous one renders and the tail of one batch overlaps the head of the
 // next.  A submission copies the prepared half to the device and launches the
 // kernel with arguments that depend only on the half; with the 16-channel
@@ -26,14 +26,13 @@ namespace ro {
 
 // Batch header (device copy of the prepared half).
 struct ServeHeader {
-    uint32_t n_tiles;
     uint32_t n_req;
     uint32_t seq;              // batch ticket (low 32 bits), posted per finished request
-    uint32_t pad0;
-    uint32_t *done;            // device [max_req] finished work items per request
+    uint32_t *done;            // device [max_req] finished units per request
     volatile uint32_t *flags;  // mapped host [max_req] completion tickets
-    uint32_t pad[56];
+    uint32_t pad[58];
 };
+static_assert(sizeof(ServeHeader) == 256, "batch header layout");
 
 // Work items of a W x H request: its 8 x 8 blocks (16 per 32 x 32 tile) in
 // groups of kSegBlocks.
@@ -44,6 +43,28 @@ __host__ __device__ inline uint32_t serve_segments(int W, int H) {
 
 
 constexpr int kServeP = 4;  // lanes per ray, as in the frame kernel
+
+// Renders the units that q hands out (its counters, range and chunk are set)
+// of the request staged in sA.
+template <int NV, int BPV, int EC>
+__device__ __forceinline__ void serve_units(const RenderArgs &sA, UnitQueue<kServeP> &q, const float4 *s_tf,
+                                            const ChanLds *s_ch, const ChanPar<NV> *s_par, const uint32_t *s_runs,
+                                            const LevLds *s_lv, const NodeLds *s_nd) {
+    q.tiles_x = ((uint32_t)sA.W + 31) / 32;
+    q.W = sA.W;
+    q.H = sA.H;
+    uint32_t st[7] = {0, 0, 0, 0, 0, 0, 0};
+    render_rays<NV, BPV, false, EC, 0, kServeP>(sA, q, s_tf, s_ch, s_par, s_runs, s_lv, s_nd, st);
+    if (sA.stats) {
+#pragma unroll
+        for (int j = 0; j < 7; ++j) {
+            uint32_t v = st[j];
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+            if ((threadIdx.x & 63) == 0 && v) atomicAdd(&sA.stats[j], (unsigned long long)v);
+        }
+    }
+}
 
 // Renders work item `seg` (kSegBlocks consecutive 8 x 8-pixel blocks, the
 // blocks of a 32 x 32 tile consecutive, tiles in raster order) of the
@@ -60,70 +81,69 @@ __device__ __forceinline__ void serve_item(const RenderArgs &sA, uint32_t seg, u
     q.counter = s_next;
     q.n_units = min(kSegBlocks, n_blk - first) * kServeP;
     q.offset = first * kServeP;
-    q.tiles_x = tiles_x;
     q.n_queues = 1;
     q.chunk = 1;
-    q.W = sA.W;
-    q.H = sA.H;
-    uint32_t st[7] = {0, 0, 0, 0, 0, 0, 0};
-    render_rays<NV, BPV, false, EC, 0, kServeP>(sA, q, s_tf, s_ch, s_par, s_runs, s_lv, s_nd, st);
-    if (sA.stats) {
-#pragma unroll
-        for (int j = 0; j < 7; ++j) {
-            uint32_t v = st[j];
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-            if ((threadIdx.x & 63) == 0 && v) atomicAdd(&sA.stats[j], (unsigned long long)v);
-        }
-    }
+    serve_units<NV, BPV, EC>(sA, q, s_tf, s_ch, s_par, s_runs, s_lv, s_nd);
 }
 
-// A workgroup takes a work item, stages the request's tables if it changed,
-// renders the item and waits for its slowest wave once per item.
+constexpr uint32_t kReqCounters = RO_QUEUES * kQueueStride;  // words of a request's unit counters
+
+// A workgroup goes through the batch's requests: it stages one that still has
+// units, and its waves take units until there are none.  Bound by the rays,
+// so by how long waves stand idle: work handed to whole workgroups (96 blocks
+// of 8 x 8 pixels an item, 425 items for twelve requests of 256^2 to 1137 x
+// 640) left the last items to a few of them (64 ms; now 50).  A change of
+// request waits for the slowest of the workgroup's waves; starts spread over
+// the requests in proportion to their pixels, so that most workgroups change
+// seldom, took as long, and finish the first requests last.
 template <int NV, int BPV, int EC>
 __global__ void __launch_bounds__(kRenderLanes) __attribute__((amdgpu_waves_per_eu(kRenderLanes / 256)))
-    k_serve(const ServeHeader *__restrict__ hdr, const RenderArgs *__restrict__ descs,
-            const uint32_t *__restrict__ segs, uint32_t *__restrict__ queue) {
-    extern __shared__ float4 s_tf[];  // [NV][kTfStride] tables, then [NV][kRenderLanes] slot words
+    k_serve(const ServeHeader *__restrict__ hdr, const RenderArgs *__restrict__ descs, uint32_t *counters,
+            uint32_t *used_up) {
+    extern __shared__ float4 s_tf[];  // tables, per-ray words, miss tables (render_lds_bytes)
     __shared__ RenderArgs sA;
     __shared__ ChanLds s_ch[NV];
     __shared__ ChanPar<NV> s_par;
     __shared__ uint32_t s_runs[NV * kMaxRuns];
     __shared__ LevLds s_lv[kMaxL];
     __shared__ NodeLds s_nd[kMaxD + 1];
-    __shared__ uint32_t s_seg, s_next;
-    const uint32_t n_segs = hdr->n_tiles;
-    int cur = -1;
-    for (;;) {
-        if (threadIdx.x == 0) {
-            s_seg = atomicAdd(queue, 1u);
-            s_next = 0;
-        }
+    __shared__ uint32_t s_skip[2], s_taken;
+    const uint32_t n_req = hdr->n_req;
+    const uint32_t lane = threadIdx.x & 63;
+    if (threadIdx.x == 0) s_taken = 0;
+    for (uint32_t req = 0; req < n_req; ++req) {
+        // set once a workgroup has found no more units: then nobody needs to
+        // look (two words in turn, so one barrier a round is enough)
+        if (threadIdx.x == 0)
+            s_skip[req & 1] = __hip_atomic_load(used_up + req, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
-        const uint32_t seg = s_seg;
-        if (seg >= n_segs) break;
-        const uint32_t sw = segs[seg];
-        const int req = (int)(sw >> 26);
-        if (req != cur) {
-            const uint32_t *src = (const uint32_t *)(descs + req);
-            uint32_t *dst = (uint32_t *)&sA;
-            for (unsigned i = threadIdx.x; i < sizeof(RenderArgs) / 4; i += blockDim.x) dst[i] = src[i];
-            __syncthreads();
-            stage_frame<NV>(sA, s_tf, s_ch, &s_par, s_runs, s_lv, s_nd);
-            cur = req;
-        }
-        serve_item<NV, BPV, EC>(sA, sw & 0x3FFFFFFu, &s_next, s_tf, s_ch, &s_par, s_runs, s_lv, s_nd);
-        __threadfence();  // this item's pixels are visible device-wide before it is counted
-        __syncthreads();  // sA, the LDS tables, s_seg and s_next are reused by the next segment
+        if (s_skip[req & 1]) continue;
+        const uint32_t *src = (const uint32_t *)(descs + req);
+        uint32_t *dst = (uint32_t *)&sA;
+        for (unsigned i = threadIdx.x; i < sizeof(RenderArgs) / 4; i += blockDim.x) dst[i] = src[i];
+        __syncthreads();
+        stage_frame<NV>(sA, s_tf, s_ch, &s_par, s_runs, s_lv, s_nd);
+        const uint32_t n_blk = (((uint32_t)sA.W + 31) / 32) * (((uint32_t)sA.H + 31) / 32) * 16;
+        UnitQueue<kServeP> q;
+        q.counter = counters + req * kReqCounters;
+        q.n_units = n_blk * kServeP;
+        q.offset = 0;
+        q.n_queues = RO_QUEUES;
+        q.chunk = queue_chunk(n_blk) * kServeP;
+        serve_units<NV, BPV, EC>(sA, q, s_tf, s_ch, &s_par, s_runs, s_lv, s_nd);
+        if (lane == 0 && q.taken) atomicAdd(&s_taken, q.taken);
+        __threadfence();  // this workgroup's pixels are visible device-wide before its units are counted
+        __syncthreads();  // sA and the LDS tables are reused by the next request
         if (threadIdx.x == 0) {
-            // the request's last work item posts its completion to the host:
-            // its pixels (and those of every other item, each fenced before
-            // its count) are written before the flag
-            const uint32_t c = atomicAdd(hdr->done + req, 1u) + 1u;
-            if (c == serve_segments(sA.W, sA.H)) {
+            __hip_atomic_store(used_up + req, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // the workgroup that brings the count to the request's units
+            // posts its completion to the host: its pixels (and the others',
+            // each fenced before their count) are written before the flag
+            if (s_taken && atomicAdd(hdr->done + req, s_taken) + s_taken == n_blk * kServeP) {
                 __threadfence_system();
                 hdr->flags[req] = hdr->seq;
             }
+            s_taken = 0;
         }
     }
 }
@@ -232,9 +252,10 @@ __global__ void k_zero(uint32_t *p, uint32_t n) {
     for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
 }
 
-__global__ void k_serve_reset(uint32_t *queue, uint32_t *done, uint32_t n) {
-    if (threadIdx.x == 0) *queue = 0;
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) done[i] = 0;
+__global__ void k_serve_reset(uint32_t *counters, uint32_t *used_up, uint32_t *done, uint32_t n) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n * kReqCounters) counters[i] = 0;
+    if (i < n) used_up[i] = done[i] = 0;
 }
 
 ro_status build_render_args(ro_octree *tr, const ro_frame_desc *fd, float *rgba, RenderArgs &A);
@@ -250,7 +271,7 @@ struct ro_server {
     uint8_t *host;        // pinned host memory: 2 halves
     uint32_t *flags;      // mapped pinned host memory: [2][max_req] completion tickets
     uint32_t *flags_dev;  // its device address
-    uint8_t *dev;         // caller-owned device buffer: 2 halves, 2 queue counters, [2][max_req] counts
+    uint8_t *dev;         // caller-owned device buffer: 2 halves, the words of each (see serve_used_up)
     size_t half;          // bytes per half
     int cur;              // half the next prepare writes
     int ready;            // half prepared and not yet submitted (-1: none)
@@ -288,8 +309,8 @@ extern "C" ro_status ro_serve_work_items(int32_t width, int32_t height, uint32_t
     return RO_OK;
 }
 
-static size_t serve_half_bytes(uint32_t max_req, uint32_t max_tiles) {
-    size_t b = sizeof(ServeHeader) + (size_t)max_req * sizeof(RenderArgs) + 4 * (size_t)max_tiles;
+static size_t serve_half_bytes(uint32_t max_req) {
+    size_t b = sizeof(ServeHeader) + (size_t)max_req * sizeof(RenderArgs);
     return (b + 4095) / 4096 * 4096;
 }
 
@@ -314,11 +335,17 @@ static inline uint32_t *ring_head(const ro_server *s) { return (uint32_t *)(s->d
 static inline uint32_t *ring_closed(const ro_server *s) { return (uint32_t *)(s->dev + 2 * s->half + 1028); }
 static inline uint32_t *ring_done(const ro_server *s) { return (uint32_t *)(s->dev + 2 * s->half + 1280); }
 
-static inline uint32_t *serve_queue(const ro_server *s, int h) {
+// requests of half h that have no units left (max_req <= 64 words)
+static inline uint32_t *serve_used_up(const ro_server *s, int h) {
     return (uint32_t *)(s->dev + 2 * s->half + 256 * (size_t)h);
 }
 
-// per-request finished work-item counts of half h (max_req <= 64 words)
+// per-request unit counters of half h
+static inline uint32_t *serve_counters(const ro_server *s, int h) {
+    return (uint32_t *)(s->dev + 2 * s->half + 1536) + (size_t)h * s->max_req * kReqCounters;
+}
+
+// per-request finished unit counts of half h (max_req <= 64 words)
 static inline uint32_t *serve_done(const ro_server *s, int h) {
     return (uint32_t *)(s->dev + 2 * s->half + 512 + 256 * (size_t)h);
 }
@@ -374,11 +401,11 @@ static void serve_launch_e(const ro_server *s, int h, hipStream_t st) {
     const uint8_t *d = s->dev + (size_t)h * s->half;
     const ServeHeader *dh = (const ServeHeader *)d;
     const RenderArgs *dd = (const RenderArgs *)(d + sizeof(ServeHeader));
-    const uint32_t *dt = (const uint32_t *)(d + sizeof(ServeHeader) + (size_t)s->max_req * sizeof(RenderArgs));
-    uint32_t *q = serve_queue(s, h);
-    hipLaunchKernelGGL(k_serve_reset, dim3(1), dim3(64), 0, st, q, serve_done(s, h), s->max_req);
-    hipLaunchKernelGGL((k_serve<NV, BPV, EC>), dim3(s->ncu), dim3(kRenderLanes), render_lds_bytes(NV, kServeP), st, dh, dd, dt,
-                       q);
+    uint32_t *c = serve_counters(s, h), *u = serve_used_up(s, h);
+    hipLaunchKernelGGL(k_serve_reset, dim3((s->max_req * kReqCounters + 255) / 256), dim3(256), 0, st, c, u,
+                       serve_done(s, h), s->max_req);
+    hipLaunchKernelGGL((k_serve<NV, BPV, EC>), dim3(s->ncu), dim3(kRenderLanes), render_lds_bytes(NV, kServeP), st, dh, dd,
+                       c, u);
 }
 
 // compile-time brick edge for 32^3 and 16^3 bricks (see the frame kernel)
@@ -406,7 +433,8 @@ static hipError_t serve_enqueue(const ro_server *s, int h, hipStream_t st) {
 
 extern "C" ro_status ro_serve_query(uint32_t max_requests, uint32_t max_tiles, size_t *device_bytes) {
     RO_CHECK(device_bytes, RO_E_ARG, "null argument");
-    *device_bytes = 2 * serve_half_bytes(max_requests, max_tiles) + 1536;
+    (void)max_tiles;  // the work items of continuous admission are in host memory
+    *device_bytes = 2 * serve_half_bytes(max_requests) + 1536 + 2 * 4 * (size_t)max_requests * kReqCounters;
     return RO_OK;
 }
 
@@ -441,7 +469,7 @@ extern "C" ro_status ro_serve_create(ro_octree *t, uint32_t max_requests, uint32
     s->tree = t;
     s->max_req = max_requests;
     s->max_tiles = max_tiles;
-    s->half = serve_half_bytes(max_requests, max_tiles);
+    s->half = serve_half_bytes(max_requests);
     s->dev = (uint8_t *)device_buf;
     s->ready = -1;
     s->nv[0] = s->nv[1] = 16;
@@ -550,22 +578,15 @@ extern "C" ro_status ro_serve_prepare(ro_server *s, uint32_t n, const ro_frame_d
     uint8_t *base = s->host + (size_t)h * s->half;
     ServeHeader *hh = (ServeHeader *)base;
     RenderArgs *hd = (RenderArgs *)(base + sizeof(ServeHeader));
-    uint32_t *ht = (uint32_t *)(base + sizeof(ServeHeader) + (size_t)s->max_req * sizeof(RenderArgs));
-    nt = 0;
     for (uint32_t r = 0; r < n; ++r) {
         RenderArgs A;
         ro_status st = build_render_args(s->tree, &fds[r], rgba[r], A);
         if (st) {
-            hh->n_tiles = 0;
+            hh->n_req = 0;
             return st;
         }
         memcpy(&hd[r], &A, sizeof(A));
-        // a request's segments are consecutive: a workgroup re-stages its
-        // LDS tables only when it crosses into the next request
-        const uint32_t ns = serve_segments(fds[r].width, fds[r].height);
-        for (uint32_t i = 0; i < ns; ++i) ht[nt++] = (r << 26) | i;
     }
-    hh->n_tiles = nt;
     hh->n_req = n;
     hh->seq = (uint32_t)s->next_ticket;  // the ticket the next submission assigns
     hh->done = serve_done(s, h);
