@@ -113,25 +113,29 @@ __global__ __launch_bounds__(256) void k_meta_parent(TreeGeo t, const uint16_t *
     if (*p != v) *p = v;
 }
 
-// Node i of level d, channel c: min of the children's mins, max of maxes.
-__device__ inline void meta_node(const TreeGeo &t, int d, uint64_t i, uint32_t *meta, int m, int c) {
+// Children of node i of level d in channel c, and their reduction: min of the
+// mins, max of the maxes.
+__device__ inline void meta_load(const TreeGeo &t, int d, uint64_t i, const uint32_t *meta, int m, int c,
+                                 uint32_t v[8]) {
     uint32_t x, y, z, c0[3], cn[3];
     node_coords(t, d, i, &x, &y, &z);
     child_range(t, d, x, y, z, c0, cn);
-    uint32_t mn = 0xFFFFu, mx = 0;
     const uint32_t n = cn[0] * cn[1] * cn[2], lx = cn[0] >> 1, ly = lx + (cn[1] >> 1);
-    uint32_t v[8];
 #pragma unroll
     for (uint32_t k = 0; k < 8; ++k)  // an axis of one child takes no bit of k
         v[k] = k < n ? meta[(uint64_t)node_index(t, d + 1, c0[0] + (k & (cn[0] - 1)),
                                                  c0[1] + ((k >> lx) & (cn[1] - 1)), c0[2] + (k >> ly)) * m + c]
                      : 0x0000FFFFu;
+}
+
+__device__ inline uint32_t meta_of(const uint32_t v[8]) {
+    uint32_t mn = 0xFFFFu, mx = 0;
 #pragma unroll
     for (uint32_t k = 0; k < 8; ++k) {
         mn = min(mn, v[k] & 0xFFFFu);
         mx = max(mx, v[k] >> 16);
     }
-    meta[((uint64_t)t.noff[d] + i) * m + c] = mn | (mx << 16);
+    return mn | (mx << 16);
 }
 
 // Parents of level d: 2^gl lanes per node over the channels from c_first of
@@ -140,17 +144,29 @@ __global__ __launch_bounds__(256) void k_meta_reduce(TreeGeo t, int d, uint32_t 
                                                      int c_first, uint32_t chans) {
     const uint64_t tid = (uint64_t)blockIdx.x * 256 + threadIdx.x, i = tid >> gl;
     const int c = c_first + (int)(tid & ((1u << gl) - 1));
-    if (i < level_nodes(t, d) && c < m && (chans >> c & 1u)) meta_node(t, d, i, meta, m, c);
+    if (i >= level_nodes(t, d) || c >= m || !(chans >> c & 1u)) return;
+    uint32_t v[8];
+    meta_load(t, d, i, meta, m, c, v);
+    meta[((uint64_t)t.noff[d] + i) * m + c] = meta_of(v);
 }
 
-// Levels d, d - 1, .. 0 by one block.
+// Levels d, d - 1, .. 0 by one block.  A level is one round trip to memory
+// for every four nodes of a lane, whose loads are all issued first.
 __global__ __launch_bounds__(1024) void k_meta_top(TreeGeo t, int d, uint32_t *meta, int m, int gl, int c_first,
                                                    uint32_t chans) {
+    const int c = c_first + (int)(threadIdx.x & ((1u << gl) - 1));
+    const bool on = c < m && (chans >> c & 1u);
+    const uint32_t step = 1024u >> gl;  // nodes a round
     for (; d >= 0; --d) {
-        const uint32_t n = (uint32_t)level_nodes(t, d) << gl;
-        for (uint32_t k = threadIdx.x; k < n; k += 1024) {
-            const int c = c_first + (int)(k & ((1u << gl) - 1));
-            if (c < m && (chans >> c & 1u)) meta_node(t, d, k >> gl, meta, m, c);
+        const uint32_t n = (uint32_t)level_nodes(t, d);
+        for (uint32_t i0 = threadIdx.x >> gl; i0 < n; i0 += 4 * step) {
+            uint32_t v[4][8];
+#pragma unroll
+            for (uint32_t r = 0; r < 4; ++r)
+                if (on && i0 + r * step < n) meta_load(t, d, i0 + r * step, meta, m, c, v[r]);
+#pragma unroll
+            for (uint32_t r = 0; r < 4; ++r)
+                if (on && i0 + r * step < n) meta[((uint64_t)t.noff[d] + i0 + r * step) * m + c] = meta_of(v[r]);
         }
         __syncthreads();
     }
@@ -362,32 +378,26 @@ __global__ __launch_bounds__(256) void k_res_leaf(VolGeo g, TreeGeo t, const Lea
     }
 }
 
-// Residency masks of node i of level d and channel c: the OR of the
-// children.  Returns whether it changed.
-__device__ inline bool res_node(const TreeGeo &t, int d, uint32_t i, uint32_t c, int m, uint16_t *mask) {
+// Residency masks of the children of node i of level d in channel c.
+__device__ inline void res_load(const TreeGeo &t, int d, uint32_t i, uint32_t c, int m, const uint16_t *mask,
+                                uint32_t v[8]) {
     uint32_t x, y, z, c0[3], cn[3];
     node_coords(t, d, i, &x, &y, &z);
     child_range(t, d, x, y, z, c0, cn);
     const uint32_t n = cn[0] * cn[1] * cn[2], lx = cn[0] >> 1, ly = lx + (cn[1] >> 1);
-    uint32_t v[8], o = 0;
 #pragma unroll
     for (uint32_t k = 0; k < 8; ++k)  // an axis of one child takes no bit of k
         v[k] = k < n ? (uint32_t)mask[(uint64_t)node_index(t, d + 1, c0[0] + (k & (cn[0] - 1)),
                                                            c0[1] + ((k >> lx) & (cn[1] - 1)), c0[2] + (k >> ly)) *
                                           m + c]
                      : 0u;
-#pragma unroll
-    for (uint32_t k = 0; k < 8; ++k) o |= v[k];
-    uint16_t *p = mask + ((uint64_t)t.noff[d] + i) * m + c;
-    const bool changed = *p != (uint16_t)o;
-    if (changed) *p = (uint16_t)o;
-    return changed;
 }
 
 // The wave's nodes of level d from i0 on, kResRounds at a time per group of
 // 2^gl lanes (a lane per channel): flagged nodes get the OR of their
 // children; a change flags the parent.  A lane per node reads the flags, so
-// that a stretch without flags costs one load.
+// that a stretch without flags costs one load, and the rounds' loads are all
+// issued before the first is used.
 constexpr uint32_t kResRounds = 4;
 __device__ inline void res_wave(const TreeGeo &t, int d, uint32_t i0, int m, int gl, uint16_t *mask, uint8_t *flags,
                                 bool all) {
@@ -399,11 +409,27 @@ __device__ inline void res_wave(const TreeGeo &t, int d, uint32_t i0, int m, int
     }
     const unsigned long long want = __ballot(mine);
     const uint32_t c = lane & ((1u << gl) - 1), sub = lane >> gl;
+    if (want == 0) return;
+    uint32_t v[kResRounds][8], own[kResRounds];
+    bool on[kResRounds];
+#pragma unroll
     for (uint32_t r = 0; r < kResRounds; ++r) {
         const uint32_t k = r * per + sub;
-        if (k >= 64 || !(want >> k & 1) || c >= (uint32_t)m) continue;
-        const uint32_t i = i0 + k;
-        if (res_node(t, d, i, c, m, mask) && d > 0 && !all) {
+        on[r] = k < 64 && (want >> (k & 63) & 1) && c < (uint32_t)m;
+        if (!on[r]) continue;
+        res_load(t, d, i0 + k, c, m, mask, v[r]);
+        own[r] = mask[((uint64_t)t.noff[d] + i0 + k) * m + c];
+    }
+#pragma unroll
+    for (uint32_t r = 0; r < kResRounds; ++r) {
+        if (!on[r]) continue;
+        uint32_t o = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < 8; ++k) o |= v[r][k];
+        if (o == own[r]) continue;
+        const uint32_t i = i0 + r * per + sub;
+        mask[((uint64_t)t.noff[d] + i) * m + c] = (uint16_t)o;
+        if (d > 0 && !all) {
             uint32_t x, y, z;
             node_coords(t, d, i, &x, &y, &z);
             flags[parent_of(t, d, x, y, z)] = 1;
