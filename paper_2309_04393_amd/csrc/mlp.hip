@@ -45,6 +45,25 @@ constexpr int kWaves = 4;          // waves per workgroup
 constexpr int kPartials = 256;     // most workgroups of the gradient kernel: one partial each, one per CU
 constexpr int kStat = 4;           // per-partial scalars: loss sum, mask count
 
+// A partial holds the weight gradients as fragments (D layout, four values of
+// a lane together: 8 of W1, 16 of W2, 4 of W3), then the biases and the
+// scalars, so that a wave stores and sums 16 bytes a lane.
+constexpr int kFrag1 = 0, kFrag2 = 8, kFrag3 = 24, kFrags = 28;
+constexpr int kPartB1 = kFrags * 256, kPartB2 = kPartB1 + 64, kPartB3 = kPartB2 + 64, kPartStat = kPartB3 + 16,
+              kPartLen = kPartStat + kStat;
+static_assert(kPartLen == kNP + kStat && kPartLen % 4 == 0, "partial length");
+
+// Parameter at position k of a partial (k < kPartStat).
+__device__ __forceinline__ int param_of(int k) {
+    if (k >= kPartB3) return kB3 + k - kPartB3;
+    if (k >= kPartB2) return kB2 + k - kPartB2;
+    if (k >= kPartB1) return kB1 + k - kPartB1;
+    const int f = k >> 8, lane = k >> 2 & 63, r = lane & 15, row = 4 * (lane >> 4) + (k & 3);
+    if (f >= kFrag3) return kW3 + (16 * (f - kFrag3) + row) * 16 + r;
+    const int g = f >= kFrag2 ? f - kFrag2 : f;
+    return (f >= kFrag2 ? kW2 : kW1) + (16 * (g >> 2) + row) * 64 + 16 * (g & 3) + r;
+}
+
 __device__ __forceinline__ f4_t mfma16(half4_t a, half4_t b, f4_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x16f16(a, b, c, 0, 0, 0);
 }
@@ -159,19 +178,65 @@ __global__ void __launch_bounds__(256) k_mlp_fwd(const _Float16 *__restrict__ x,
     }
 }
 
-// Gradient partials, one per block: kNP + kStat floats to part[block].
-// 32768 rows: 80 us with 256 waves on 64 CUs and the tiles in LDS, 24 us with
-// two tiles on each of 1024 waves.  A wave holds the weights, the sums and a
-// tile in 426 registers, so a SIMD has one wave and what bounds it is that
-// wave's own chain: half issue (4000 instructions), half waits.
-constexpr int kPartLen = kNP + kStat;
+// Inputs of one tile: A of x and of x^T, labels and masks in both orders,
+// [row 4 q + i][r] and [row r][4 q + i]; zero past the end.
+struct Tile {
+    half4_t xa[2], xt[2];
+    uint8_t y[4], m[4];
+    uint32_t yt, mt;  // four bytes
+};
+
+__device__ __forceinline__ float byte_of(uint32_t v, int i) { return (float)(v >> (8 * i) & 255u); }
+
+// kWide: x is 8-byte aligned, y and msk are 4-byte aligned.
 template <bool kWide>
+__device__ __forceinline__ void load_tile(const _Float16 *__restrict__ x, const uint8_t *__restrict__ y,
+                                          const uint8_t *__restrict__ msk, uint32_t rows, uint32_t r0, Tile &T) {
+    const int r = threadIdx.x & 15, q = (threadIdx.x & 63) >> 4;
+    load_x<kWide>(x, rows, r0, T.xa);
+    T.yt = T.mt = 0;
+    if (r0 + r < rows) {
+        const size_t at = (size_t)(r0 + r) * 16 + 4 * q;
+        if (kWide) {
+            T.yt = *(const uint32_t *)(y + at);
+            T.mt = *(const uint32_t *)(msk + at);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                T.yt |= (uint32_t)y[at + i] << (8 * i);
+                T.mt |= (uint32_t)msk[at + i] << (8 * i);
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t row = r0 + 4 * q + i;
+        T.y[i] = T.m[i] = 0;
+        T.xt[0][i] = T.xt[1][i] = (_Float16)0.0f;
+        if (row >= rows) continue;
+        T.y[i] = y[(size_t)row * 16 + r];
+        T.m[i] = msk[(size_t)row * 16 + r];
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) T.xt[mt][i] = x[(size_t)row * 32 + 16 * mt + r];
+    }
+}
+
+// Gradient partials, one per block: kPartLen floats to part[block].
+// 32768 rows: 80 us with 256 waves on 64 CUs and the tiles in LDS, 18.6 us with
+// two tiles on each of 1024 waves.  A wave holds the weights, the sums and a
+// tile in 446 registers, so a SIMD has one wave and what bounds it is that
+// wave's own chain: 2.5 us a tile, the rest loading weights and summing.
+template <bool kWide, bool kLoss>
 __global__ void __launch_bounds__(256, 1) k_mlp_grad(const _Float16 *__restrict__ x, const uint8_t *__restrict__ y,
                                                      const uint8_t *__restrict__ msk, uint32_t rows,
                                                      const _Float16 *__restrict__ wh, const float *__restrict__ p,
                                                      float *__restrict__ part) {
-    __shared__ float S[2][kPartLen];
+    __shared__ f4_t S[2][kPartLen / 4];
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
+    const uint32_t ntiles = (rows + 15) / 16;
+    uint32_t t = blockIdx.x * kWaves + wv;
+    Tile cur;  // the next tile's inputs are on their way while one is worked on
+    if (t < ntiles) load_tile<kWide>(x, y, msk, rows, t * 16, cur);
     const Weights W(wh);
     // W2^T and W3^T as B fragments: rows of the matrices
     half4_t w2t[4][4], w3t[4];
@@ -204,43 +269,27 @@ __global__ void __launch_bounds__(256, 1) k_mlp_grad(const _Float16 *__restrict_
         }
     }
     const f4_t zero = {0, 0, 0, 0};
-    const uint32_t ntiles = (rows + 15) / 16;
-    for (uint32_t t = blockIdx.x * kWaves + wv; t < ntiles; t += gridDim.x * kWaves) {
+    for (; t < ntiles; t += gridDim.x * kWaves) {
         const uint32_t r0 = t * 16;
-        half4_t xa[2], xt[2];  // A of x, A of x^T
-        load_x<kWide>(x, rows, r0, xa);
-        // labels and masks in both orders: [row 4 q + i][r], [row r][4 q + i]
-        float mk[4], yy[4], mkt[4], yyt[4];
+        const Tile T = cur;
+        if (t + gridDim.x * kWaves < ntiles) load_tile<kWide>(x, y, msk, rows, (t + gridDim.x * kWaves) * 16, cur);
         const bool in_r = r0 + r < rows;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const bool in = r0 + 4 * q + i < rows;
-            const size_t at = (size_t)(r0 + 4 * q + i) * 16 + r, att = (size_t)(r0 + r) * 16 + 4 * q + i;
-            mk[i] = in ? (float)msk[at] : 0.0f;
-            yy[i] = in ? (float)y[at] : 0.0f;
-            mkt[i] = in_r ? (float)msk[att] : 0.0f;
-            yyt[i] = in_r ? (float)y[att] : 0.0f;
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt)
-                xt[mt][i] = in ? x[(size_t)(r0 + 4 * q + i) * 32 + 16 * mt + r] : (_Float16)0.0f;
-        }
         // forward: rows x units (h, for the weight gradients) and units x rows
         // (ht, the next layer's operand); bit 4 j + i of on*: the unit is on
         f4_t z = zero, zt = zero;
         half4_t h1[4], h1t[4], h2[4], h2t[4];
-        uint32_t on1 = 0, on2 = 0, on2t = 0;
+        f4_t s1[4], s2[4], s2t[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             f4_t a = zero, at = zero;
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
-                a = mfma16(xa[ks], W.w1[ks][j], a);
-                at = mfma16(W.w1[ks][j], xa[ks], at);
+                a = mfma16(T.xa[ks], W.w1[ks][j], a);
+                at = mfma16(W.w1[ks][j], T.xa[ks], at);
             }
             a += b1[j];
             at += b1t[j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) on1 |= (a[i] > 0.0f ? 1u : 0u) << (4 * j + i);
+            s1[j] = a;
             h1[j] = to_half(relu(a));
             h1t[j] = to_half(relu(at));
         }
@@ -254,11 +303,8 @@ __global__ void __launch_bounds__(256, 1) k_mlp_grad(const _Float16 *__restrict_
             }
             a += b2[j];
             at += b2t[j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                on2 |= (a[i] > 0.0f ? 1u : 0u) << (4 * j + i);
-                on2t |= (at[i] > 0.0f ? 1u : 0u) << (4 * j + i);
-            }
+            s2[j] = a;
+            s2t[j] = at;
             h2[j] = to_half(relu(a));
             h2t[j] = to_half(relu(at));
         }
@@ -275,14 +321,14 @@ __global__ void __launch_bounds__(256, 1) k_mlp_grad(const _Float16 *__restrict_
         for (int i = 0; i < 4; ++i) {
             float d = 0.0f, dt = 0.0f;
             if (r0 + 4 * q + i < rows) {
-                const float zz = z[i];
+                const float zz = z[i], mk = (float)T.m[i], yy = (float)T.y[i];
                 const float s = 1.0f / (1.0f + expf(-zz));
-                d = mk[i] * (s - yy[i]);
+                d = mk * (s - yy);
                 // softplus(z) - y z, stably
-                lsum += mk[i] * (fmaxf(zz, 0.0f) + log1pf(expf(-fabsf(zz))) - yy[i] * zz);
-                msum += mk[i];
+                if (kLoss) lsum += mk * (fmaxf(zz, 0.0f) + log1pf(expf(-fabsf(zz))) - yy * zz);
+                msum += mk;
             }
-            if (in_r) dt = mkt[i] * (1.0f / (1.0f + expf(-zt[i])) - yyt[i]);
+            if (in_r) dt = byte_of(T.mt, i) * (1.0f / (1.0f + expf(-zt[i])) - byte_of(T.yt, i));
             dzf[i] = d;
             dzft[i] = dt;
             gb3 += d;
@@ -296,8 +342,8 @@ __global__ void __launch_bounds__(256, 1) k_mlp_grad(const _Float16 *__restrict_
             f4_t a = mfma16(dzt, w3t[j], zero), at = mfma16(w3t[j], dzt, zero);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                a[i] = on2 >> (4 * j + i) & 1u ? a[i] : 0.0f;
-                at[i] = on2t >> (4 * j + i) & 1u ? at[i] : 0.0f;
+                a[i] = s2[j][i] > 0.0f ? a[i] : 0.0f;
+                at[i] = s2t[j][i] > 0.0f ? at[i] : 0.0f;
                 gb2[j] += a[i];
             }
             d2[j] = to_half(a);
@@ -315,7 +361,7 @@ __global__ void __launch_bounds__(256, 1) k_mlp_grad(const _Float16 *__restrict_
             for (int ks = 0; ks < 4; ++ks) a = mfma16(d2t[ks], w2t[ks][j], a);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                a[i] = on1 >> (4 * j + i) & 1u ? a[i] : 0.0f;
+                a[i] = s1[j][i] > 0.0f ? a[i] : 0.0f;
                 gb1[j] += a[i];
             }
             d1[j] = to_half(a);
@@ -324,7 +370,7 @@ __global__ void __launch_bounds__(256, 1) k_mlp_grad(const _Float16 *__restrict_
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-            for (int nt = 0; nt < 4; ++nt) g1[mt][nt] = mfma16(xt[mt], d1[nt], g1[mt][nt]);
+            for (int nt = 0; nt < 4; ++nt) g1[mt][nt] = mfma16(T.xt[mt], d1[nt], g1[mt][nt]);
     }
     // bias partials: sum the four lane groups (q) of each column
 #pragma unroll
@@ -341,36 +387,38 @@ __global__ void __launch_bounds__(256, 1) k_mlp_grad(const _Float16 *__restrict_
         lsum += __shfl_xor(lsum, off, 64);
         msum += __shfl_xor(msum, off, 64);
     }
-    // (wave 0 + wave 2) + (wave 1 + wave 3), in parameter layout
-    float *o = S[wv & 1];
+    // (wave 0 + wave 2) + (wave 1 + wave 3)
+    f4_t *o = S[wv & 1];
+    float *ob = (float *)o;
+#pragma unroll
     for (int turn = 0; turn < 2; ++turn) {
         if (wv >> 1 == turn) {
-            auto put = [&](int k, float v) { o[k] = turn ? o[k] + v : v; };
+            auto put = [&](int f, f4_t v) { o[f * 64 + lane] = turn ? o[f * 64 + lane] + v : v; };
+            auto put1 = [&](int k, float v) { ob[k] = turn ? ob[k] + v : v; };
 #pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
+            for (int mt = 0; mt < 4; ++mt) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int row = 16 * mt + 4 * q + i;
-#pragma unroll
-                    for (int nt = 0; nt < 4; ++nt) {
-                        if (mt < 2) put(kW1 + row * 64 + 16 * nt + r, g1[mt & 1][nt][i]);
-                        put(kW2 + row * 64 + 16 * nt + r, g2[mt][nt][i]);
-                    }
-                    put(kW3 + row * 16 + r, g3[mt][i]);
+                for (int nt = 0; nt < 4; ++nt) {
+                    if (mt < 2) put(kFrag1 + 4 * mt + nt, g1[mt & 1][nt]);
+                    put(kFrag2 + 4 * mt + nt, g2[mt][nt]);
                 }
+                put(kFrag3 + mt, g3[mt]);
+            }
             if (q == 0) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    put(kB1 + 16 * j + r, gb1[j]);
-                    put(kB2 + 16 * j + r, gb2[j]);
+                    put1(kPartB1 + 16 * j + r, gb1[j]);
+                    put1(kPartB2 + 16 * j + r, gb2[j]);
                 }
-                put(kB3 + r, gb3);
+                put1(kPartB3 + r, gb3);
             }
-            if (lane < kStat) put(kNP + lane, lane == 0 ? lsum : lane == 1 ? msum : 0.0f);
+            if (lane < kStat) put1(kPartStat + lane, lane == 0 ? lsum : lane == 1 ? msum : 0.0f);
         }
         __syncthreads();
     }
-    for (int k = threadIdx.x; k < kPartLen; k += 256) part[(size_t)blockIdx.x * kPartLen + k] = S[0][k] + S[1][k];
+    f4_t *to = (f4_t *)(part + (size_t)blockIdx.x * kPartLen);
+#pragma unroll 4
+    for (int k = threadIdx.x; k < kPartLen / 4; k += 256) to[k] = S[0][k] + S[1][k];
 }
 
 struct AdamStep {
@@ -380,7 +428,7 @@ struct AdamStep {
 // Sum of the partials in a fixed order (deterministic), the mean over the
 // unmasked entries, and, with kStep, the Adam step on the FP32 master weights
 // with their FP16 copies: one launch, where a sum, a scaling and a step were
-// three.  A block takes 64 parameters; each of its 16 waves sums every 16th
+// three.  A block takes 64 positions of the partials; each of its 16 waves sums every 16th
 // partial of them (coalesced rows, independent loads), then a pairwise tree
 // over the 16 wave sums in LDS.  The count of unmasked entries is summed by
 // every block for itself, in the same order.
@@ -396,7 +444,7 @@ __global__ void __launch_bounds__(64 * kRedGroups) k_mlp_update(const float *__r
     const int k = blockIdx.x * 64 + lane;
     // partial 16 lane + gi is lane's: 256 at most, so one a lane is enough
     static_assert(kPartials <= 64 * kRedGroups, "one count per thread");
-    float n = lane * kRedGroups + gi < nparts ? part[(size_t)(lane * kRedGroups + gi) * kPartLen + kNP + 1] : 0.0f;
+    float n = lane * kRedGroups + gi < nparts ? part[(size_t)(lane * kRedGroups + gi) * kPartLen + kPartStat + 1] : 0.0f;
     float acc = 0.0f;
     if (k < kPartLen) {
 #pragma unroll 4
@@ -415,20 +463,21 @@ __global__ void __launch_bounds__(64 * kRedGroups) k_mlp_update(const float *__r
         __syncthreads();
     }
     if (gi != 0 || k >= kPartLen) return;
-    if (k >= kNP) {
-        stat[k - kNP] = sm[0][lane];
+    if (k >= kPartStat) {
+        stat[k - kPartStat] = sm[0][lane];
         return;
     }
+    const int e = param_of(k);
     const float gk = sm[0][lane] / fmaxf(cnt[0], 1.0f);
-    grad[k] = gk;
+    grad[e] = gk;
     if (!kStep) return;
-    const float mk = st.b1 * m[k] + (1.0f - st.b1) * gk;
-    const float vk = st.b2 * v[k] + (1.0f - st.b2) * gk * gk;
-    m[k] = mk;
-    v[k] = vk;
-    const float w = p[k] - st.lr * (mk / st.c1) / (sqrtf(vk / st.c2) + st.eps);
-    p[k] = w;
-    put_half(wh, k, w);
+    const float mk = st.b1 * m[e] + (1.0f - st.b1) * gk;
+    const float vk = st.b2 * v[e] + (1.0f - st.b2) * gk * gk;
+    m[e] = mk;
+    v[e] = vk;
+    const float w = p[e] - st.lr * (mk / st.c1) / (sqrtf(vk / st.c2) + st.eps);
+    p[e] = w;
+    put_half(wh, e, w);
 }
 
 __global__ void k_mlp_refresh(const float *__restrict__ p, _Float16 *__restrict__ wh) {
@@ -546,19 +595,19 @@ extern "C" ro_status ro_mlp_forward(ro_mlp *n, const uint16_t *x, uint32_t rows,
     return RO_OK;
 }
 
-// Gradients of the rows and, with a step, the weights' update.
+// Gradients of the rows and, with a step, the weights' update; the loss where
+// it is asked for (its logarithm is a tenth of the kernel's instructions).
 static ro_status mlp_grad(ro_mlp *n, const uint16_t *x, const uint8_t *y, const uint8_t *mask, uint32_t rows,
-                          const AdamStep *step, hipStream_t s) {
+                          const AdamStep *step, bool loss, hipStream_t s) {
     const uint32_t tiles = (rows + 15) / 16;
     uint32_t blocks = (tiles + kWaves - 1) / kWaves;
     if (blocks > (uint32_t)kPartials) blocks = kPartials;
     if (blocks < 1) blocks = 1;  // no rows: zero gradients
-    if ((uintptr_t)x % 8 == 0)
-        hipLaunchKernelGGL(k_mlp_grad<true>, dim3(blocks), dim3(64 * kWaves), 0, s, (const _Float16 *)x, y, mask, rows,
-                           n->wh, n->p, n->part);
-    else
-        hipLaunchKernelGGL(k_mlp_grad<false>, dim3(blocks), dim3(64 * kWaves), 0, s, (const _Float16 *)x, y, mask, rows,
-                           n->wh, n->p, n->part);
+    const bool wide = (uintptr_t)x % 8 == 0 && (uintptr_t)y % 4 == 0 && (uintptr_t)mask % 4 == 0;
+    auto grad = wide ? (loss ? k_mlp_grad<true, true> : k_mlp_grad<true, false>)
+                     : (loss ? k_mlp_grad<false, true> : k_mlp_grad<false, false>);
+    hipLaunchKernelGGL(grad, dim3(blocks), dim3(64 * kWaves), 0, s, (const _Float16 *)x, y, mask, rows, n->wh, n->p,
+                       n->part);
     RO_HIP(hipGetLastError());
     const dim3 grid((kPartLen + 63) / 64), block(64 * kRedGroups);
     if (step)
@@ -575,7 +624,7 @@ extern "C" ro_status ro_mlp_gradients(ro_mlp *n, const uint16_t *x, const uint8_
                                       uint32_t rows, float *grads_host, float *loss_host, void *stream) {
     RO_CHECK(n && x && y && mask && grads_host, RO_E_ARG, "null argument");
     hipStream_t s = (hipStream_t)stream;
-    ro_status st = mlp_grad(n, x, y, mask, rows, nullptr, s);
+    ro_status st = mlp_grad(n, x, y, mask, rows, nullptr, loss_host != nullptr, s);
     if (st) return st;
     std::vector<float> g(kNP + kStat);
     RO_HIP(hipMemcpyAsync(g.data(), n->g, sizeof(float) * (kNP + kStat), hipMemcpyDeviceToHost, s));
@@ -602,7 +651,7 @@ extern "C" ro_status ro_mlp_train_step(ro_mlp *n, const uint16_t *x, const uint8
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
     const float t = (float)(n->step + 1);
     const AdamStep step = {lr, b1, b2, eps, 1.0f - powf(b1, t), 1.0f - powf(b2, t)};
-    ro_status st = mlp_grad(n, x, y, mask, rows, &step, s);
+    ro_status st = mlp_grad(n, x, y, mask, rows, &step, loss_host != nullptr, s);
     if (st) return st;
     n->step += 1;
     if (loss_host) {
