@@ -291,6 +291,7 @@ struct UnitQueue {
     uint32_t n_units;   // units this queue hands out: offset .. offset + n_units - 1
     uint32_t offset, tiles_x;
     uint32_t n_queues, chunk;
+    uint32_t split;     // log2 of the parts that a unit's pixels are handed out in (P = 4 only)
     int W, H;
     bool exhausted;
     uint32_t q, tried;  // current queue, queues found used up (wave-uniform)
@@ -335,7 +336,9 @@ struct UnitQueue {
         }
         ++taken;
         u += offset;
-        const uint32_t b = u / P, t = b >> 4, i = (threadIdx.x & 63u) / P;
+        const uint32_t i = (threadIdx.x & 63u) / P, part = u & ((1u << split) - 1);
+        u >>= split;
+        const uint32_t b = u / P, t = b >> 4;
         x = (int)((t % tiles_x) * 32 + (b & 3u) * 8);
         y = (int)((t / tiles_x) * 32 + ((b >> 2) & 3u) * 8);
         if (P == 4) {
@@ -348,7 +351,7 @@ struct UnitQueue {
             x += (int)(i & 7u);
             y += (int)(i >> 3);
         }
-        v = x < W && y < H;
+        v = x < W && y < H && (P != 4 || (i >> (4 - split)) == part);
         return true;
     }
 };

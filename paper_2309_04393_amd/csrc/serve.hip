@@ -51,6 +51,7 @@ __device__ __forceinline__ void serve_units(const RenderArgs &sA, UnitQueue<kSer
                                             const ChanLds *s_ch, const ChanPar<NV> *s_par, const uint32_t *s_runs,
                                             const LevLds *s_lv, const NodeLds *s_nd) {
     q.tiles_x = ((uint32_t)sA.W + 31) / 32;
+    q.split = 0;
     q.W = sA.W;
     q.H = sA.H;
     uint32_t st[7] = {0, 0, 0, 0, 0, 0, 0};
