@@ -98,7 +98,7 @@ struct ro_volume {
 namespace ro {
 // LRU select: bins of its histograms, words of its state before the victims,
 // and the candidates that it may rank beyond those asked for.
-constexpr uint32_t kSelHistWords = 3 * 2048, kSelStateWords = 32, kSelSlack = 4096;
+constexpr uint32_t kSelHistWords = 3 * 2048, kSelStateWords = 128, kSelSlack = 4096;
 }  // namespace ro
 
 // Scratch layout of a cache (byte offsets into bufs.scratch).

@@ -27,16 +27,37 @@ __device__ inline void node_coords(const TreeGeo &t, int d, uint64_t i, uint32_t
     *z = (uint32_t)(i >> (t.nlog[d][0] + t.nlog[d][1]));
 }
 
+// Children of node i of level d in an array of their level, 2^gl entries per
+// node, this lane's the `lane`-th; `none` past the last child.  An axis of one
+// child takes no bit of k.
+template <typename T>
+__device__ inline void lds_children(const TreeGeo &t, int d, uint32_t i, int gl, uint32_t lane, const T *lv,
+                                    uint32_t none, uint32_t v[8]) {
+    uint32_t x, y, z, c0[3], cn[3];
+    node_coords(t, d, i, &x, &y, &z);
+    child_range(t, d, x, y, z, c0, cn);
+    const uint32_t n = cn[0] * cn[1] * cn[2], lx = cn[0] >> 1, ly = lx + (cn[1] >> 1);
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k)
+        v[k] = k < n ? (uint32_t)lv[((node_index(t, d + 1, c0[0] + (k & (cn[0] - 1)),
+                                                 c0[1] + ((k >> lx) & (cn[1] - 1)), c0[2] + (k >> ly)) -
+                                      t.noff[d + 1])
+                                     << gl) +
+                                    lane]
+                     : none;
+}
+
 static __host__ __device__ inline uint64_t level_nodes(const TreeGeo &t, int d) {
     return 1ull << (t.nlog[d][0] + t.nlog[d][1] + t.nlog[d][2]);
 }
 
 static inline unsigned nblocks(uint64_t n) { return (unsigned)((n + 255) / 256); }
 
-// Nodes of the levels that one block takes through together, top levels
-// first to last in one launch: a level of 512 nodes is 8 rounds of 1024
-// lanes at 16 channels, about what a launch of its own costs.
-constexpr uint64_t kTopNodes = 512;
+// Nodes of the deepest level that one block takes through to the root in one
+// launch, the levels above it from LDS (a round trip to memory per level took
+// 14 us for the residency masks, as long as the launches it replaced).  A
+// level of 512 nodes is two turns of 1024 lanes at 16 channels.
+constexpr uint32_t kTopNodes = 512;
 
 // Lanes per node (log2): one per channel, so that a node's row is read and
 // written as one piece and its lanes are in one wave.
@@ -150,25 +171,41 @@ __global__ __launch_bounds__(256) void k_meta_reduce(TreeGeo t, int d, uint32_t 
     meta[((uint64_t)t.noff[d] + i) * m + c] = meta_of(v);
 }
 
-// Levels d, d - 1, .. 0 by one block.  A level is one round trip to memory
-// for every four nodes of a lane, whose loads are all issued first.
+// Levels d, d - 1, .. 0 by one block: the deepest one from memory, four nodes
+// of a lane at a time with all their loads issued first, the others from LDS.
 __global__ __launch_bounds__(1024) void k_meta_top(TreeGeo t, int d, uint32_t *meta, int m, int gl, int c_first,
                                                    uint32_t chans) {
-    const int c = c_first + (int)(threadIdx.x & ((1u << gl) - 1));
+    __shared__ uint32_t lv[2][kTopNodes * kMaxC];
+    const uint32_t lane = threadIdx.x & ((1u << gl) - 1), step = 1024u >> gl;  // nodes a round
+    const int c = c_first + (int)lane;
     const bool on = c < m && (chans >> c & 1u);
-    const uint32_t step = 1024u >> gl;  // nodes a round
-    for (; d >= 0; --d) {
-        const uint32_t n = (uint32_t)level_nodes(t, d);
-        for (uint32_t i0 = threadIdx.x >> gl; i0 < n; i0 += 4 * step) {
-            uint32_t v[4][8];
+    const uint32_t n0 = (uint32_t)level_nodes(t, d);
+    for (uint32_t i0 = threadIdx.x >> gl; i0 < n0; i0 += 4 * step) {
+        uint32_t v[4][8];
 #pragma unroll
-            for (uint32_t r = 0; r < 4; ++r)
-                if (on && i0 + r * step < n) meta_load(t, d, i0 + r * step, meta, m, c, v[r]);
+        for (uint32_t r = 0; r < 4; ++r)
+            if (on && i0 + r * step < n0) meta_load(t, d, i0 + r * step, meta, m, c, v[r]);
 #pragma unroll
-            for (uint32_t r = 0; r < 4; ++r)
-                if (on && i0 + r * step < n) meta[((uint64_t)t.noff[d] + i0 + r * step) * m + c] = meta_of(v[r]);
+        for (uint32_t r = 0; r < 4; ++r) {
+            const uint32_t i = i0 + r * step;
+            if (!on || i >= n0) continue;
+            const uint32_t w = meta_of(v[r]);
+            meta[((uint64_t)t.noff[d] + i) * m + c] = w;
+            lv[0][(i << gl) + lane] = w;
         }
+    }
+    int from = 0;
+    for (--d; d >= 0; --d, from ^= 1) {
         __syncthreads();
+        const uint32_t n = (uint32_t)level_nodes(t, d);
+        for (uint32_t i = threadIdx.x >> gl; i < n; i += step) {
+            if (!on) continue;
+            uint32_t v[8];
+            lds_children(t, d, i, gl, lane, lv[from], 0x0000FFFFu, v);
+            const uint32_t w = meta_of(v);
+            meta[((uint64_t)t.noff[d] + i) * m + c] = w;
+            lv[from ^ 1][(i << gl) + lane] = w;
+        }
     }
 }
 
@@ -451,15 +488,57 @@ __global__ __launch_bounds__(256) void k_res_prop(TreeGeo t, int d, int m, int g
     if (i0 < level_nodes(t, d)) res_wave(t, d, (uint32_t)i0, m, gl, mask, flags, all != 0);
 }
 
-// Levels d, d - 1, .. 0 by one block.
+// Levels d, d - 1, .. 0 by one block, if a node of level d is flagged: all
+// nodes of level d from memory, the levels above from LDS (a node that is not
+// flagged gets the masks that it has).  Clears the levels' flags.
 __global__ __launch_bounds__(1024) void k_res_top(TreeGeo t, int d, int m, int gl, uint16_t *mask, uint8_t *flags,
                                                   int all) {
-    const uint32_t per = res_wave_nodes(gl);
-    for (; d >= 0; --d) {
-        const uint32_t n = (uint32_t)level_nodes(t, d);
-        for (uint32_t i0 = (threadIdx.x >> 6) * per; i0 < n; i0 += 16 * per)
-            res_wave(t, d, i0, m, gl, mask, flags, all != 0);
+    __shared__ uint16_t lv[2][kTopNodes * kMaxC];
+    const uint32_t lane = threadIdx.x & ((1u << gl) - 1), step = 1024u >> gl;
+    const uint32_t n0 = (uint32_t)level_nodes(t, d);
+    const bool on = lane < (uint32_t)m;
+    if (!all) {
+        bool any = false;
+        for (uint32_t i = threadIdx.x; i < t.noff[d + 1]; i += 1024)
+            if (flags[i]) {
+                flags[i] = 0;
+                any = true;
+            }
+        if (!__syncthreads_or(any)) return;
+    }
+    for (uint32_t i0 = threadIdx.x >> gl; i0 < n0; i0 += 4 * step) {
+        uint32_t v[4][8], own[4];
+#pragma unroll
+        for (uint32_t r = 0; r < 4; ++r) {
+            const uint32_t i = i0 + r * step;
+            if (!on || i >= n0) continue;
+            res_load(t, d, i, lane, m, mask, v[r]);
+            own[r] = mask[((uint64_t)t.noff[d] + i) * m + lane];
+        }
+#pragma unroll
+        for (uint32_t r = 0; r < 4; ++r) {
+            const uint32_t i = i0 + r * step;
+            if (!on || i >= n0) continue;
+            uint32_t o = 0;
+#pragma unroll
+            for (uint32_t k = 0; k < 8; ++k) o |= v[r][k];
+            if (o != own[r]) mask[((uint64_t)t.noff[d] + i) * m + lane] = (uint16_t)o;
+            lv[0][(i << gl) + lane] = (uint16_t)o;
+        }
+    }
+    int from = 0;
+    for (--d; d >= 0; --d, from ^= 1) {
         __syncthreads();
+        const uint32_t n = (uint32_t)level_nodes(t, d);
+        for (uint32_t i = threadIdx.x >> gl; i < n; i += step) {
+            if (!on) continue;
+            uint32_t v[8], o = 0;
+            lds_children(t, d, i, gl, lane, lv[from], 0u, v);
+#pragma unroll
+            for (uint32_t k = 0; k < 8; ++k) o |= v[k];
+            mask[((uint64_t)t.noff[d] + i) * m + lane] = (uint16_t)o;
+            lv[from ^ 1][(i << gl) + lane] = (uint16_t)o;
+        }
     }
 }
 
