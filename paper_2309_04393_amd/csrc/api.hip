@@ -724,7 +724,13 @@ extern "C" ro_status ro_update_residency(ro_octree *t, void *stream) {
     if (many) radix_sort(d, tmp, t->cache->vol->g.total);
     else std::sort(d.begin(), d.end());
     d.erase(std::unique(d.begin(), d.end()), d.end());
-    ro_status st = octree_update(t, d, (hipStream_t)stream);
+    ro_status st;
+    try {
+        st = octree_update(t, d, (hipStream_t)stream);
+    } catch (...) {
+        set_error("out of host memory");
+        st = RO_E_NOMEM;
+    }
     if (st) {
         t->cache->dirty.swap(d);  // keep the work for a retry
         return st;

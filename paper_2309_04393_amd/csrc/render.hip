@@ -41,7 +41,8 @@ namespace ro {
 // 70 ms; aligned addresses alone (wrong voxels) save 2 %.  Frames of a few
 // thousand units are bound by their longest rays: four lanes per ray cut
 // those (455 x 256, 16 channels: 10.0 ms -> 2.1; 512 x 512, 4 channels:
-// 5.0 -> 2.2; 64 x 64, one channel: 0.59 -> 0.18).
+// 5.0 -> 2.2; 64 x 64, one channel: 0.59 -> 0.18, and 0.13 with its units in
+// parts, see render_device).
 
 // Persistent grid (one workgroup per CU) whose waves take units of pixels
 // from a device counter independently of each other, so a CU never waits
@@ -308,7 +309,7 @@ ro_status render_device(ro_octree *tr, const ro_frame_desc *fd, float *rgba, hip
     Q.tiles_x = tiles_x;
     Q.n_blocks = tiles_x * tiles_y * 16;
     // the block counter is in the last 256 bytes of the octree's scratch
-    // buffer (residency work items use the rest); cleared by a kernel, not a
+    // buffer (the residency update's lists use the rest); cleared by a kernel, not a
     // memset
     Q.counter = (uint32_t *)((uint8_t *)tr->b.scratch + tr->scratch_bytes - 256);
     Q.grid = dim3((unsigned)(ncu > 0 ? ncu : 256));
