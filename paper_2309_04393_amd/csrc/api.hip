@@ -501,7 +501,7 @@ extern "C" ro_status ro_octree_query(const ro_volume *v, const ro_octree_desc *d
     o->node_meta = sizeof(uint32_t) * t.n_nodes * v->g.m;
     o->node_mask = sizeof(uint16_t) * t.n_nodes * v->g.m;
     o->node_flags = t.n_nodes;
-    o->scratch = 16 * 65536 + 256;  // leaf-update work items
+    o->scratch = 16 * 65536 + kFrameTail;  // lists of the updates, the frame kernel's counters
     o->leaf_level = t.n_leaves * v->g.m;
     return RO_OK;
 }
@@ -523,7 +523,7 @@ extern "C" ro_status ro_octree_create(ro_cache *c, const ro_octree_desc *d,
     o->desc = *d;
     o->b = *b;
     o->t = t;
-    o->scratch_bytes = 16 * 65536 + 256;
+    o->scratch_bytes = 16 * 65536 + kFrameTail;
     hipStream_t s = (hipStream_t)stream;
     uint64_t nm = t.n_nodes * (uint64_t)c->vol->g.m;
     ro_status r;

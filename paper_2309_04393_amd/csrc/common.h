@@ -96,6 +96,9 @@ struct ro_volume {
 };
 
 namespace ro {
+// End of a tree's scratch: the frame kernel's unit counters.
+constexpr size_t kFrameTail = 2048;
+
 // LRU select: bins of its histograms, words of its state before the victims,
 // and the candidates that it may rank beyond those asked for.
 constexpr uint32_t kSelHistWords = 3 * 2048, kSelStateWords = 128, kSelSlack = 4096;

@@ -575,11 +575,11 @@ ro_status octree_update(ro_octree *tr, const std::vector<uint32_t> &dirty, hipSt
     const VolGeo &g = tr->cache->vol->g;
     const TreeGeo &t = tr->t;
     const int D = t.depth;
-    // runs first, then the bricks, in the tree's scratch (its last 256 bytes
-    // are the frame kernel's)
+    // runs first, then the bricks, in the tree's scratch (its end is
+    // the frame kernel's)
     constexpr size_t kRunBytes = 4096;
     constexpr size_t kRunsMax = kRunBytes / sizeof(LeafRun);  // as many channels x levels as a volume has
-    const size_t cap = (tr->scratch_bytes - 256 - kRunBytes) / sizeof(uint32_t);
+    const size_t cap = (tr->scratch_bytes - kFrameTail - kRunBytes) / sizeof(uint32_t);
     std::vector<LeafRun> runs;
     runs.reserve(kRunsMax);
     std::vector<uint8_t> buf;
@@ -670,7 +670,7 @@ ro_status octree_meta_from_bricks(ro_octree *tr, const std::vector<uint32_t> &de
     const VolGeo &g = tr->cache->vol->g;
     const TreeGeo &t = tr->t;
     const int D = t.depth;
-    const size_t cap = (tr->scratch_bytes - 256) / sizeof(MetaItem);
+    const size_t cap = (tr->scratch_bytes - kFrameTail) / sizeof(MetaItem);
     // A level's items are one launch (the launches of coarser levels finish
     // first); all levels' items go up in one copy, and `start` counts anew in
     // each level.

@@ -308,10 +308,10 @@ ro_status render_device(ro_octree *tr, const ro_frame_desc *fd, float *rgba, hip
     const uint32_t tiles_x = (uint32_t)(fd->width + 31) / 32, tiles_y = (uint32_t)(fd->height + 31) / 32;
     Q.tiles_x = tiles_x;
     Q.n_blocks = tiles_x * tiles_y * 16;
-    // the block counter is in the last 256 bytes of the octree's scratch
+    // the unit counters are at the end of the octree's scratch
     // buffer (the residency update's lists use the rest); cleared by a kernel, not a
     // memset
-    Q.counter = (uint32_t *)((uint8_t *)tr->b.scratch + tr->scratch_bytes - 256);
+    Q.counter = (uint32_t *)((uint8_t *)tr->b.scratch + tr->scratch_bytes - kFrameTail);
     Q.grid = dim3((unsigned)(ncu > 0 ? ncu : 256));
     // a frame with fewer units of pixels than the chip has waves uses as many
     // waves of each workgroup as it has units per CU (64 x 64 pixels: 0.37 ms
@@ -331,7 +331,6 @@ ro_status render_device(ro_octree *tr, const ro_frame_desc *fd, float *rgba, hip
     const uint32_t per_cu = ((n_units << Q.split) + Q.grid.x - 1) / Q.grid.x;
     Q.n_waves = per_cu < kRenderLanes / 64 ? per_cu : kRenderLanes / 64;
     Q.chunk = (queue_chunk(Q.n_blocks) * (uint32_t)p) << Q.split;
-    static_assert(RO_QUEUES * kQueueStride * 4 <= 256, "queue counters exceed the scratch tail");
     st = launch_fill_u32(Q.counter, (uint64_t)RO_QUEUES * kQueueStride, 0u, s);
     if (st) return st;
     // the diagnostic outputs (per-level reads, required bricks) take the AOV kernel

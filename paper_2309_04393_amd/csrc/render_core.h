@@ -267,7 +267,6 @@ struct RayLds {
 // work on separate neighbouring chunks (their L2s hold different lines)
 // while all of them still sweep the image together (the Infinity Cache is
 // shared).  Counter reads and the unit are wave-uniform.
-constexpr int kQueueStride = 8;  // words between queue counters (32 bytes)
 // Per-XCD block queues: blocks are dealt to them in chunks of RO_CHUNK
 // consecutive blocks (16 chunks per queue at 1080p).  On the 16-channel
 // 1080p frame chunks of 256 measured 0.6 % faster than 64, 16 0.7 % slower,
@@ -278,6 +277,13 @@ constexpr int kQueueStride = 8;  // words between queue counters (32 bytes)
 #ifndef RO_CHUNK
 #define RO_CHUNK 256
 #endif
+// Words between queue counters: 256 bytes, so that they are in different
+// memory channels.  At 32 bytes a light 1080p frame (ten samples a pixel, a
+// device atomic per 4 x 4 pixels) waited for the atomics of one channel: 4
+// channels far away 1.43 ms to 1.09, homogeneous nodes 0.84 to 0.39.  (Four units per atomic relieve it too, but the units of a block then
+// run one after another in one wave: 43 ms to 51 for 16 channels.)
+constexpr int kQueueStride = 64;
+static_assert(RO_QUEUES * kQueueStride * 4 <= kFrameTail, "unit counters");
 // Blocks per chunk of an image of n_blocks: smaller images in smaller chunks,
 // whole 32 x 32 tiles of them.
 __host__ __device__ inline uint32_t queue_chunk(uint32_t n_blocks) {
