@@ -417,6 +417,18 @@ __device__ __forceinline__ float wave_min(float v) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
+// The lanes of a wave exchange values through LDS without a barrier of the
+// workgroup (the miss table; the slot words of a ray): what lanes wrote before
+// this point is what all lanes read after it, and what they read before it is
+// what was there.  LDS serves a wave in order, so it costs no instruction; it
+// keeps the compiler from taking a lane's last store or load for the word's
+// value.  Called by the whole wave.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // EC: the brick edge with halo known at compile time (0: read from A).  A
 // constant edge turns the four gather offsets into instruction immediates.
 // EXT: bit 0 render-and-skip of nodes homogeneous for all channels, bit 1
@@ -645,11 +657,13 @@ __device__ __forceinline__ void render_rays(const RenderArgs &A, UnitQueue<P> &s
             const uint32_t ek = e[0], em = e[1], en = e[2];
             const bool hit = ek == key && em == msk;
             if (!hit && em) count_misses(ek, em, en);
+            wave_sync();
             if (ln == 0) {
                 e[0] = key;
                 e[1] = msk;
                 e[2] = hit ? en + n : n;
             }
+            wave_sync();
             todo &= ~like;
         }
     };
@@ -1379,6 +1393,7 @@ __device__ __forceinline__ void render_rays(const RenderArgs &A, UnitQueue<P> &s
     constexpr int kVisitLanes = 24;
     double klim = -1.0;
     if ((threadIdx.x & 63u) < kMissEntries) lds.miss[3 * (threadIdx.x & 63u) + 1] = 0;
+    wave_sync();
     src.init();
     while (true) {
         const bool fin = has && (done || k > kend);
@@ -1391,6 +1406,7 @@ __device__ __forceinline__ void render_rays(const RenderArgs &A, UnitQueue<P> &s
             bool v = false;
             if (!src.next(x, y, v)) break;
             start(x, y, v);
+            wave_sync();
         }
         const bool active = has && !done && k <= kend;
         const bool wv = active && k >= kseg;
@@ -1408,7 +1424,9 @@ __device__ __forceinline__ void render_rays(const RenderArgs &A, UnitQueue<P> &s
         }
         if (!(bv | bs)) continue;  // rays that just began without a sample
         if (bv && (!bs || __popcll(bv) >= kVisitLanes)) {
+            wave_sync();
             if (wv) visit();
+            wave_sync();
             flush(fpend, fmask, fkey);
             fpend = 0;
             continue;
