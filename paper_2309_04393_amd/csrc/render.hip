@@ -50,14 +50,16 @@ namespace ro {
 template <int NV, int BPV, bool AOV, int EC, int EXT, int P>
 __global__ void __launch_bounds__(kRenderLanes) __attribute__((amdgpu_waves_per_eu(kRenderLanes / 256)))
     k_render(const RenderArgs A, uint32_t *counter, uint32_t n_blocks, uint32_t tiles_x, uint32_t chunk,
-             uint32_t n_waves, uint32_t split) {
+             uint32_t n_waves, uint32_t split, uint32_t take) {
     extern __shared__ float4 s_tf[];  // tables, per-ray words, miss tables (render_lds_bytes)
     __shared__ ChanLds s_ch[NV];
     __shared__ ChanPar<NV> s_par;
     __shared__ uint32_t s_runs[NV * kMaxRuns];
     __shared__ LevLds s_lv[kMaxL];
     __shared__ NodeLds s_nd[kMaxD + 1];
+    __shared__ UnitLds s_wg;
 
+    if (threadIdx.x == 0) s_wg.clear();
     stage_frame<NV>(A, s_tf, s_ch, &s_par, s_runs, s_lv, s_nd);
     if ((threadIdx.x >> 6) >= n_waves) return;  // a small frame: its blocks are spread over the CUs
 
@@ -69,6 +71,8 @@ __global__ void __launch_bounds__(kRenderLanes) __attribute__((amdgpu_waves_per_
     q.n_queues = RO_QUEUES;
     q.chunk = chunk;
     q.split = P == 4 ? split : 0;
+    q.take = take;
+    q.wg = &s_wg;
     q.W = A.W;
     q.H = A.H;
     uint32_t st[7] = {0, 0, 0, 0, 0, 0, 0};
@@ -93,7 +97,7 @@ constexpr int lanes_per_ray(bool aov) { return aov ? 1 : 4; }
 struct QueueLaunch {
     dim3 grid;
     uint32_t *counter;
-    uint32_t n_blocks, tiles_x, chunk, n_waves, split;
+    uint32_t n_blocks, tiles_x, chunk, n_waves, split, take;
 };
 
 template <int NV, int BPV, bool AOV, int EC, int EXT>
@@ -104,7 +108,7 @@ static hipError_t launch_one(const RenderArgs &A, const QueueLaunch &Q, hipStrea
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_render<NV, BPV, AOV, EC, EXT, P>), Q.grid, dim3(kRenderLanes), lds, s, A, Q.counter, Q.n_blocks,
-                       Q.tiles_x, Q.chunk, Q.n_waves, Q.split);
+                       Q.tiles_x, Q.chunk, Q.n_waves, Q.split, Q.take);
     return hipGetLastError();
 }
 
@@ -331,6 +335,7 @@ ro_status render_device(ro_octree *tr, const ro_frame_desc *fd, float *rgba, hip
     const uint32_t per_cu = ((n_units << Q.split) + Q.grid.x - 1) / Q.grid.x;
     Q.n_waves = per_cu < kRenderLanes / 64 ? per_cu : kRenderLanes / 64;
     Q.chunk = (queue_chunk(Q.n_blocks) * (uint32_t)p) << Q.split;
+    Q.take = p == 4 ? units_at_once(n_units, Q.grid.x * (kRenderLanes / 64)) : 1;
     st = launch_fill_u32(Q.counter, (uint64_t)RO_QUEUES * kQueueStride, 0u, s);
     if (st) return st;
     // the diagnostic outputs (per-level reads, required bricks) take the AOV kernel

@@ -84,6 +84,8 @@ __device__ __forceinline__ void serve_item(const RenderArgs &sA, uint32_t seg, u
     q.offset = first * kServeP;
     q.n_queues = 1;
     q.chunk = 1;
+    q.take = 1;
+    q.wg = nullptr;
     serve_units<NV, BPV, EC>(sA, q, s_tf, s_ch, s_par, s_runs, s_lv, s_nd);
 }
 
@@ -109,6 +111,7 @@ __global__ void __launch_bounds__(kRenderLanes) __attribute__((amdgpu_waves_per_
     __shared__ LevLds s_lv[kMaxL];
     __shared__ NodeLds s_nd[kMaxD + 1];
     __shared__ uint32_t s_skip[2], s_taken;
+    __shared__ UnitLds s_wg;
     const uint32_t n_req = hdr->n_req;
     const uint32_t lane = threadIdx.x & 63;
     if (threadIdx.x == 0) s_taken = 0;
@@ -119,6 +122,7 @@ __global__ void __launch_bounds__(kRenderLanes) __attribute__((amdgpu_waves_per_
             s_skip[req & 1] = __hip_atomic_load(used_up + req, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
         if (s_skip[req & 1]) continue;
+        if (threadIdx.x == 0) s_wg.clear();
         const uint32_t *src = (const uint32_t *)(descs + req);
         uint32_t *dst = (uint32_t *)&sA;
         for (unsigned i = threadIdx.x; i < sizeof(RenderArgs) / 4; i += blockDim.x) dst[i] = src[i];
@@ -131,6 +135,8 @@ __global__ void __launch_bounds__(kRenderLanes) __attribute__((amdgpu_waves_per_
         q.offset = 0;
         q.n_queues = RO_QUEUES;
         q.chunk = queue_chunk(n_blk) * kServeP;
+        q.take = kMaxTake;  // other requests fill in for a workgroup's heavy units
+        q.wg = &s_wg;
         serve_units<NV, BPV, EC>(sA, q, s_tf, s_ch, &s_par, s_runs, s_lv, s_nd);
         if (lane == 0 && q.taken) atomicAdd(&s_taken, q.taken);
         __threadfence();  // this workgroup's pixels are visible device-wide before its units are counted
