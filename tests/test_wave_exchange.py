@@ -18,9 +18,8 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 @pytest.mark.parametrize("inst", ["1, 1, false, 18, 0, 4", "4, 2, false, 34, 2, 4"])
 def test_lds_exchange_is_fenced(tmp_path, inst):
     src = tmp_path / "one.hip"
-    src.write_text('#define RO_PART 9\n#include "render.hip"\nnamespace ro {\ntemplate __global__ void '
-                   "k_render<%s>(const RenderArgs, uint32_t *, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t);\n}\n"
-                   % inst)
+    src.write_text('#define RO_PART 9\n#include "render.hip"\n'
+                   "const void *instance() { return (const void *)&ro::k_render<%s>; }\n" % inst)
     out = tmp_path / "one.ll"
     subprocess.run([HIPCC, "-O3", "-std=c++17", "--offload-arch=gfx950", "--cuda-device-only", "-emit-llvm", "-S",
                     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
