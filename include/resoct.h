@@ -526,11 +526,13 @@ ro_status ro_pf_candidates(ro_prefetch *p, const float *z_dev, float threshold, 
 /* Batched rendering for a serving loop (an addition to the paper's method):
  * one persistent kernel renders up to 64 frame requests of different
  * viewports, channel subsets, transfer functions and cameras over the shared
- * cache and octree; its workgroups take 4 x 4-pixel units of one request
- * after another from device counters (continuous admission deals in work
- * items of up to 96 blocks of 8 x 8 pixels, which ro_serve_work_items counts
- * and the limits are given in).  Each pixel runs the same code as ro_render, so a request's image is
- * the same alone and in any batch.
+ * cache and octree.  A request has places for as many workgroups as it has
+ * work items (up to 96 blocks of 8 x 8 pixels each: ro_serve_work_items
+ * counts them, and the limits are given in them); the workgroups take places
+ * in the requests' order and then help where work is left, and their waves
+ * take 4 x 4-pixel units from device counters (continuous admission deals in
+ * whole work items).  Each pixel runs the same code as ro_render, so a
+ * request's image is the same alone and in any batch.
  *
  * A server owns pinned host memory for two batches ("halves", used
  * alternately) and two non-blocking streams of default priority, one per

@@ -1,10 +1,10 @@
 // Multi-request rendering for the serving loop (an addition to the paper's
 // method): one persistent kernel renders a batch of frame requests of
 // different viewports, channel subsets and transfer functions over the
-// shared cache and octree.  A workgroup stages a request's descriptor and
-// tables in LDS; its waves then take the request's 4 x 4-pixel units from
-// device counters as the frame kernel's waves do, and when the request is
-// used up the workgroup goes on to the next one that is not.  Every pixel
+// shared cache and octree.  A workgroup takes a place at a request and stages
+// its descriptor and tables in LDS; its waves then take the request's 4 x
+// 4-pixel units from device counters as the frame kernel's waves do, and when
+// the request is used up the workgroup goes on to another.  Every pixel
 // runs the same per-ray code as the frame kernel, so a request's image does
 // not depend on what else is in the batch.
 //
@@ -30,9 +30,10 @@ struct ServeHeader {
     uint32_t seq;              // batch ticket (low 32 bits), posted per finished request
     uint32_t *done;            // device [max_req] finished units per request
     volatile uint32_t *flags;  // mapped host [max_req] completion tickets
-    uint32_t pad[58];
+    uint32_t first[65];        // places (work items) of the requests before each one, then of all
+    uint32_t pad[57];
 };
-static_assert(sizeof(ServeHeader) == 256, "batch header layout");
+static_assert(sizeof(ServeHeader) == 512, "batch header layout");
 
 // Work items of a W x H request: its 8 x 8 blocks (16 per 32 x 32 tile) in
 // groups of kSegBlocks.
@@ -91,18 +92,50 @@ __device__ __forceinline__ void serve_item(const RenderArgs &sA, uint32_t seg, u
 
 constexpr uint32_t kReqCounters = RO_QUEUES * kQueueStride;  // words of a request's unit counters
 
-// A workgroup goes through the batch's requests: it stages one that still has
-// units, and its waves take units until there are none.  Bound by the rays,
-// so by how long waves stand idle: work handed to whole workgroups (96 blocks
-// of 8 x 8 pixels an item, 425 items for twelve requests of 256^2 to 1137 x
-// 640) left the last items to a few of them (64 ms; now 50).  A change of
-// request waits for the slowest of the workgroup's waves; starts spread over
-// the requests in proportion to their pixels, so that most workgroups change
-// seldom, took as long, and finish the first requests last.
+// The workgroup's next request, or n_req if no request has units left; by a
+// whole wave, the same in every lane.  A request has places for as many
+// workgroups as it has work items, handed out in the requests' order; once
+// they are gone the workgroups help where units are left, each looking from
+// another request on.
+__device__ __forceinline__ uint32_t next_request(const ServeHeader *__restrict__ hdr, uint32_t n_req,
+                                                 uint32_t *place, const uint32_t *used_up) {
+    uint32_t lane = threadIdx.x;
+    asm volatile("" : "+v"(lane));
+    lane &= 63;
+    const uint32_t end = lane < n_req ? hdr->first[lane + 1] : ~0u, all = hdr->first[n_req];
+    while (true) {
+        uint32_t t = 0;
+        if (lane == 0) t = atomicAdd(place, 1u);
+        t = (uint32_t)__builtin_amdgcn_readfirstlane((int)t);
+        const uint64_t left = __ballot(
+            lane < n_req && __hip_atomic_load(used_up + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0);
+        if (t >= all) {
+            if (!left) return n_req;
+            const uint32_t from = blockIdx.x % n_req;
+            const uint64_t after = left >> from << from;
+            return (uint32_t)__builtin_ctzll(after ? after : left);
+        }
+        const uint32_t r = (uint32_t)__popcll(__ballot(end <= t));
+        if (left >> r & 1) return r;
+        // a used-up request's other places are of no use
+        if (lane == 0) atomicMax(place, hdr->first[r + 1]);
+    }
+}
+
+// A workgroup takes a place at a request, stages it, and its waves take units
+// until there are none.  Bound by the rays, so by how long waves stand idle:
+// work handed to whole workgroups (96 blocks of 8 x 8 pixels an item, 425
+// items for twelve requests of 256^2 to 1137 x 640) left the last items to a
+// few of them (64 ms with them, 41.6 now).  A change of request costs the
+// staging of its tables and the wait for the slowest of the workgroup's waves:
+// with all workgroups on each request in turn that was what a batch of short
+// rays took (12 requests, 4 channels, rays of three samples: 1.47 ms, 0.96
+// with places; 16 channels 1.83 and 1.25; long rays 43.5 and 41.6).  Twice or
+// half as many places are within 10 % of this.
 template <int NV, int BPV, int EC>
 __global__ void __launch_bounds__(kRenderLanes) __attribute__((amdgpu_waves_per_eu(kRenderLanes / 256)))
     k_serve(const ServeHeader *__restrict__ hdr, const RenderArgs *__restrict__ descs, uint32_t *counters,
-            uint32_t *used_up) {
+            uint32_t *used_up, uint32_t *place) {
     extern __shared__ float4 s_tf[];  // tables, per-ray words, miss tables (render_lds_bytes)
     __shared__ RenderArgs sA;
     __shared__ ChanLds s_ch[NV];
@@ -110,18 +143,18 @@ __global__ void __launch_bounds__(kRenderLanes) __attribute__((amdgpu_waves_per_
     __shared__ uint32_t s_runs[NV * kMaxRuns];
     __shared__ LevLds s_lv[kMaxL];
     __shared__ NodeLds s_nd[kMaxD + 1];
-    __shared__ uint32_t s_skip[2], s_taken;
+    __shared__ uint32_t s_req, s_taken;
     __shared__ UnitLds s_wg;
     const uint32_t n_req = hdr->n_req;
-    const uint32_t lane = threadIdx.x & 63;
     if (threadIdx.x == 0) s_taken = 0;
-    for (uint32_t req = 0; req < n_req; ++req) {
-        // set once a workgroup has found no more units: then nobody needs to
-        // look (two words in turn, so one barrier a round is enough)
-        if (threadIdx.x == 0)
-            s_skip[req & 1] = __hip_atomic_load(used_up + req, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    while (true) {
+        if (threadIdx.x < 64) {
+            const uint32_t r = next_request(hdr, n_req, place, used_up);
+            if (threadIdx.x == 0) s_req = r;
+        }
         __syncthreads();
-        if (s_skip[req & 1]) continue;
+        const uint32_t req = s_req;
+        if (req >= n_req) break;
         if (threadIdx.x == 0) s_wg.clear();
         const uint32_t *src = (const uint32_t *)(descs + req);
         uint32_t *dst = (uint32_t *)&sA;
@@ -138,9 +171,9 @@ __global__ void __launch_bounds__(kRenderLanes) __attribute__((amdgpu_waves_per_
         q.take = kMaxTake;  // other requests fill in for a workgroup's heavy units
         q.wg = &s_wg;
         serve_units<NV, BPV, EC>(sA, q, s_tf, s_ch, &s_par, s_runs, s_lv, s_nd);
-        if (lane == 0 && q.taken) atomicAdd(&s_taken, q.taken);
+        if ((threadIdx.x & 63) == 0 && q.taken) atomicAdd(&s_taken, q.taken);
         __threadfence();  // this workgroup's pixels are visible device-wide before its units are counted
-        __syncthreads();  // sA and the LDS tables are reused by the next request
+        __syncthreads();  // sA, s_req and the LDS tables are reused by the next request
         if (threadIdx.x == 0) {
             __hip_atomic_store(used_up + req, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             // the workgroup that brings the count to the request's units
@@ -259,10 +292,11 @@ __global__ void k_zero(uint32_t *p, uint32_t n) {
     for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
 }
 
-__global__ void k_serve_reset(uint32_t *counters, uint32_t *used_up, uint32_t *done, uint32_t n) {
+__global__ void k_serve_reset(uint32_t *counters, uint32_t *used_up, uint32_t *done, uint32_t *place, uint32_t n) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n * kReqCounters) counters[i] = 0;
     if (i < n) used_up[i] = done[i] = 0;
+    if (i == 0) *place = 0;
 }
 
 ro_status build_render_args(ro_octree *tr, const ro_frame_desc *fd, float *rgba, RenderArgs &A);
@@ -352,6 +386,11 @@ static inline uint32_t *serve_counters(const ro_server *s, int h) {
     return (uint32_t *)(s->dev + 2 * s->half + 1536) + (size_t)h * s->max_req * kReqCounters;
 }
 
+// place counter of half h
+static inline uint32_t *serve_place(const ro_server *s, int h) {
+    return (uint32_t *)(s->dev + 2 * s->half + 1536 + 2 * 4 * (size_t)s->max_req * kReqCounters + 256 * (size_t)h);
+}
+
 // per-request finished unit counts of half h (max_req <= 64 words)
 static inline uint32_t *serve_done(const ro_server *s, int h) {
     return (uint32_t *)(s->dev + 2 * s->half + 512 + 256 * (size_t)h);
@@ -408,11 +447,11 @@ static void serve_launch_e(const ro_server *s, int h, hipStream_t st) {
     const uint8_t *d = s->dev + (size_t)h * s->half;
     const ServeHeader *dh = (const ServeHeader *)d;
     const RenderArgs *dd = (const RenderArgs *)(d + sizeof(ServeHeader));
-    uint32_t *c = serve_counters(s, h), *u = serve_used_up(s, h);
+    uint32_t *c = serve_counters(s, h), *u = serve_used_up(s, h), *p = serve_place(s, h);
     hipLaunchKernelGGL(k_serve_reset, dim3((s->max_req * kReqCounters + 255) / 256), dim3(256), 0, st, c, u,
-                       serve_done(s, h), s->max_req);
+                       serve_done(s, h), p, s->max_req);
     hipLaunchKernelGGL((k_serve<NV, BPV, EC>), dim3(s->ncu), dim3(kRenderLanes), render_lds_bytes(NV, kServeP), st, dh, dd,
-                       c, u);
+                       c, u, p);
 }
 
 // compile-time brick edge for 32^3 and 16^3 bricks (see the frame kernel)
@@ -441,7 +480,7 @@ static hipError_t serve_enqueue(const ro_server *s, int h, hipStream_t st) {
 extern "C" ro_status ro_serve_query(uint32_t max_requests, uint32_t max_tiles, size_t *device_bytes) {
     RO_CHECK(device_bytes, RO_E_ARG, "null argument");
     (void)max_tiles;  // the work items of continuous admission are in host memory
-    *device_bytes = 2 * serve_half_bytes(max_requests) + 1536 + 2 * 4 * (size_t)max_requests * kReqCounters;
+    *device_bytes = 2 * serve_half_bytes(max_requests) + 1536 + 2 * 4 * (size_t)max_requests * kReqCounters + 512;
     return RO_OK;
 }
 
@@ -585,6 +624,7 @@ extern "C" ro_status ro_serve_prepare(ro_server *s, uint32_t n, const ro_frame_d
     uint8_t *base = s->host + (size_t)h * s->half;
     ServeHeader *hh = (ServeHeader *)base;
     RenderArgs *hd = (RenderArgs *)(base + sizeof(ServeHeader));
+    hh->first[0] = 0;
     for (uint32_t r = 0; r < n; ++r) {
         RenderArgs A;
         ro_status st = build_render_args(s->tree, &fds[r], rgba[r], A);
@@ -593,6 +633,7 @@ extern "C" ro_status ro_serve_prepare(ro_server *s, uint32_t n, const ro_frame_d
             return st;
         }
         memcpy(&hd[r], &A, sizeof(A));
+        hh->first[r + 1] = hh->first[r] + serve_segments(fds[r].width, fds[r].height);
     }
     hh->n_req = n;
     hh->seq = (uint32_t)s->next_ticket;  // the ticket the next submission assigns
