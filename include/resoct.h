@@ -324,7 +324,8 @@ ro_status ro_octree_set_leaf_unknown(ro_octree *t, uint32_t channel, void *strea
  * (ro_octree_set_leaf_unknown).  Inner nodes of the touched channels are
  * then reduced again.  Reads the slots: call it after the ro_stream_bricks
  * that uploaded them, on the same stream or after it has completed.  Returns
- * after the work is queued (it waits for its own copies of the work list). */
+ * once the work is queued; the tree keeps the list of work until it has been
+ * copied.  Refuses a stream under capture. */
 ro_status ro_octree_leaf_metadata_from_bricks(ro_octree *t, uint32_t n, const uint32_t *ids_host,
                                               void *stream);
 
@@ -332,7 +333,8 @@ ro_status ro_octree_leaf_metadata_from_bricks(ro_octree *t, uint32_t n, const ui
  * (Sec. 5.3): each leaf overlapping such a brick gets bit l of its channel's
  * mask set iff the level-l brick containing it is resident; then every
  * inner node whose children changed gets the OR of its children, level by
- * level, stopping where nothing changed. */
+ * level, stopping where nothing changed.  Returns once the work is queued, as
+ * ro_octree_leaf_metadata_from_bricks does; refuses a stream under capture. */
 ro_status ro_update_residency(ro_octree *t, void *stream);
 
 /* From-scratch recomputation of every mask from the page tables. */

@@ -373,7 +373,7 @@ extern "C" ro_status ro_stream_bricks(ro_cache *c, uint32_t frame, uint32_t n,
     try {
         dn.resize(n);
         f.resize(n);
-        up.reserve(3 * (size_t)n);
+        up.reserve(n);
         src.reserve(n);
         touch.reserve(n);
         result.resize(kSelStateWords + (size_t)n);
@@ -408,10 +408,15 @@ extern "C" ro_status ro_stream_bricks(ro_cache *c, uint32_t frame, uint32_t n,
     for (uint32_t b : up) c->pt_host[b] = kInvalid;
     const uint32_t n_up = (uint32_t)up.size();
     // one copy carries the batch: uploads, their staged indices, slots to touch
-    up.insert(up.end(), src.begin(), src.end());
-    up.insert(up.end(), touch.begin(), touch.end());
-    ro_status st = stream_bricks_device(c, frame, n_up, (uint32_t)touch.size(), up.data(), staged,
-                                        (hipStream_t)stream, result.data());
+    uint8_t *list = nullptr;
+    ro_status st = c->batch.make(4 * (2 * (size_t)n_up + touch.size()), (hipStream_t)stream, &list);
+    if (st) return st;
+    if (n_up) {
+        memcpy(list, up.data(), 4 * (size_t)n_up);
+        memcpy(list + 4 * (size_t)n_up, src.data(), 4 * (size_t)n_up);
+    }
+    if (!touch.empty()) memcpy(list + 8 * (size_t)n_up, touch.data(), 4 * touch.size());
+    st = stream_bricks_device(c, frame, n_up, (uint32_t)touch.size(), staged, (hipStream_t)stream, result.data());
     if (st) return st;
     // Mirror the device's decisions.
     const uint32_t k_eff = n_up ? result[0] : 0;

@@ -102,6 +102,35 @@ constexpr size_t kFrameTail = 2048;
 // LRU select: bins of its histograms, words of its state before the victims,
 // and the candidates that it may rank beyond those asked for.
 constexpr uint32_t kSelHistWords = 3 * 2048, kSelStateWords = 128, kSelSlack = 4096;
+
+// Host copy of a list on its way to the device: the call that sends it need
+// not wait for the copy, since the list stays until the next one is made (or
+// the owner goes), which waits for the event behind it.  The event is
+// recorded behind the call's last launch: right behind the copy, the launches
+// waited for its packet (a batch of one brick 46 us to 70).  Refuses a
+// stream under capture, whose replays would read another call's list.
+class SentList {
+    std::vector<uint8_t> buf;
+    hipEvent_t used = nullptr;
+    hipStream_t stream = nullptr;
+    enum { kIdle, kSent, kMarked } state = kIdle;
+
+    ro_status wait();
+
+public:
+    SentList() = default;
+    SentList(const SentList &) = delete;
+    SentList &operator=(const SentList &) = delete;
+    ~SentList() {
+        (void)wait();
+        if (used) (void)hipEventDestroy(used);
+    }
+    // n bytes to fill, once the last list has been copied
+    ro_status make(size_t n, hipStream_t s, uint8_t **out);
+    ro_status send(void *dev);  // all of them, on the stream of make()
+    void mark();                // behind the call's last launch
+    void done() { state = kIdle; }  // the stream has been waited for
+};
 }  // namespace ro
 
 // Scratch layout of a cache (byte offsets into bufs.scratch).
@@ -126,6 +155,7 @@ struct ro_cache {
     std::vector<uint32_t> dirty;       // bricks inserted / evicted since the last residency update
     std::vector<uint32_t> chmap;       // cache channel -> source channel (Sec. 5.2)
     uint32_t seq_next;
+    ro::SentList batch;                // of the last ro_stream_bricks
 };
 
 struct ro_octree {
@@ -134,6 +164,7 @@ struct ro_octree {
     ro_octree_buffers b;
     ro::TreeGeo t;
     size_t scratch_bytes;
+    ro::SentList list;  // of the last residency or metadata update
 };
 
 namespace ro {
@@ -143,10 +174,10 @@ ro_status launch_fill_u16(uint16_t *p, uint64_t n, uint16_t v, hipStream_t s);
 ro_status launch_fill_u8(uint8_t *p, uint64_t n, uint8_t v, hipStream_t s);
 
 // Uploads n_new bricks (batch: dense indices, staged indices) and stamps
-// n_touch slots (batch, after the uploads).  result (kSelStateWords + n_new
-// words) receives the number of slots found and then their indices.
+// n_touch slots (batch, after the uploads), both in c->batch.  result
+// (kSelStateWords + n_new words) receives the number of slots found and then their indices.
 ro_status stream_bricks_device(ro_cache *c, uint32_t frame, uint32_t n_new, uint32_t n_touch,
-                               const uint32_t *batch, const void *staged, hipStream_t s, uint32_t *result);
+                               const void *staged, hipStream_t s, uint32_t *result);
 ro_status read_requests_device(ro_cache *c, uint32_t cap, uint32_t *ids, uint32_t *counts,
                                uint32_t *n_unique, uint64_t *total, hipStream_t s);
 size_t compact_scratch_bytes(uint64_t n, uint32_t lim);

@@ -582,17 +582,18 @@ ro_status octree_update(ro_octree *tr, const std::vector<uint32_t> &dirty, hipSt
     const size_t cap = (tr->scratch_bytes - kFrameTail - kRunBytes) / sizeof(uint32_t);
     std::vector<LeafRun> runs;
     runs.reserve(kRunsMax);
-    std::vector<uint8_t> buf;
     size_t first = 0, n_items = 0;  // bricks of the pending launch: dirty[first .. first + n_items)
     uint64_t work = 0;
     auto launch = [&]() -> ro_status {
         if (n_items == 0) return RO_OK;
         // one copy: the runs (a few), padded, and the bricks
         const size_t at = runs.size() * sizeof(LeafRun);
-        buf.resize(at + n_items * sizeof(uint32_t));
-        memcpy(buf.data(), runs.data(), at);
-        memcpy(buf.data() + at, dirty.data() + first, n_items * sizeof(uint32_t));
-        RO_HIP(hipMemcpyAsync(tr->b.scratch, buf.data(), buf.size(), hipMemcpyHostToDevice, s));
+        uint8_t *list = nullptr;
+        ro_status st = tr->list.make(at + n_items * sizeof(uint32_t), s, &list);
+        if (st) return st;
+        memcpy(list, runs.data(), at);
+        memcpy(list + at, dirty.data() + first, n_items * sizeof(uint32_t));
+        if ((st = tr->list.send(tr->b.scratch))) return st;
         hipLaunchKernelGGL(k_res_leaf, dim3(nblocks(work)), dim3(256), 0, s, g, t, (const LeafRun *)tr->b.scratch,
                            (uint32_t)runs.size(), (const uint32_t *)((uint8_t *)tr->b.scratch + at), (uint32_t)work,
                            tr->cache->b.page_table, tr->b.node_mask, tr->b.node_flags);
@@ -624,8 +625,6 @@ ro_status octree_update(ro_octree *tr, const std::vector<uint32_t> &dirty, hipSt
             if (n_items == cap || work + (1ull << lz) > 0x7FFFFFFFull) {
                 ro_status st = launch();
                 if (st) return st;
-                // the host buffer must outlive the copy: wait before reuse
-                RO_HIP(hipStreamSynchronize(s));
                 runs.clear();
                 first = i;
                 n_items = 0;
@@ -640,11 +639,8 @@ ro_status octree_update(ro_octree *tr, const std::vector<uint32_t> &dirty, hipSt
     }
     ro_status st = launch();
     if (!st) st = res_propagate(tr, 0, s);
-    if (st) return st;
-    // the list must outlive its copy; waited for behind the last launch, so
-    // that the device has no gap before the propagation
-    RO_HIP(hipStreamSynchronize(s));
-    return RO_OK;
+    tr->list.mark();
+    return st;
 }
 
 ro_status octree_rebuild(ro_octree *tr, hipStream_t s) {
@@ -686,7 +682,11 @@ ro_status octree_meta_from_bricks(ro_octree *tr, const std::vector<uint32_t> &de
     int cur_level = -1;
     auto launch = [&]() -> ro_status {
         if (items.empty()) return RO_OK;
-        RO_HIP(hipMemcpyAsync(tr->b.scratch, items.data(), items.size() * sizeof(MetaItem), hipMemcpyHostToDevice, s));
+        uint8_t *list = nullptr;
+        ro_status st = tr->list.make(items.size() * sizeof(MetaItem), s, &list);
+        if (st) return st;
+        memcpy(list, items.data(), items.size() * sizeof(MetaItem));
+        if ((st = tr->list.send(tr->b.scratch))) return st;
         // at most 2^22 blocks of four waves per launch
         constexpr uint64_t kChunk = 1ull << 24;
         for (size_t k = 0; k < runs.size(); ++k) {
@@ -728,8 +728,6 @@ ro_status octree_meta_from_bricks(ro_octree *tr, const std::vector<uint32_t> &de
         if (items.size() == cap) {
             ro_status st = launch();
             if (st) return st;
-            // the host buffer must outlive the copy: wait before reuse
-            RO_HIP(hipStreamSynchronize(s));
             items.clear();
             runs.clear();
         }
@@ -748,10 +746,8 @@ ro_status octree_meta_from_bricks(ro_octree *tr, const std::vector<uint32_t> &de
     }
     ro_status st = launch();
     if (!st) st = meta_reduce(tr, D - 1, lanes_log(g.m), 0, chans, s);
-    if (st) return st;
-    // the list must outlive its copy; waited for behind the last launch
-    RO_HIP(hipStreamSynchronize(s));
-    return RO_OK;
+    tr->list.mark();
+    return st;
 }
 
 }  // namespace ro

@@ -33,6 +33,44 @@ ro_status launch_fill_u32(uint32_t *p, uint64_t n, uint32_t v, hipStream_t s) { 
 ro_status launch_fill_u16(uint16_t *p, uint64_t n, uint16_t v, hipStream_t s) { return fill(p, n, v, s); }
 ro_status launch_fill_u8(uint8_t *p, uint64_t n, uint8_t v, hipStream_t s) { return fill(p, n, v, s); }
 
+// ----------------------------------------------------------- lists to send
+
+ro_status SentList::wait() {
+    const int was = state;
+    state = kIdle;
+    if (was == kMarked) RO_HIP(hipEventSynchronize(used));
+    if (was == kSent) RO_HIP(hipStreamSynchronize(stream));
+    return RO_OK;
+}
+
+ro_status SentList::make(size_t n, hipStream_t s, uint8_t **out) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    RO_HIP(hipStreamIsCapturing(s, &cap));
+    RO_CHECK(cap == hipStreamCaptureStatusNone, RO_E_STATE, "the stream is being captured");
+    ro_status st = wait();
+    if (st) return st;
+    if (!used) RO_HIP(hipEventCreateWithFlags(&used, hipEventDisableTiming));
+    try {
+        buf.resize(n);
+    } catch (...) {
+        RO_CHECK(false, RO_E_NOMEM, "out of host memory");
+    }
+    stream = s;
+    *out = buf.data();
+    return RO_OK;
+}
+
+ro_status SentList::send(void *dev) {
+    state = kSent;
+    RO_HIP(hipMemcpyAsync(dev, buf.data(), buf.size(), hipMemcpyHostToDevice, stream));
+    return RO_OK;
+}
+
+void SentList::mark() {
+    // (without the event the next list waits for the stream)
+    if (state == kSent && hipEventRecord(used, stream) == hipSuccess) state = kMarked;
+}
+
 // ------------------------------------------------------ block-level helpers
 
 // Exclusive prefix sum over the block (blockDim.x == 256, 4 waves of 64):
@@ -691,7 +729,7 @@ __global__ void __launch_bounds__(256) k_scatter(const SelState *__restrict__ st
 }
 
 ro_status stream_bricks_device(ro_cache *c, uint32_t frame, uint32_t n_new, uint32_t n_touch,
-                               const uint32_t *batch, const void *staged, hipStream_t s, uint32_t *result) {
+                               const void *staged, hipStream_t s, uint32_t *result) {
     const VolGeo &g = c->vol->g;
     uint8_t *sc = (uint8_t *)c->b.scratch;
     const uint32_t S = c->desc.n_slots;
@@ -703,11 +741,15 @@ ro_status stream_bricks_device(ro_cache *c, uint32_t frame, uint32_t n_new, uint
     const uint32_t *uploads = (uint32_t *)(sc + c->sc.batch), *srcidx = uploads + n_new, *touch = srcidx + n_new;
     uint32_t *cand_slot = (uint32_t *)(sc + c->sc.outpairs);  // at least n_slots words
     if (n_new + n_touch == 0) return RO_OK;
-    RO_HIP(hipMemcpyAsync(sc + c->sc.batch, batch, 4 * (2 * (size_t)n_new + n_touch), hipMemcpyHostToDevice, s));
+    ro_status st = c->batch.send(sc + c->sc.batch);
+    if (st) return st;
     hipLaunchKernelGGL(k_touch_clear, dim3((std::max(n_touch, kSelHistWords) + 1023) / 1024), dim3(1024), 0, s,
                        c->b.stamps, touch, n_touch, frame, hist, sel);
     RO_HIP(hipGetLastError());
-    if (n_new == 0) return RO_OK;  // the copy from pageable memory is complete when its call returns
+    if (n_new == 0) {
+        c->batch.mark();
+        return RO_OK;
+    }
     const uint32_t cap = std::min(n_new + kSelSlack, S);
     const uint32_t nb = std::min((S + kSelThreads - 1) / kSelThreads, kSelBlocks);
     // no pass where all slots fit the candidates: the rank takes them apart
@@ -733,6 +775,7 @@ ro_status stream_bricks_device(ro_cache *c, uint32_t frame, uint32_t n_new, uint
     RO_HIP(hipGetLastError());
     RO_HIP(hipMemcpyAsync(result, sel, 4 * (kSelStateWords + (size_t)n_new), hipMemcpyDeviceToHost, s));
     RO_HIP(hipStreamSynchronize(s));
+    c->batch.done();
     result[0] = ((const SelState *)result)->keff;
     memmove(result + 1, result + kSelStateWords, 4 * (size_t)result[0]);
     return RO_OK;
