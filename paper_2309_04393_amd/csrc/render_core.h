@@ -573,6 +573,7 @@ __device__ __forceinline__ void render_rays(const RenderArgs &A, UnitQueue<P> &s
     // level index (<< 24) they share
     uint32_t npend = 0, pmask = 0, pkey = 0;
     uint32_t fpend = 0, fmask = 0, fkey = 0;  // those of the visit before, to be added
+    uint32_t smiss = 0;            // with rates: this lane's sample's missing channels, to be added
     int lc[3] = {-1, -1, -1};      // L0 origin of the last visited leaf or skipped node (none yet)
     int lcd = 0;                   // its depth: the nodes above it are known not to be skipped
     uint32_t last_key = kInvalid;  // (level, cell) of the last visit when uniform
@@ -749,10 +750,13 @@ __device__ __forceinline__ void render_rays(const RenderArgs &A, UnitQueue<P> &s
     // atomics leave the XCD, and on a frame with few bricks every ray of a
     // wave, and the next units' rays, add to the same counters: one atomic per
     // ray, visit and channel took 26 ms of a 960 x 540 frame of a 16-channel
-    // slide without bricks, one per wave and brick 7.
+    // slide without bricks, one per wave and brick 7.  (With rates the samples
+    // of a ray differ in the channels that take part, so each is added by
+    // itself: a 1080p frame of 8 channels, half of the bricks resident, 250 ms
+    // with an atomic per sample and channel, 25 now.)
     // (Called by the whole wave: every lane takes part.)
     auto flush = [&](uint32_t n_own, uint32_t mask, uint32_t key_own) {
-        uint64_t todo = __ballot(n_own != 0 && mask != 0 && q == 0);
+        uint64_t todo = __ballot(n_own != 0 && mask != 0);
         const int ln = (int)(threadIdx.x & 63u);
         while (todo) {
             const int first = __builtin_ctzll(todo);
@@ -1456,19 +1460,9 @@ __device__ __forceinline__ void render_rays(const RenderArgs &A, UnitQueue<P> &s
             npend += taken;
         } else {
             // misses and stamps per sample (a visit's samples differ in which
-            // channels take part)
+            // channels take part); the wave adds the misses after the samples
             const bool counts = P == 1 || (uint32_t)q < taken;
-            uint32_t mp = counts ? missmask & part : 0u;
-            while (mp) {
-                const int j = __builtin_ctz(mp);
-                mp &= mp - 1u;
-                const ChanLds ch = s_ch[j];
-                const LevLds lv = s_lv[min(max(lod, ch.lo), ch.hi)];
-                atomicAdd(&gmem(A.cnt)[brick_dense(lv, (uint32_t)ch.c, A.per_channel, lc[0] >> field(lv.sh, 0),
-                                                   lc[1] >> field(lv.sh, 1), lc[2] >> field(lv.sh, 2))],
-                          1u);
-                ++st_miss;
-            }
+            smiss = counts ? missmask & part : 0u;
             uint32_t sp = counts ? have & part & ~stamped : 0u;
             const uint32_t now = all_of_ray(sp);
             while (sp) {
@@ -1509,7 +1503,7 @@ __device__ __forceinline__ void render_rays(const RenderArgs &A, UnitQueue<P> &s
     while (true) {
         const bool fin = has && (done || k > kend);
         if (__any(fin)) {
-            flush(fin ? npend : 0u, pmask, pkey);
+            flush(fin && q == 0 ? npend : 0u, pmask, pkey);
             if (fin) finish();
         }
         if (!__any(has)) {
@@ -1538,12 +1532,16 @@ __device__ __forceinline__ void render_rays(const RenderArgs &A, UnitQueue<P> &s
             wave_sync();
             if (wv) visit();
             wave_sync();
-            flush(fpend, fmask, fkey);
+            flush(q == 0 ? fpend : 0u, fmask, fkey);
             fpend = 0;
             continue;
         }
         ++st_iters;  // a stepping iteration of the wave (lane busy or idle)
         if (ws) sample();
+        if (rates) {
+            flush(smiss ? 1u : 0u, smiss, pkey);
+            smiss = 0;
+        }
     }
     // the table's sums
     for (int i = 0; i < kMissEntries; ++i) {
