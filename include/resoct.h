@@ -167,7 +167,7 @@ ro_status ro_read_requests(ro_cache *c, uint32_t cap, uint32_t *ids_host, uint32
  * work space in a fixed device array of the library instead of the cache's
  * scratch buffer.  Allocates nothing.  Limits: cap <= RO_NOALLOC_MAX_PAIRS
  * and a volume of at most 2^26 bricks; beyond them RO_E_CAPACITY and nothing
- * is enqueued.  The array (about 2.5 MiB) exists once per GPU until the
+ * is enqueued.  The array (about 3 MiB) exists once per GPU until the
  * process ends and keeps the last call's contents; every call on a GPU uses
  * that GPU's copy, so calls that overlap on one GPU (other threads or
  * streams) race.  Synchronises. */

@@ -8,7 +8,8 @@
 // Sample positions and every integer decision derived from them (box, leaf,
 // brick, level) are computed in FP64; interpolation, transfer functions and
 // the channel mix in FP32; the compositing state in FP64, sample after
-// sample, so the image does not depend on the number of lanes.  Per ray, the
+// sample, so the image is the same bit for bit with one lane per ray (the
+// diagnostic outputs) and with four.  Per ray, the
 // state of the current (leaf, level) visit is cached: which channels are
 // empty there, the slot each channel samples, and which channels miss their
 // desired brick; misses are summed while the missing channels and their
@@ -33,16 +34,26 @@ namespace ro {
 // 512 lanes 5 % slower on both (with one lane per ray).
 //
 // What bounds the frame kernel: on the 16-channel 1080p frame (1024 x 1024 x
-// 192 voxels, half a voxel per pixel, 8.4e8 ray samples) 42.5 ms against 58
+// 192 voxels, half a voxel per pixel, 8.4e8 ray samples) 41.0 ms against 58
 // with one lane per ray in lockstep.  Vector instructions fill two thirds of
 // the issue slots and the address and tag units are busy throughout: 1.2e9
 // gathers of 64 lanes, each 18.5 tag lookups.  Gathers of single 16-bit
 // voxels (8 per channel instead of 4) touch as many lines each and took
 // 70 ms; aligned addresses alone (wrong voxels) save 2 %.  Frames of a few
 // thousand units are bound by their longest rays: four lanes per ray cut
-// those (455 x 256, 16 channels: 10.0 ms -> 2.1; 512 x 512, 4 channels:
-// 5.0 -> 2.2; 64 x 64, one channel: 0.59 -> 0.18, and 0.13 with its units in
-// parts, see render_device).
+// those (512 x 512, 4 channels: 5.0 ms -> 2.1; 24 x 24, 16 channels: 8.2 ->
+// 1.16, and 0.73 with its units in parts, see render_device; 64 x 64, one
+// channel: 0.58 -> 0.13).  Rays that end at once are bound by vector
+// instructions: a unit of 16 of them is 1300 to 1900, 400 of them its set-up.
+// A full-HD frame of rays that all end within eight samples is what one lane
+// per ray was better at (4 channels, 2.4 samples a pixel 0.34 ms, 0.36 now; 1
+// channel, 7.6 samples 0.45 and 0.53; 16 channels, 0.6 samples 0.35 and 0.43).
+//
+// Scratch: none with up to eight channels but for 8 bytes a lane in one
+// instance; with 16 channels 28 to 32, three addresses that are read where
+// sums of misses leave for the counters, not in the channel loop.  Render-and-
+// skip keeps 28 to 60, per-channel rates 16 to 56 (none with one channel), the
+// diagnostic kernel 24 to 60.
 
 // Persistent grid (one workgroup per CU) whose waves take units of pixels
 // from a device counter independently of each other, so a CU never waits
@@ -78,7 +89,7 @@ __global__ void __launch_bounds__(kRenderLanes) __attribute__((amdgpu_waves_per_
     uint32_t st[7] = {0, 0, 0, 0, 0, 0, 0};
     render_rays<NV, BPV, AOV, EC, EXT, P>(A, q, s_tf, s_ch, &s_par, s_runs, s_lv, s_nd, st);
     if (A.stats) {
-        // every lane of the workgroup is here: reduce over the wave, one atomic per wave
+        // whole waves are here: reduce over the wave, one atomic per wave
 #pragma unroll
         for (int j = 0; j < 7; ++j) {
             uint32_t v = st[j];
@@ -318,18 +329,18 @@ ro_status render_device(ro_octree *tr, const ro_frame_desc *fd, float *rgba, hip
     Q.counter = (uint32_t *)((uint8_t *)tr->b.scratch + tr->scratch_bytes - kFrameTail);
     Q.grid = dim3((unsigned)(ncu > 0 ? ncu : 256));
     // a frame with fewer units of pixels than the chip has waves uses as many
-    // waves of each workgroup as it has units per CU (64 x 64 pixels: 0.37 ms
-    // against 0.49 ms on the few CUs that came first), and deals its blocks in
-    // smaller chunks, whole 32 x 32 tiles of them
+    // waves of each workgroup as it has units per CU (64 x 64 pixels: 0.135 ms,
+    // 0.149 where the waves that come first take them all), and deals its
+    // blocks in smaller chunks, whole 32 x 32 tiles of them
     const int p = lanes_per_ray((fd->flags & (RO_RENDER_AOV | RO_RENDER_BRICKS | RO_RENDER_NODES)) != 0);
     const uint32_t n_units = Q.n_blocks * (uint32_t)p;
     Q.split = 0;
     // and where that leaves SIMDs without a wave, a wave takes a part of a
     // unit's pixels: fewer rays in a wave have fewer steps that are not their
     // own (one part against several up to a wave per SIMD, one channel 24 x
-    // 24 and 64 x 64: 140 us to 110, 169 to 133; 16 channels 24 x 24: 2.28 ms
-    // to 1.44; two waves per SIMD: 64 x 64 with 16 channels 10 % less, but
-    // 128 x 128 10 % more)
+    // 24 and 64 x 64: 173 us to 107, 170 to 135; 16 channels 24 x 24: 1.16 ms
+    // to 0.73; up to two waves per SIMD took 10 % less for 64 x 64 with 16
+    // channels, but 10 % more for 128 x 128)
     if (p == 4)
         while (Q.split < 4 && ((uint64_t)n_units << (Q.split + 1)) <= (uint64_t)Q.grid.x * 4) ++Q.split;
     const uint32_t per_cu = ((n_units << Q.split) + Q.grid.x - 1) / Q.grid.x;

@@ -258,9 +258,8 @@ struct RayLds {
     __device__ __forceinline__ double &inverse(int a) { return inv[a * kRays]; }
 };
 
-// Pixel source of the stepping loop: a wave takes its 64 / P pixels at once
-// (8 x 8 of them for P = 1, 4 x 4 for P = 4) and the next ones when all its
-// rays have ended.
+// Pixel source of the stepping loop: a wave takes a unit of 64 / P pixels (8 x
+// 8 for P = 1, 4 x 4 for P = 4) and the next one when all its rays have ended.
 //
 // Units of pixels are handed out by device counters (the units of an 8 x 8
 // block, the blocks of a 32 x 32 tile are consecutive, tiles in raster
@@ -274,10 +273,11 @@ struct RayLds {
 // work on separate neighbouring chunks (their L2s hold different lines)
 // while all of them still sweep the image together (the Infinity Cache is
 // shared).  Counter reads and the unit are wave-uniform.
+//
 // Per-XCD block queues: blocks are dealt to them in chunks of RO_CHUNK
 // consecutive blocks (16 chunks per queue at 1080p).  On the 16-channel
 // 1080p frame chunks of 256 measured 0.6 % faster than 64, 16 0.7 % slower,
-// 1024 as 256, and 4096 (one region per XCD) 4 % slower.
+// 1024 as 256, and 4096 (one region per XCD) 4 % slower (with one lane per ray).
 #ifndef RO_QUEUES
 #define RO_QUEUES 8
 #endif
@@ -285,10 +285,9 @@ struct RayLds {
 #define RO_CHUNK 256
 #endif
 // Words between queue counters: 256 bytes, so that they are in different
-// memory channels.  At 32 bytes a light 1080p frame (ten samples a pixel, a
-// device atomic per 4 x 4 pixels) waited for the atomics of one channel: 4
-// channels far away 1.43 ms to 1.09, homogeneous nodes 0.84 to 0.39.  (Four units per atomic relieve it too, but the units of a block then
-// run one after another in one wave: 43 ms to 51 for 16 channels.)
+// memory channels.  At 32 bytes a 1080p frame of short rays with an atomic
+// per unit waited for the atomics of one channel (homogeneous nodes 0.84 ms,
+// 0.39 at 256; with several units per atomic 0.37 and 0.35).
 constexpr int kQueueStride = 64;
 // Units that a workgroup takes at once, by the units that the image has per
 // wave.  One atomic for several units leaves the queues' memory channels alone
@@ -1487,14 +1486,17 @@ __device__ __forceinline__ void render_rays(const RenderArgs &A, UnitQueue<P> &s
     // of the wave (as of when the limit was last set).  The distance is in
     // whole groups of P samples, 1.25 of them per sample that a pixel's
     // footprint spans: where neighbouring rays are far apart their samples
-    // share few lines anyway and fewer waits count more (one group on the
-    // 16-channel 1080p frame at half a voxel a pixel: 42.5 ms, two groups
-    // 44.7; on a 455 x 256 frame of the same channels at three voxels a pixel
-    // one group 2.6 ms, five 2.1).
+    // share few lines anyway and fewer waits count more (this against always
+    // one group: 16 channels 1080p at half a voxel a pixel, where it is one
+    // group, 41.0 ms both, and 42.0 with another group; 512 x 512, 4 channels,
+    // two voxels a pixel 2.10 against 2.35; 720p, 8 channels, adaptive 3.25
+    // against 4.27).
     // Visits wait until kVisitLanes lanes need one or no ray can sample: a
     // visit is a chain of dependent loads and several hundred instructions,
-    // whatever the number of lanes that take part (512 x 512, 4 channels:
-    // every visit at once 2.7 ms, at four lanes 2.6, 16: 2.2, 24: 2.15).
+    // whatever the number of lanes that take part (every visit at once, at 8,
+    // 16 and 24 lanes: 512 x 512, 4 channels 2.42 ms, 2.33, 2.15, 2.10; 720p,
+    // 8 channels, adaptive 3.64, 3.46, 3.31, 3.25; 455 x 256, 16 channels,
+    // six voxels a pixel 2.68, 2.62, 2.78, 2.99).
     constexpr int kVisitLanes = 24;
     double klim = -1.0;
     if ((threadIdx.x & 63u) < kMissEntries) lds.miss[3 * (threadIdx.x & 63u) + 1] = 0;

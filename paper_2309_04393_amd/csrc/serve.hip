@@ -70,9 +70,9 @@ __device__ __forceinline__ void serve_units(const RenderArgs &sA, UnitQueue<kSer
 
 // Renders work item `seg` (kSegBlocks consecutive 8 x 8-pixel blocks, the
 // blocks of a 32 x 32 tile consecutive, tiles in raster order) of the
-// request staged in sA.  The workgroup's waves take the item's blocks from
-// the LDS counter *s_next (zero on entry) one at a time, so waves that
-// finish early take more blocks.
+// request staged in sA.  The workgroup's waves take the item's 4 x 4-pixel
+// units from the LDS counter *s_next (zero on entry) one at a time, so waves
+// that finish early take more of them.
 template <int NV, int BPV, int EC>
 __device__ __forceinline__ void serve_item(const RenderArgs &sA, uint32_t seg, uint32_t *s_next, const float4 *s_tf,
                                            const ChanLds *s_ch, const ChanPar<NV> *s_par, const uint32_t *s_runs,
@@ -131,7 +131,11 @@ __device__ __forceinline__ uint32_t next_request(const ServeHeader *__restrict__
 // with all workgroups on each request in turn that was what a batch of short
 // rays took (12 requests, 4 channels, rays of three samples: 1.47 ms, 0.96
 // with places; 16 channels 1.83 and 1.25; long rays 43.5 and 41.6).  Twice or
-// half as many places are within 10 % of this.
+// half as many places are within 10 % of this.  (The instances show 15 to 28
+// spilled registers: values of the change of request, stored once and read
+// back per request, and two reads where sums of misses leave for the counters.
+// With the descriptor read by scalar loads instead of from LDS they are as
+// many and the batches 1 % faster.)
 template <int NV, int BPV, int EC>
 __global__ void __launch_bounds__(kRenderLanes) __attribute__((amdgpu_waves_per_eu(kRenderLanes / 256)))
     k_serve(const ServeHeader *__restrict__ hdr, const RenderArgs *__restrict__ descs, uint32_t *counters,
