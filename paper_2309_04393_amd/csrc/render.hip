@@ -8,13 +8,13 @@
 // Sample positions and every integer decision derived from them (box, leaf,
 // brick, level) are computed in FP64; interpolation, transfer functions and
 // the channel mix in FP32; the compositing state in FP64, sample after
-// sample, so the image is the same bit for bit with one lane per ray (the
-// diagnostic outputs) and with four.  Per ray, the
-// state of the current (leaf, level) visit is cached: which channels are
-// empty there, the slot each channel samples, and which channels miss their
-// desired brick; misses are summed while the missing channels and their
-// desired bricks stay the same, over the rays of a wave, before they reach
-// the device counters.
+// sample, so the image does not depend on the number of lanes (one per ray,
+// the diagnostic outputs, and four gave the same bits in 28 frames compared).
+// Per ray, the state of the current (leaf, level) visit is cached: which
+// channels are empty there, the slot each channel samples, and which channels
+// miss their desired brick; misses are summed while the missing channels and
+// their desired bricks stay the same, over the rays of a wave, before they
+// reach the device counters.
 //
 // Every table a lane indexes with a lane-dependent value (channel
 // parameters, zero-alpha runs, per-level brick grid and LOD thresholds,

@@ -293,8 +293,9 @@ constexpr int kQueueStride = 64;
 // wave.  One atomic for several units leaves the queues' memory channels alone
 // (1080p with nothing in view: 0.30 ms with one, 0.24 with two, 0.15 with
 // four), and neighbouring waves work on neighbouring pixels (4 channels far
-// away 1.20, 0.99, 0.95; a batch of twelve requests 51.8, 44.8, 44.8).  But
-// the frame waits for the workgroup whose units are the heavy ones: far away
+// away 1.20, 0.99, 0.95; a batch of twelve requests 51.8, 44.8, 44.8; a
+// fly-through of 16 channels 84.3, 84.0, 83.4, though the fabric brings 124,
+// 143, 166 GB a frame).  But the frame waits for the workgroup whose units are the heavy ones: far away
 // 1.29 with eight; 720p, 8 channels, 19 units a wave: 3.28, 3.28, 3.35; 512 x
 // 512, 5 units a wave: 2.10 with one, 2.25 with four.
 constexpr uint32_t kMaxTake = 4;
